@@ -445,14 +445,15 @@ pp_status pp_ppr_adjoint_unrolled(pp_graph g, int32_t k, const int32_t* sources,
 
 /* ------------------------------------------------------- triangle counting */
 /* Workspace bytes of pp_tc_run for graph g (device, caller-owned, 256-byte
- * aligned). */
+ * aligned): the count of every edge (4 bytes each) and the row partials. */
 size_t pp_tc_workspace_bytes(pp_graph g);
 
 /* Triangles per vertex (Sec. 3.2; the NodeIterator listing of Sec. 4.2):
  * tc[v] = 1/2 * #{(w1, w2) : w1, w2 in N(v), w2 in N(w1)}, N = the graph's
  * CSR rows (out-neighbours), which must be in strictly ascending order (the
- * call fails with PP_E_GRAPH otherwise; tc is then undefined).  The counts of
- * one edge (v, w1) are found by intersecting the two rows.  dir = PP_PULL
+ * call fails with PP_E_GRAPH otherwise; tc is then undefined).  The count of
+ * an edge (v, w1) is the size of the two rows' intersection, formed once for
+ * both directions of a symmetric edge.  dir = PP_PULL
  * credits v (each counter written once, no atomics); PP_PUSH credits w1 with
  * a 64-bit integer fetch-and-add.  On a symmetric graph both give the number
  * of triangles containing each vertex.  tc: int64[n] device, caller ids.

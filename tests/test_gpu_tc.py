@@ -1,6 +1,7 @@
 """Triangle counting, pushing and pulling forms, against the oracle (exact)."""
 import numpy as np
 import pytest
+import scipy.sparse as sp
 import torch
 
 import graphgen as gg
@@ -87,3 +88,42 @@ def test_unsorted_rows_are_rejected():
     g = pp.Graph(bad, relabel=False)
     with pytest.raises(pp.PPError):
         pp.triangles(g, pp.PP_PULL)
+
+
+@pytest.mark.parametrize("n,directed", [(300, False), (300, True), ((1 << 20) + 77, False), ((1 << 20) + 77, True)])
+def test_owner_rows_at_the_class_edges(n, directed):
+    # dense blobs whose row lengths straddle the lane (16), wavefront (64) and
+    # bitmap classes, on ids that reach past one bitmap window (2^20) when n
+    # does; directed: about half the edges have no edge back
+    rng = np.random.default_rng(n + directed)
+    src, dst = [], []
+    at = np.sort(rng.choice(n, size=280, replace=False))
+    at[:2], at[-2:] = (0, 1), (n - 2, n - 1)
+    for size in (15, 16, 17, 18, 33, 64, 65, 66, 67, 130, 270):
+        ids = rng.choice(at, size=size, replace=False)
+        a, b = np.meshgrid(ids, ids)
+        keep = (a < b) if not directed else (a != b) & (rng.random(a.shape) < 0.7)
+        src += a[keep].tolist()
+        dst += b[keep].tolist()
+    host = gg.from_edges(n, src, dst, not directed, name=f"blobs{n}{'d' if directed else ''}")
+    if not directed:
+        _same(host)
+        return
+    host.ensure_transpose()
+    A = sp.csr_matrix((np.ones(host.nnz, dtype=np.int64), host.idx, host.off), shape=(n, n))
+    C = A.multiply(A @ A.T)  # common out-neighbours of the ends of every edge
+    np.testing.assert_array_equal(_tc(host, pp.PP_PULL), np.asarray(C.sum(1)).ravel() // 2)
+    np.testing.assert_array_equal(_tc(host, pp.PP_PUSH), np.asarray(C.sum(0)).ravel() // 2)
+
+
+def test_self_loops_count_as_before():
+    # a stored self-loop (v, v) meets v's whole row
+    off = np.array([0, 3, 5, 7], dtype=np.int64)
+    idx = np.array([0, 1, 2, 0, 2, 0, 1], dtype=np.int32)
+    host = gg.HostGraph(3, off, idx, True, name="loop")
+    host.in_off, host.in_idx = off, idx
+    rows = [set(idx[off[v]:off[v + 1]].tolist()) for v in range(3)]
+    pull = [sum(len(rows[v] & rows[w]) for w in rows[v]) // 2 for v in range(3)]
+    push = [sum(len(rows[v] & rows[w]) for v in range(3) if w in rows[v]) // 2 for w in range(3)]
+    assert _tc(host, pp.PP_PULL).tolist() == pull
+    assert _tc(host, pp.PP_PUSH).tolist() == push
