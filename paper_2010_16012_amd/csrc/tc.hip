@@ -13,7 +13,7 @@
 // written to both slots without a search.  k_tc_slices then sums the counts of
 // each row's slots; a slot without one (a directed edge to a longer row that
 // has no edge back) is intersected there.  What bounds it: LDS bit tests and
-// the barriers between a slice's rows.  R-MAT 16 (163M tests): 0.44 ms a call,
+// the barriers between a slice's rows.  R-MAT 16 (163M tests): 0.35 ms a call,
 // against 20.3 ms with a wavefront per 256 edges that searched or merged both
 // directions of every pair in global memory.
 //
@@ -37,7 +37,11 @@ constexpr int32_t kTcLight = 16;   // lane-serial intersections up to this short
 // tests are under 1% of the total on skewed graphs, and a bitmap costs the
 // workgroup three barriers); longer ones become a bitmap.
 constexpr int32_t kTcMid = 64;
-constexpr int32_t kTcGroup = 16;            // lanes that stream one shorter row
+// Lanes that stream one shorter row, and loads each keeps in flight.  R-MAT 16
+// / 18, a call: 16 x 4 0.446 / 2.50 ms, 16 x 8 0.389 / 2.04, 32 x 4 0.380 /
+// 2.20, 32 x 8 0.351 / 1.86, 64 x 4 0.402 / 2.22, 8 x 4 0.523 / 3.06.
+constexpr int kTcGroup = 32;
+constexpr int kTcLoads = 8;
 constexpr int32_t kTcWindow = 1 << 20;      // vertices one bitmap covers (128 KB of LDS)
 constexpr int32_t kTcMaxWaves = 16;
 
@@ -145,7 +149,7 @@ __device__ __forceinline__ bool tc_owned(int32_t dv, int32_t v, int32_t dw, int3
 // adds the entries that `hit` accepts to the edge.
 template <typename F>
 __device__ __forceinline__ void tc_stream(const int32_t* idx, TcEdge& ed, int32_t b, int32_t e, int gl, F hit) {
-    constexpr int U = 4;
+    constexpr int U = kTcLoads;
     int32_t cnt = 0, back = -1;
     const int32_t v = ed.v;
     for (int32_t j0 = b + gl; j0 < e; j0 += U * kTcGroup) {
