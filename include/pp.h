@@ -146,7 +146,10 @@ pp_status pp_set_push_tuning(int32_t hot, int32_t push_blocks);
  * store, and a second kernel sums every bin in LDS; the slice sizes come from
  * one counting walk of the sweep's static work assignment at registration.
  * No global atomics remain (the remote updates of Sec. 5's
- * Partition-Awareness, buffered instead of applied one by one).  Needs hot >
+ * Partition-Awareness, buffered instead of applied one by one).  On graphs of
+ * at least 8192 vertices and 65536 edges (and at most 2^25 vertices) every
+ * update, hot targets included, is buffered by target block instead, at a place
+ * fixed at registration, and summed there in slot order.  Needs hot >
  * 0; its workspace (8 bytes per edge plus tables) is part of
  * pp_graph_workspace_bytes.  Takes effect at the next pp_graph_create. */
 pp_status pp_set_push_bins(int32_t on);
@@ -198,9 +201,13 @@ pp_status pp_graph_slices(pp_graph g, int32_t* info);
  *   y[u] = (1-f)/n + f * sum over edges (v,u) of P_uv * x[v],
  * P_uv = 1/d(v) (unweighted) or w(v->u)/s(v) (weighted); a vertex with
  * d(v) = 0 contributes nothing.  x, y: float[n], distinct.  pp_pr_push
- * scatters along CSR rows with FP32 atomics (nnz atomic adds per call; the
- * summation order, hence the last bits, may vary between runs); pp_pr_pull
- * gathers along CSC rows with no atomics (bit-reproducible).  f in [0, 1).
+ * sends every edge's value to its target: through the target block's buffer
+ * (graphs of at least 8192 vertices and 65536 edges with pp_set_push_bins(1);
+ * fixed summation order), else by scattering along the CSR rows with the
+ * privatised and binned or atomic updates of pp_set_push_tuning and
+ * pp_set_push_bins (the summation order, hence the last bits, may vary between
+ * runs).  pp_pr_pull gathers along CSC rows with no atomics
+ * (bit-reproducible).  f in [0, 1).
  * Uses the graph's scratch: calls on one graph must be ordered. */
 pp_status pp_pr_push(pp_graph g, const float* x, float* y, float f, void* stream);
 pp_status pp_pr_pull(pp_graph g, const float* x, float* y, float f, void* stream);

@@ -275,26 +275,31 @@ __global__ void k_gather_weights(int64_t nnz, const float* __restrict__ csr_w, c
     if (j < nnz) csc_w[j] = csr_w[map[j]];
 }
 
-// Largest out- and in-row length.
+// Largest out- and in-row length, the last vertex with in-edges, and how many
+// vertices have none.  A workgroup takes many vertices: one atomic each from
+// every wavefront of a large graph queued for 2.2 ms at n = 2^22.
 __global__ void k_max_deg(int32_t n, const int32_t* __restrict__ off, const int32_t* __restrict__ in_off,
                           int32_t* __restrict__ out) {
-    const int32_t v = blockIdx.x * blockDim.x + threadIdx.x;
-    int32_t a = 0, b = 0, c = 0;  // c: v + 1 for a vertex with in-edges
-    if (v < n) {
-        a = row_len(off, v);
-        b = row_len(in_off, v);
-        c = (b > 0) ? v + 1 : 0;
+    int32_t a = 0, b = 0, c = 0, z = 0;  // c: v + 1 for a vertex with in-edges
+    for (int32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gridDim.x * blockDim.x) {
+        const int32_t d = row_len(in_off, v);
+        a = max(a, row_len(off, v));
+        b = max(b, d);
+        if (d > 0) c = v + 1;
+        else ++z;
     }
 #pragma unroll
     for (int s = 32; s > 0; s >>= 1) {
         a = max(a, __shfl_xor(a, s));
         b = max(b, __shfl_xor(b, s));
         c = max(c, __shfl_xor(c, s));
+        z += __shfl_xor(z, s);
     }
     if ((threadIdx.x & 63) == 0) {
         atomicMax(&out[0], a);
         atomicMax(&out[1], b);
         atomicMax(&out[2], c);
+        atomicAdd(&out[3], z);
     }
 }
 
@@ -349,7 +354,7 @@ struct WsLayout {
     size_t inv_s, out_deg, pull_list, push_list, buf0, buf1, buf2, csc_w, csc_row, split_tab, split_part, hot_part, err,
         tiles, keys, perm, iperm, r_csr_off, r_csc_off, r_csr_idx, r_csc_idx, r_csr_w, sl_idx, sl_prow,
         sl_units, sl_segs, sl_wg, sl_part, sl_cpart, sl_cbeg, pb_base, pb_cnt, pb_fill, pb_units, pb_ulo, pb_pairs,
-        pb_part, total;
+        pb_part, rt_edges, rt_tables, total;
     int32_t split_cap;
     int64_t sl_rows_cap, sl_slices_cap, sl_pairs_cap, sl_units_cap, sl_chunks_cap, sl_idx_cap;
 };
@@ -406,8 +411,14 @@ static WsLayout layout(int32_t n, int64_t nnz, uint32_t flags, const Tuning& t, 
         L.pb_fill = take(slices * 4);
         L.pb_units = take(units * 3 * 4);
         L.pb_ulo = take(((size_t)push_bins_cap(n) + 1) * 4);
-        L.pb_pairs = take(nz * 8);
+        L.pb_pairs = take(std::max(nz * 8, route_possible(n, nnz) ? route_edge_bytes(n, nnz) : 0));
         L.pb_part = take(units * kPushBinW * 4);
+    }
+    if (route_possible(n, nnz)) {
+        // a routed graph never runs the binned push: its pairs hold the
+        // routed sweep's per-edge arrays instead
+        L.rt_edges = push_binned(t, n) ? L.pb_pairs : take(route_edge_bytes(n, nnz));
+        L.rt_tables = take(route_table_bytes(n, nnz));
     }
     L.err = take(64 * 4);
     const size_t tiles = std::max<size_t>((size_t)ceil_div(n, kTile) * kMaxKeys, (size_t)ceil_div(n, kScanTile) + 1);
@@ -498,7 +509,7 @@ static pp_status partition(int32_t n, int nkeys, const uint8_t* keys, int32_t* t
     return PP_OK;
 }
 
-static pp_status exclusive_scan(int32_t n, const int32_t* in, int32_t* out, int32_t* tsum, int32_t* total,
+pp_status exclusive_scan(int32_t n, const int32_t* in, int32_t* out, int32_t* tsum, int32_t* total,
                                 hipStream_t st) {
     const int32_t tiles = std::max(ceil_div(n, kScanTile), 1);
     hipLaunchKernelGGL(k_scan_tiles, dim3(tiles), dim3(256), 0, st, n, in, out, tsum);
@@ -1082,13 +1093,13 @@ PP_EXPORT pp_status pp_graph_create(int32_t n, int64_t nnz, const int32_t* csr_o
                        d.csc_off, d.csc_row);
     hipLaunchKernelGGL(k_degrees, dim3(ceil_div(n, 256)), dim3(256), 0, st, n, d.csr_off, d.csr_w, d.out_deg,
                        d.inv_s);
-    hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, st, 3, d.err + 48);
-    hipLaunchKernelGGL(k_max_deg, dim3(ceil_div(n, 256)), dim3(256), 0, st, n, d.csr_off, d.csc_off, d.err + 48);
+    hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, st, 4, d.err + 48);
+    hipLaunchKernelGGL(k_max_deg, dim3(std::min(ceil_div(n, 256), 512)), dim3(256), 0, st, n, d.csr_off, d.csc_off, d.err + 48);
     {
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return fail(hip_error(e, "graph degree kernels"));
     }
-    int32_t maxd[3];
+    int32_t maxd[4];
     {
         hipError_t e = hipMemcpyAsync(maxd, d.err + 48, sizeof(maxd), hipMemcpyDeviceToHost, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);
@@ -1097,6 +1108,7 @@ PP_EXPORT pp_status pp_graph_create(int32_t n, int64_t nnz, const int32_t* csr_o
     g->max_out_deg = maxd[0];
     g->max_in_deg = maxd[1];
     g->in_active = maxd[2];
+    g->empty_in = maxd[3];
     {
         int dev = 0, cus = 0, lds = 0, lds_cu = 0;
         hipError_t e = hipGetDevice(&dev);
@@ -1125,6 +1137,11 @@ PP_EXPORT pp_status pp_graph_create(int32_t n, int64_t nnz, const int32_t* csr_o
     }
     if (d.pb_base) {
         s = build_push_bins(g, st);
+        if (s != PP_OK) return fail(s);
+    }
+    if (route_possible(n, nnz)) {
+        hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, st, 1, d.err + 41);
+        s = build_route(g, at(L.rt_edges), at(L.rt_tables), st);
         if (s != PP_OK) return fail(s);
     }
     *out = g;

@@ -162,6 +162,33 @@ inline int32_t push_units_cap(int32_t n, int64_t nnz) {
     return (int32_t)std::min<int64_t>(kPushBinUnits, nnz / kPushBinMinUnit + 1) + push_bins_cap(n);
 }
 
+// Routed sweep (route.hip): source slices of kRouteWidth ids, target blocks of
+// about kRouteEdges in-edge slots (a block ends with a row unless the row has
+// more than kRouteSlack slots).
+constexpr int kRouteShift = 15;
+constexpr int32_t kRouteWidth = 1 << kRouteShift;
+constexpr int32_t kRouteEdges = 16384;
+constexpr int32_t kRouteSlack = 1024;
+constexpr int32_t kRouteSlots = kRouteEdges + kRouteSlack;
+constexpr int32_t kRouteMaxSlices = 1024;
+// Pushes are routed from here on (a step, global -> routed: R-MAT 14 54.7 ->
+// 19.9 us, ER n = 30,001 50.8 -> 17.3, R-MAT 20 260 -> 107, ER n = 2M 611 -> 90).
+constexpr int32_t kRouteMinN = 8192;
+constexpr int64_t kRouteMinEdges = 1 << 16;
+
+struct RouteBlock {
+    int32_t p0, p1;  // in-edge slots [p0, p1)
+    int32_t r0, r1;  // rows r0..r1 own them
+};
+
+struct RoutePlan {
+    int32_t entries = 0;
+    int32_t slices = 0;
+    int32_t blocks = 0;  // 0: no routed sweep
+    bool split = false;  // some rows cross blocks
+    bool pull = false;   // the pulling form takes it too
+};
+
 // Work decomposition of one binned sweep launch: every bin owns a contiguous
 // range of work units; heavy bins come first so the longest rows start first.
 struct BinPlan {
@@ -231,6 +258,16 @@ struct GraphDev {
     float* sl_part;
     float* sl_cpart;
     int32_t* sl_cbeg;
+    // routed sweep (RoutePlan): source offset and slot position of every edge
+    // in run order, the values sent, run starts, blocks, partial sums of rows
+    // that cross blocks
+    uint16_t* rt_src;
+    uint16_t* rt_pos;
+    float* rt_val;
+    int32_t* rt_run;
+    RouteBlock* rt_blk;
+    float* rt_head;
+    float* rt_tail;
 };
 
 // Caller id of internal vertex i.
@@ -247,6 +284,7 @@ struct pp_graph_s {
     pp::BinPlan push_plan;
     pp::SlicePlan slices;
     pp::PushBins pbins;
+    pp::RoutePlan route;
     int32_t split_pull_entries;  // rows of the pull split table
     int32_t split_push_entries;
     int32_t split_cap;           // capacity of each split table
@@ -255,6 +293,7 @@ struct pp_graph_s {
     // every vertex with an in-edge lies below this id (after degree
     // relabelling, the vertices without in-edges form the tail of the ids)
     int32_t in_active;
+    int32_t empty_in;            // vertices without in-edges
     int32_t num_cu;              // compute units of the device the graph lives on
     int32_t max_lds;             // LDS bytes one workgroup may allocate
     int32_t lds_per_cu;          // LDS bytes of one compute unit
@@ -315,6 +354,17 @@ Teleport uniform_teleport(int32_t n, float f);
 pp_status launch_pull(pp_graph g, const float* c, float* c_next, float* y, float f, hipStream_t st,
                       int32_t skip_below = 0, const Teleport* tp = nullptr);
 pp_status launch_push(pp_graph g, const float* c, float* y, hipStream_t st);
+// Routed sweeps (route.hip): both forms as one sweep that writes y (caller
+// ids) and / or the next contributions, like launch_pull.
+bool route_possible(int32_t n, int64_t nnz);
+size_t route_edge_bytes(int32_t n, int64_t nnz);
+size_t route_table_bytes(int32_t n, int64_t nnz);
+pp_status build_route(pp_graph g, void* edges, void* tables, hipStream_t st);
+bool route_for(pp_graph g, pp_dir dir);
+pp_status launch_route(pp_graph g, const float* c, float* c_next, float* y, float f, hipStream_t st,
+                       const Teleport* tp = nullptr);
+// Exclusive scan of n values into out[0..n] (graph.hip); tsum: n / 1024 + 1.
+pp_status exclusive_scan(int32_t n, const int32_t* in, int32_t* out, int32_t* tsum, int32_t* total, hipStream_t st);
 // Sizes the binned push's slices (registration; sets g->pbins).
 pp_status build_push_bins(pp_graph g, hipStream_t st);
 // One personalised PageRank column with the single-vector sweeps (pr.hip):

@@ -738,6 +738,7 @@ pp_status launch_pull(pp_graph g, const float* c, float* c_next, float* y, float
     const SlicePlan& sl = g->slices;
     const BinPlan& pp_ = g->pull_plan;
     const bool hot = a.hot > 0;
+    if (skip_below == 0 && route_for(g, PP_PULL)) return launch_route(g, c, c_next, y, f, st, &tp);
     if (sl.rows > 0 && skip_below == 0 && !g->weighted) {
         // tiled rows [0, R), then the plain pull of the other rows in the same launch
         for (int b = 0; b < PP_NUM_BINS; ++b) {
@@ -813,6 +814,13 @@ pp_status launch_pull(pp_graph g, const float* c, float* c_next, float* y, float
     return PP_OK;
 }
 
+// One sweep that finishes every row itself: the pull, or the routed push.
+static pp_status launch_owner(pp_graph g, pp_dir dir, const float* c, float* c_next, float* y, float f,
+                              hipStream_t st, const Teleport* tp = nullptr) {
+    if (dir == PP_PUSH) return launch_route(g, c, c_next, y, f, st, tp);
+    return launch_pull(g, c, c_next, y, f, st, 0, tp);
+}
+
 // One personalised column with the single-vector sweeps: x_0 = e_s (s
 // internal), iters steps of x <- (1-f) e_s + f P x in direction dir (PP_PULL
 // or PP_PUSH), x_iters written to x_out[caller id * x_stride].  Uses the
@@ -829,7 +837,7 @@ pp_status run_single_ppr(pp_graph g, pp_dir dir, int32_t s, int32_t iters, float
         PP_LAUNCH_CHECK("k_ppr1_init");
         return PP_OK;
     }
-    if (dir == PP_PULL) {
+    if (dir == PP_PULL || route_for(g, PP_PUSH)) {
         const Teleport tp{0.f, s, tele, x_stride};
         float* cn = g->d.buf1;
         hipLaunchKernelGGL(k_ppr1_init, vb, vt, 0, st, n, s, g->d.inv_s, f, c, (float*)nullptr, (float*)nullptr,
@@ -837,7 +845,7 @@ pp_status run_single_ppr(pp_graph g, pp_dir dir, int32_t s, int32_t iters, float
         PP_LAUNCH_CHECK("k_ppr1_init");
         for (int32_t t = 0; t < iters; ++t) {
             const bool last = (t == iters - 1);
-            pp_status r = launch_pull(g, c, last ? nullptr : cn, last ? x_out : nullptr, f, st, 0, &tp);
+            pp_status r = launch_owner(g, dir, c, last ? nullptr : cn, last ? x_out : nullptr, f, st, &tp);
             if (r != PP_OK) return r;
             std::swap(c, cn);
         }
@@ -892,9 +900,11 @@ PP_EXPORT pp_status pp_pr_push(pp_graph g, const float* x, float* y, float f, vo
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int32_t n = g->d.n;
     const dim3 vb(ceil_div(n, 256)), vt(256);
-    hipLaunchKernelGGL(k_pr_prologue, vb, vt, 0, st, n, x, g->d.perm, g->d.inv_s, f, g->d.buf0, g->d.buf1,
-                       teleport(n, f));
+    const bool routed = route_for(g, PP_PUSH);
+    hipLaunchKernelGGL(k_pr_prologue, vb, vt, 0, st, n, x, g->d.perm, g->d.inv_s, f, g->d.buf0,
+                       routed ? nullptr : g->d.buf1, teleport(n, f));
     PP_LAUNCH_CHECK("k_pr_prologue");
+    if (routed) return launch_route(g, g->d.buf0, nullptr, y, f, st);
     s = launch_push(g, g->d.buf0, g->d.buf1, st);
     if (s != PP_OK) return s;
     hipLaunchKernelGGL(k_pr_push_epilogue, vb, vt, 0, st, n, (const float*)g->d.buf1, g->d.inv_s, f, (float*)nullptr,
@@ -948,7 +958,7 @@ PP_EXPORT pp_status pp_pr_run(pp_graph g, pp_dir dir, int32_t iters, float f, fl
         }
         return PP_OK;
     }
-    if (dir == PP_PULL) {
+    if (dir == PP_PULL || route_for(g, PP_PUSH)) {
         float* c = g->d.buf0;
         float* cn = g->d.buf1;
         hipLaunchKernelGGL(k_pr_prologue, vb, vt, 0, st, n, (const float*)x_inout, g->d.perm, g->d.inv_s, f, c,
@@ -956,7 +966,7 @@ PP_EXPORT pp_status pp_pr_run(pp_graph g, pp_dir dir, int32_t iters, float f, fl
         PP_LAUNCH_CHECK("k_pr_prologue");
         for (int32_t t = 0; t < iters; ++t) {
             const bool last = (t == iters - 1);
-            pp_status s = launch_pull(g, c, last ? nullptr : cn, last ? x_inout : nullptr, f, st);
+            pp_status s = launch_owner(g, dir, c, last ? nullptr : cn, last ? x_inout : nullptr, f, st);
             if (s != PP_OK) return s;
             float* tmp = c;
             c = cn;

@@ -6,7 +6,9 @@
 // merged in fixed order (Sec. 5 Partition-Awareness, the workgroup being the
 // owner); the others are either hardware FP32 atomics or, binned, appended
 // to per-workgroup slices of 16384-id bins and summed in LDS by a second
-// kernel (the remote updates buffered instead of applied one by one).
+// kernel (the remote updates buffered instead of applied one by one).  Graphs
+// that the routed sweep covers (route.hip) do not come here unless their
+// updates are asked for as atomics (pp_set_push_bins(0)).
 #include <hip/hip_runtime.h>
 
 #include <vector>

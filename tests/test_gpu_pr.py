@@ -461,3 +461,52 @@ def test_binned_push_matches_oracle_and_atomic_push(hot, blocks):
     finally:
         _lib.pp_set_push_tuning(8192, 1024)
         _lib.pp_set_push_bins(1)
+
+
+def _routed_graph(kind):
+    rng = np.random.default_rng(17)
+    if kind == "uniform":  # both forms routed: most gathers miss the LDS stage
+        return gg.erdos_renyi(131072 + 13, 8 * 131072, seed=4)
+    if kind == "smallest":  # one slice short of full, nnz just past the smallest planned
+        return gg.erdos_renyi(8192, 40000, seed=5)
+    if kind == "slice+1":  # a second source slice of one vertex
+        n = 32769
+        s, t = rng.integers(0, n, (2, 300000))
+        s[:50] = n - 1
+        return gg.from_edges(n, s, t, True, name=kind)
+    if kind == "hub":  # a row of many blocks, rows on both sides of the slack (1,024 slots)
+        n = 60000
+        s = np.concatenate([np.zeros(n - 1, int), rng.integers(0, n, 200000)] +
+                           [np.full(d, 7 + i) for i, d in enumerate((1023, 1024, 1025, 5000, 17000))])
+        t = np.concatenate([np.arange(1, n), rng.integers(0, n, 200000)] +
+                           [rng.choice(n, d, replace=False) for d in (1023, 1024, 1025, 5000, 17000)])
+        return gg.from_edges(n, s, t, True, name=kind)
+    # directed, weighted, long runs of vertices without in-edges, no edges in the last rows
+    n = 150000
+    s = rng.integers(0, n, 1500000)
+    t = rng.integers(0, n // 3, 1500000) * 2 + rng.integers(0, 2, 1500000) * (n // 10)
+    host = gg.from_edges(n, s, np.minimum(t, n - 50), False, name=kind)
+    return gg.with_weights(host, seed=3)
+
+
+@pytest.mark.parametrize("kind", ["uniform", "smallest", "slice+1", "hub", "weighted directed"])
+def test_routed_sweep(kind):
+    host = _routed_graph(kind)
+    src = gg.pick_vertices(host, 2, seed=5)
+    want, _ = oracle.ppr(host.off, host.idx, src, F, T=12, weights=host.weights)
+    want_x = oracle.pagerank(host.off, host.idx, F, 12) if host.weights is None else None
+    for rl in (True, False):
+        g = pp.Graph(host, relabel=rl)
+        for d in DIRS:
+            announce(f"routed {kind} n={host.n} nnz={host.nnz} dir={d} relabel={rl}")
+            X = pp.ppr(g, src, iters=12, f=F, k_tile=1, direction=d)[0].cpu().numpy().astype(np.float64)
+            assert np.abs(X - want).sum(axis=0).max() <= PR_L1_TOL, (rl, d)
+            x = pp.pagerank(g, 12, F, d)
+            assert torch.equal(x, pp.pagerank(g, 12, F, d)), (rl, d)  # fixed summation order
+            if want_x is not None:
+                assert np.abs(x.cpu().numpy().astype(np.float64) - want_x).sum() <= PR_L1_TOL, (rl, d)
+            x0 = torch.rand(host.n, device="cuda") / host.n
+            y = torch.empty_like(x0)
+            (_lib.pp_pr_push if d == pp.PP_PUSH else _lib.pp_pr_pull)(g.handle, x0, y, F)
+            assert torch.equal(y, pp.pagerank(g, 1, F, d, x0=x0)), (rl, d)
+        g.close()
