@@ -203,7 +203,8 @@ pp_status pp_graph_slices(pp_graph g, int32_t* info);
  * d(v) = 0 contributes nothing.  x, y: float[n], distinct.  pp_pr_push
  * sends every edge's value to its target: through the target block's buffer
  * (graphs of at least 8192 vertices and 65536 edges with pp_set_push_bins(1);
- * fixed summation order), else by scattering along the CSR rows with the
+ * fixed summation order; graphs of at most 10240 vertices and some 30000 edges
+ * run in one workgroup, likewise), else by scattering along the CSR rows with the
  * privatised and binned or atomic updates of pp_set_push_tuning and
  * pp_set_push_bins (the summation order, hence the last bits, may vary between
  * runs).  pp_pr_pull gathers along CSC rows with no atomics

@@ -363,6 +363,10 @@ pp_status build_route(pp_graph g, void* edges, void* tables, hipStream_t st);
 bool route_for(pp_graph g, pp_dir dir);
 pp_status launch_route(pp_graph g, const float* c, float* c_next, float* y, float f, hipStream_t st,
                        const Teleport* tp = nullptr);
+// Whole runs of small graphs in one launch (small.hip).
+bool small_for(pp_graph g, pp_dir dir);
+pp_status launch_small(pp_graph g, int32_t iters, float f, const float* x, float* y, const Teleport& tp,
+                       hipStream_t st);
 // Exclusive scan of n values into out[0..n] (graph.hip); tsum: n / 1024 + 1.
 pp_status exclusive_scan(int32_t n, const int32_t* in, int32_t* out, int32_t* tsum, int32_t* total, hipStream_t st);
 // Sizes the binned push's slices (registration; sets g->pbins).

@@ -349,44 +349,6 @@ __device__ __forceinline__ uint32_t unit_entry(const UnitData& U, int j) {
     return (w[j >> 1] >> (16 * (j & 1))) & 0xFFFFu;
 }
 
-// Cross-lane moves through DPP: the data moves within the VALU, with no LDS
-// round trip (the shuffles they replace were the tiled sweep's critical
-// path).  A lane whose source lane lies outside its row, or whose row is
-// masked off, gets 0.  Controls: row_shr:n = 0x110 + n; row_bcast:15 = 0x142
-// (lane 15 of each row to the next row; rows 1 and 3 written); row_bcast:31
-// = 0x143 (lane 31 to rows 2 and 3); wave_shr:1 = 0x138.
-template <int CTRL, int ROWS = 0xf>
-__device__ __forceinline__ int dpp_take(int x) {
-    return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xf, false);
-}
-template <int CTRL, int ROWS = 0xf>
-__device__ __forceinline__ float dpp_takef(float x) {
-    return __int_as_float(dpp_take<CTRL, ROWS>(__float_as_int(x)));
-}
-
-// Inclusive prefix sum over the wavefront (all lanes active).
-__device__ __forceinline__ int wave_incl_sum(int x) {
-    x += dpp_take<0x111>(x);
-    x += dpp_take<0x112>(x);
-    x += dpp_take<0x114>(x);
-    x += dpp_take<0x118>(x);
-    x += dpp_take<0x142, 0xa>(x);
-    x += dpp_take<0x143, 0xc>(x);
-    return x;
-}
-
-// One step of an inclusive segmented scan: a lane that has not started a
-// segment since the source lane adds the source's sum in front of its own.
-template <int CTRL, int ROWS = 0xf>
-__device__ __forceinline__ void seg_step(float& x, int& fresh) {
-    const float xs = dpp_takef<CTRL, ROWS>(x);
-    const int fs = dpp_take<CTRL, ROWS>(fresh);
-    if (!fresh) {
-        x = xs + x;
-        fresh = fs;
-    }
-}
-
 // Runs one unit (sums: this wavefront's 256 LDS words).
 __device__ __forceinline__ void unit_run(const TileArgs& t, const UnitData& U, int lane, const float* lds, float* sums) {
     const SliceUnit& d = U.d;
@@ -837,6 +799,7 @@ pp_status run_single_ppr(pp_graph g, pp_dir dir, int32_t s, int32_t iters, float
         PP_LAUNCH_CHECK("k_ppr1_init");
         return PP_OK;
     }
+    if (small_for(g, dir)) return launch_small(g, iters, f, nullptr, x_out, Teleport{0.f, s, tele, x_stride}, st);
     if (dir == PP_PULL || route_for(g, PP_PUSH)) {
         const Teleport tp{0.f, s, tele, x_stride};
         float* cn = g->d.buf1;
@@ -887,6 +850,7 @@ PP_EXPORT pp_status pp_pr_pull(pp_graph g, const float* x, float* y, float f, vo
     if (s != PP_OK) return s;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int32_t n = g->d.n;
+    if (small_for(g, PP_PULL)) return launch_small(g, 1, f, x, y, uniform_teleport(n, f), st);
     hipLaunchKernelGGL(k_pr_prologue, dim3(ceil_div(n, 256)), dim3(256), 0, st, n, x, g->d.perm, g->d.inv_s, f,
                        g->d.buf0, (float*)nullptr, 0.f);
     PP_LAUNCH_CHECK("k_pr_prologue");
@@ -900,6 +864,7 @@ PP_EXPORT pp_status pp_pr_push(pp_graph g, const float* x, float* y, float f, vo
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int32_t n = g->d.n;
     const dim3 vb(ceil_div(n, 256)), vt(256);
+    if (small_for(g, PP_PUSH)) return launch_small(g, 1, f, x, y, uniform_teleport(n, f), st);
     const bool routed = route_for(g, PP_PUSH);
     hipLaunchKernelGGL(k_pr_prologue, vb, vt, 0, st, n, x, g->d.perm, g->d.inv_s, f, g->d.buf0,
                        routed ? nullptr : g->d.buf1, teleport(n, f));
@@ -926,6 +891,7 @@ PP_EXPORT pp_status pp_pr_run(pp_graph g, pp_dir dir, int32_t iters, float f, fl
     const int32_t n = g->d.n;
     const float base = teleport(n, f);
     const dim3 vb(ceil_div(n, 256)), vt(256);
+    if (small_for(g, dir)) return launch_small(g, iters, f, x_inout, x_inout, uniform_teleport(n, f), st);
     if (dir == PP_SWITCH) {
         // hybrid: edges into the first `hot` vertices are pushed into LDS
         // accumulators (no global atomics), all other rows pull

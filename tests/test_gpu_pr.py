@@ -510,3 +510,36 @@ def test_routed_sweep(kind):
             (_lib.pp_pr_push if d == pp.PP_PUSH else _lib.pp_pr_pull)(g.handle, x0, y, F)
             assert torch.equal(y, pp.pagerank(g, 1, F, d, x0=x0)), (rl, d)
         g.close()
+
+
+@pytest.mark.parametrize("n,rows,deg,weighted", [
+    (1, 0, 0, False), (2, 1, 1, False), (70, 3, 60, False), (1030, 255, 16, False), (1030, 257, 16, False),
+    (2000, 512, 16, True), (2000, 513, 16, True), (5000, 1536, 15, True), (5000, 1638, 20, False), (5000, 1640, 20, False),
+    (10240, 2047, 13, False), (10241, 2047, 13, False)])
+def test_small_graph_in_one_launch(n, rows, deg, weighted):
+    # `rows` vertices with `deg` in-edges each (pieces of four slots: the thread
+    # counts change at 1,024 and 2,048 of them, the last at 8,192, weighted
+    # 6,144), one of them a hub, the others without: at both ends and in between
+    rng = np.random.default_rng(rows)
+    at = np.sort(rng.choice(np.arange(n // 8, n - n // 8), rows, replace=False)) if rows else np.zeros(0, int)
+    t = np.repeat(at, deg)
+    s = rng.integers(0, n, len(t))
+    if rows > 100:
+        s, t = np.concatenate([s, np.arange(0, n, 4)]), np.concatenate([t, np.full(len(range(0, n, 4)), at[50])])
+    host = gg.from_edges(n, s, t, False, name=f"small{n}_{rows}")
+    host.ensure_transpose()
+    if weighted:
+        gg.with_weights(host, seed=3)
+    src = np.array([int(at[0]) if rows else 0], dtype=np.int32)
+    for iters in (1, 2, 5):
+        want, _ = oracle.ppr(host.off, host.idx, src, F, T=iters, weights=host.weights)
+        want_x = oracle.pagerank(host.off, host.idx, F, iters) if not weighted else None
+        for rl in (True, False):
+            g = pp.Graph(host, relabel=rl)
+            for d in DIRS:
+                announce(f"small n={n} nnz={host.nnz} T={iters} dir={d} relabel={rl}")
+                X = pp.ppr(g, src, iters=iters, f=F, k_tile=1, direction=d)[0].cpu().numpy().astype(np.float64)
+                assert np.abs(X - want).sum() <= PR_L1_TOL, (iters, rl, d)
+                if want_x is not None:
+                    assert np.abs(pr_gpu(g, d, iters).astype(np.float64) - want_x).sum() <= PR_L1_TOL, (iters, rl, d)
+            g.close()
