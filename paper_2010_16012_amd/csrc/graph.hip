@@ -242,30 +242,82 @@ __global__ __launch_bounds__(256) void k_relabel_rows(int32_t n, const int32_t* 
     for (int32_t i = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave; i < n; i += nw) {
         const int32_t v = perm[i];
         const int32_t b = off[v], e = off[v + 1], o = off_new[i];
-        for (int32_t j = b + lane; j < e; j += kWave) {
-            if (idx_new) idx_new[o + (j - b)] = iperm[idx[j]];
-            if (w_new) w_new[o + (j - b)] = map ? wsrc[map[j]] : wsrc[j];
+        // eight slots a lane in flight: a hub's row is one wavefront's work
+        constexpr int U = 8;
+        for (int32_t j0 = b + lane; j0 < e; j0 += U * kWave) {
+            int32_t jj[U], v_[U], m_[U];
+            float w_[U];
+#pragma unroll
+            for (int k = 0; k < U; ++k) jj[k] = min(j0 + k * kWave, e - 1);
+            if (idx_new) {
+#pragma unroll
+                for (int k = 0; k < U; ++k) v_[k] = idx[jj[k]];
+#pragma unroll
+                for (int k = 0; k < U; ++k) v_[k] = iperm[v_[k]];
+#pragma unroll
+                for (int k = 0; k < U; ++k)
+                    if (j0 + k * kWave < e) idx_new[o + (jj[k] - b)] = v_[k];
+            }
+            if (w_new) {
+#pragma unroll
+                for (int k = 0; k < U; ++k) m_[k] = map ? map[jj[k]] : jj[k];
+#pragma unroll
+                for (int k = 0; k < U; ++k) w_[k] = wsrc[m_[k]];
+#pragma unroll
+                for (int k = 0; k < U; ++k)
+                    if (j0 + k * kWave < e) w_new[o + (jj[k] - b)] = w_[k];
+            }
         }
     }
 }
 
-// d(v), and the reciprocal of d(v) (or of the out-strength s(v) when
-// weighted).  Vertices with nothing leaving them get 0: they pass no mass on.
-__global__ void k_degrees(int32_t n, const int32_t* __restrict__ csr_off, const float* __restrict__ csr_w,
-                          int32_t* __restrict__ out_deg, float* __restrict__ inv_s) {
+// d(v) and the reciprocal of the out-strength s(v), summed in FP64: rows of up
+// to 16 slots in the lane, the others by the whole wavefront (one thread a row
+// took 1.2 ms at R-MAT 16, a hub's slots one dependent add after another).
+__global__ __launch_bounds__(256) void k_strengths(int32_t n, const int32_t* __restrict__ off,
+                                                   const float* __restrict__ w, int32_t* __restrict__ out_deg,
+                                                   float* __restrict__ inv_s) {
+    const int lane = threadIdx.x & (kWave - 1);
+    // a wavefront's rows lie `nw` apart: the hubs, which come first, spread out
+    const int32_t nw = gridDim.x * (blockDim.x / kWave);
+    const int32_t v = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave + lane * nw;
+    const int32_t b = v < n ? off[v] : 0, e = v < n ? off[v + 1] : 0;
+    double s = 0.0;
+    const bool wide = e - b > 16;
+    if (!wide)
+        for (int32_t j = b; j < e; ++j) s += (double)w[j];
+    uint64_t m = __ballot(wide);
+    while (m) {
+        const int src = __ffsll((long long)m) - 1;
+        m &= m - 1;
+        const int32_t lb = __shfl(b, src), le = __shfl(e, src);
+        constexpr int U = 8;
+        double t = 0.0;
+        for (int32_t j0 = lb + lane; j0 < le; j0 += U * kWave) {
+            float x[U];
+#pragma unroll
+            for (int k = 0; k < U; ++k) x[k] = w[min(j0 + k * kWave, le - 1)];
+#pragma unroll
+            for (int k = 0; k < U; ++k) t += j0 + k * kWave < le ? (double)x[k] : 0.0;
+        }
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) t += __shfl_xor(t, d);
+        if (lane == src) s = t;
+    }
+    if (v >= n) return;
+    out_deg[v] = e - b;
+    inv_s[v] = s > 0.0 ? (float)(1.0 / s) : 0.f;
+}
+
+// d(v) and its reciprocal (unweighted).  Vertices with nothing leaving them
+// get 0: they pass no mass on.
+__global__ void k_degrees(int32_t n, const int32_t* __restrict__ csr_off, int32_t* __restrict__ out_deg,
+                          float* __restrict__ inv_s) {
     const int32_t v = blockIdx.x * blockDim.x + threadIdx.x;
     if (v >= n) return;
-    const int32_t b = csr_off[v], e = csr_off[v + 1];
-    out_deg[v] = e - b;
-    float r = 0.f;
-    if (csr_w) {
-        double s = 0.0;  // once per graph: accumulate the strength in double
-        for (int32_t j = b; j < e; ++j) s += (double)csr_w[j];
-        r = s > 0.0 ? (float)(1.0 / s) : 0.f;
-    } else {
-        r = (e > b) ? 1.0f / (float)(e - b) : 0.f;
-    }
-    inv_s[v] = r;
+    const int32_t d = csr_off[v + 1] - csr_off[v];
+    out_deg[v] = d;
+    inv_s[v] = d > 0 ? 1.0f / (float)d : 0.f;
 }
 
 // Weights gathered into CSC slot order: csc_w[j] = csr_w[csc_to_csr[j]].
@@ -323,23 +375,24 @@ __global__ void k_check_indices(int32_t n, int64_t nnz, const int32_t* __restric
 }
 
 // row[j] = v for every slot j of the row of v (rows of more than 64 slots
-// are written by the whole wavefront).
+// are written by the whole wavefront).  A wavefront's 64 rows lie `nw` apart,
+// so that the hubs, which come first, spread over the wavefronts.
 __global__ void k_row_owner(int32_t n, const int32_t* off, int32_t* row) {
     const int lane = threadIdx.x & (kWave - 1);
     const int32_t gw = (int32_t)((blockIdx.x * blockDim.x + threadIdx.x) / kWave);
     const int32_t nw = (int32_t)(gridDim.x * blockDim.x / kWave);
-    for (int32_t base = gw * kWave; base < n; base += nw * kWave) {
-        const int32_t v = base + lane;
+    for (int64_t v0 = gw; v0 < n; v0 += (int64_t)nw * kWave) {
+        const int64_t v = v0 + (int64_t)lane * nw;
         const int32_t b = v < n ? off[v] : 0, e = v < n ? off[v + 1] : 0;
         const bool longrow = e - b > kWave;
         if (!longrow)
-            for (int32_t j = b; j < e; ++j) row[j] = v;
+            for (int32_t j = b; j < e; ++j) row[j] = (int32_t)v;
         uint64_t m = __ballot(longrow);
         while (m) {
             const int src = __ffsll((long long)m) - 1;
             m &= m - 1;
             const int32_t lb = __shfl(b, src), le = __shfl(e, src);
-            for (int32_t j = lb + lane; j < le; j += kWave) row[j] = base + src;
+            for (int32_t j = lb + lane; j < le; j += kWave) row[j] = (int32_t)(v0 + (int64_t)src * nw);
         }
     }
 }
@@ -1091,8 +1144,10 @@ PP_EXPORT pp_status pp_graph_create(int32_t n, int64_t nnz, const int32_t* csr_o
     }
     hipLaunchKernelGGL(k_row_owner, dim3(std::max(std::min<int32_t>(ceil_div(n, 256), 4096), 1)), dim3(256), 0, st, n,
                        d.csc_off, d.csc_row);
-    hipLaunchKernelGGL(k_degrees, dim3(ceil_div(n, 256)), dim3(256), 0, st, n, d.csr_off, d.csr_w, d.out_deg,
-                       d.inv_s);
+    if (d.csr_w)
+        hipLaunchKernelGGL(k_strengths, dim3(ceil_div(n, 256)), dim3(256), 0, st, n, d.csr_off, d.csr_w, d.out_deg,
+                           d.inv_s);
+    else hipLaunchKernelGGL(k_degrees, dim3(ceil_div(n, 256)), dim3(256), 0, st, n, d.csr_off, d.out_deg, d.inv_s);
     hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, st, 4, d.err + 48);
     hipLaunchKernelGGL(k_max_deg, dim3(std::min(ceil_div(n, 256), 512)), dim3(256), 0, st, n, d.csr_off, d.csc_off, d.err + 48);
     {
@@ -1173,7 +1228,8 @@ PP_EXPORT pp_status pp_graph_set_weights(pp_graph g, const float* csr_w, void* s
                                d.user_csc_to_csr, d.csc_w);
         }
     }
-    hipLaunchKernelGGL(k_degrees, dim3(ceil_div(n, 256)), dim3(256), 0, st, n, d.csr_off, d.csr_w, d.out_deg, d.inv_s);
+    hipLaunchKernelGGL(k_strengths, dim3(ceil_div(n, 256)), dim3(256), 0, st, n, d.csr_off, d.csr_w, d.out_deg,
+                       d.inv_s);
     PP_LAUNCH_CHECK("pp_graph_set_weights");
     return PP_OK;
 }
