@@ -508,10 +508,13 @@ __global__ __launch_bounds__(1024) void k_sum_partials(int32_t m, const float* _
     }
 }
 
-// Edge gradient of one tile, added into grad (caller CSR slot order):
-// slot (v -> u): f/s(v) * sum_j X[v,j] (Lambda[u,j] - ptl[v,j]).  One group
-// of KT lanes per slot of the row; slots of long rows spread over the groups
-// of a workgroup.  Each slot has one writer.
+// Edge gradient of one tile, stored or added into grad (caller CSR slot order):
+// slot (v -> u): f/s(v) * sum_j X[v,j] (Lambda[u,j] - ptl[v,j]).  A group of
+// KT/4 lanes, four columns each, takes kGradSlots consecutive slots of the row
+// at a time (as many Lambda rows in flight); slots of long rows spread over
+// the groups of a workgroup.  Each slot has one writer.  One slot at a time
+// and one column a lane took 353 us at R-MAT 16, k = 32, this takes 49.
+constexpr int kGradSlots = 4;
 struct GradArgs {
     KPlan kp;  // over the CSR (out-degree) lists
     const int32_t* off;
@@ -528,32 +531,59 @@ struct GradArgs {
     const int32_t* user_off;  // caller CSR offsets (slot mapping)
     int32_t k, col0;
     float f;
+    bool add;               // to what grad holds; else every slot is stored
     float* grad;
 };
 
 template <int KT>
 __device__ __forceinline__ void grad_row(const GradArgs& a, int32_t v, int32_t b, int32_t e, int32_t g,
-                                         int32_t stride, int lane) {
+                                         int32_t stride, int q) {
+    constexpr int Q = kq_lanes<KT>();
+    constexpr int U = kGradSlots;
     const int32_t vc = user_id(a.perm, v);
-    const float xv = a.x_tile ? a.x_tile[(size_t)v * KT + lane]
-                              : ((a.col0 + lane < a.k) ? a.x_caller[(size_t)vc * a.k + a.col0 + lane] : 0.f);
-    const float pv = a.ptl[(size_t)v * KT + lane];
-    const float scale = a.f * a.inv_s[v];
-    const int32_t row0 = a.off[v], crow0 = a.user_off[vc];
-    for (int32_t j = b + g; j < e; j += stride) {
-        const int32_t u = a.idx[j];
-        float t = xv * (a.lam[(size_t)u * KT + lane] - pv);
+    float4 xv;
+    if (a.x_tile) {
+        xv = reinterpret_cast<const float4*>(a.x_tile)[(size_t)v * Q + q];
+    } else {
+        float x[4];
 #pragma unroll
-        for (int s = KT / 2; s > 0; s >>= 1) t += __shfl_xor(t, s);
-        if (lane == 0) a.grad[crow0 + (j - row0)] += scale * t;
+        for (int c = 0; c < 4; ++c) {
+            const int32_t col = a.col0 + 4 * q + c;
+            x[c] = col < a.k ? a.x_caller[(size_t)vc * a.k + col] : 0.f;
+        }
+        xv = make_float4(x[0], x[1], x[2], x[3]);
+    }
+    const float4 pv = reinterpret_cast<const float4*>(a.ptl)[(size_t)v * Q + q];
+    const float scale = a.f * a.inv_s[v];
+    const float4* __restrict__ lam = reinterpret_cast<const float4*>(a.lam);
+    float* out = a.grad + a.user_off[vc] - a.off[v];
+    for (int32_t j0 = b + U * g; j0 < e; j0 += U * stride) {
+        int32_t u[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) u[k] = a.idx[min(j0 + k, e - 1)];
+        float4 l[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) l[k] = lam[(size_t)u[k] * Q + q];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            float t = (xv.x * (l[k].x - pv.x) + xv.y * (l[k].y - pv.y)) +
+                      (xv.z * (l[k].z - pv.z) + xv.w * (l[k].w - pv.w));
+#pragma unroll
+            for (int s = Q / 2; s > 0; s >>= 1) t += __shfl_xor(t, s);
+            if (q == k % Q && j0 + k < e) {
+                const float gv = scale * t;
+                out[j0 + k] = a.add ? out[j0 + k] + gv : gv;
+            }
+        }
     }
 }
 
 template <int KT>
 __global__ __launch_bounds__(kBlock) void k_kcol_grad(GradArgs a) {
-    constexpr int G = kBlock / KT;
-    const int lane = threadIdx.x % KT;
-    const int grp = threadIdx.x / KT;
+    constexpr int Q = kq_lanes<KT>();
+    constexpr int G = kBlock / Q;
+    const int q = threadIdx.x % Q;
+    const int grp = threadIdx.x / Q;
     const int32_t unit = blockIdx.x;
     const int bin = kunit_bin(a.kp, unit);
     const int32_t lu = unit - a.kp.unit_off[bin];
@@ -561,14 +591,14 @@ __global__ __launch_bounds__(kBlock) void k_kcol_grad(GradArgs a) {
         const int32_t i = lu * G + grp;
         if (i < a.kp.list_off[bin + 1] - a.kp.list_off[bin]) {
             const int32_t v = a.list[a.kp.list_off[bin] + i];
-            grad_row<KT>(a, v, a.off[v], a.off[v + 1], 0, 1, lane);
+            grad_row<KT>(a, v, a.off[v], a.off[v + 1], 0, 1, q);
         }
     } else if (bin <= 4) {
         const int32_t v = a.list[a.kp.list_off[bin] + lu];
-        grad_row<KT>(a, v, a.off[v], a.off[v + 1], grp, G, lane);
+        grad_row<KT>(a, v, a.off[v], a.off[v + 1], grp, G, q);
     } else {
         const int32_t v = a.tab[lu];
-        grad_row<KT>(a, v, a.tab[a.tab_cap + lu], a.tab[2 * a.tab_cap + lu], grp, G, lane);
+        grad_row<KT>(a, v, a.tab[a.tab_cap + lu], a.tab[2 * a.tab_cap + lu], grp, G, q);
     }
 }
 
@@ -1026,7 +1056,7 @@ static pp_status run_tile(pp_graph g, bool adjoint, pp_dir dir, int32_t k, int32
 // added into grad (caller CSR slot order).
 template <int KT>
 static pp_status adjoint_grad(pp_graph g, int32_t k, int32_t col0, float f, const float* lam, float* ptl,
-                              float* part, const float* x_caller, float* grad, hipStream_t st,
+                              float* part, const float* x_caller, float* grad, bool add, hipStream_t st,
                               const float* x_tile = nullptr) {
     const Walk w = walk_csr(g, KT);
     KArgs a{};
@@ -1049,7 +1079,7 @@ static pp_status adjoint_grad(pp_graph g, int32_t k, int32_t col0, float f, cons
     if (launch_kpull<KT>(a, w.nsplit, st, g->weighted) < 0)
         return set_error(PP_E_GRAPH, "inconsistent k-column sweep plan");
     GradArgs ga{};
-    ga.kp = w.kp;
+    ga.kp = kplan_pull4(w.kp, KT);
     ga.off = w.off;
     ga.idx = w.idx;
     ga.list = w.list;
@@ -1065,8 +1095,9 @@ static pp_status adjoint_grad(pp_graph g, int32_t k, int32_t col0, float f, cons
     ga.k = k;
     ga.col0 = col0;
     ga.f = f;
+    ga.add = add;
     ga.grad = grad;
-    if (w.kp.units > 0) hipLaunchKernelGGL(k_kcol_grad<KT>, dim3(w.kp.units), dim3(kBlock), 0, st, ga);
+    if (ga.kp.units > 0) hipLaunchKernelGGL(k_kcol_grad<KT>, dim3(ga.kp.units), dim3(kBlock), 0, st, ga);
     PP_LAUNCH_CHECK("ppr adjoint gradient");
     return PP_OK;
 }
@@ -1123,7 +1154,8 @@ static pp_status unrolled_tile(pp_graph g, int32_t k, int32_t col0, int32_t T, f
     float* ptl = t1;
     hipLaunchKernelGGL(k_kcol_adjoint_init<KT>, cb, ct, 0, st, n, k, col0, g->d.perm, g_caller, lam, (double*)nullptr);
     for (int32_t t = T - 1; t >= 0; --t) {
-        pp_status s = adjoint_grad<KT>(g, k, col0, f, lam, ptl, part, nullptr, grad, st, hist + (size_t)t * tile);
+        pp_status s = adjoint_grad<KT>(g, k, col0, f, lam, ptl, part, nullptr, grad, true, st,
+                                       hist + (size_t)t * tile);
         if (s != PP_OK) return s;
         hipLaunchKernelGGL(k_scale_f32, dim3(std::min<int64_t>(ceil_div(cells, 256), 65536)), dim3(256), 0, st, cells,
                            f, ptl);
@@ -1191,8 +1223,6 @@ static pp_status ppr_call(const PprCall& c, int32_t* iters_done) {
         PP_HIP(hipMemcpyAsync(&bad, flag, sizeof(int32_t), hipMemcpyDeviceToHost, c.st));
         PP_HIP(hipStreamSynchronize(c.st));
         if (bad) return set_error(PP_E_RANGE, "a source lies outside [0, n)");
-    } else if (c.g->d.nnz > 0) {
-        hipLaunchKernelGGL(k_zero_f32, dim3(ceil_div(c.g->d.nnz, 256)), dim3(256), 0, c.st, c.g->d.nnz, c.grad);
     }
     int32_t most = 0;
     for (int32_t col0 = 0; col0 < c.k; col0 += KT) {
@@ -1209,7 +1239,7 @@ static pp_status ppr_call(const PprCall& c, int32_t* iters_done) {
             float* t0 = reinterpret_cast<float*>(c.base + c.L.t0);
             float* ptl = (latest == t0) ? reinterpret_cast<float*>(c.base + c.L.t1) : t0;
             s = adjoint_grad<KT>(c.g, c.k, col0, c.f, latest, ptl, reinterpret_cast<float*>(c.base + c.L.part),
-                                 c.x_caller, c.grad, c.st);
+                                 c.x_caller, c.grad, col0 > 0, c.st);
             if (s != PP_OK) return s;
         }
     }
