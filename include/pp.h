@@ -333,8 +333,10 @@ size_t pp_ppr_scratch_bytes(pp_graph g, int32_t k, int32_t k_tile);
  * caller ids (output).  Columns run in tiles of k_tile (8, 16, 32, 64; the
  * last tile may be partial); a tile's rows hold k_tile contiguous values so every edge
  * moves one coalesced k_tile-float row.  dir PP_PULL gathers along CSC (no
- * atomics, deterministic), PP_PUSH scatters along CSR with FP64 atomics into
- * an FP64 accumulator.  PP_SWITCH applies the Generic-Switch strategy of
+ * atomics, deterministic, FP32 sums), PP_PUSH delivers every update to its
+ * target's owner, who sums in FP64 along the CSC list of what is sent to it
+ * (deterministic); with pp_set_push_bins(0) it scatters along CSR with FP64
+ * atomics into an FP64 accumulator instead.  PP_SWITCH applies the Generic-Switch strategy of
  * Sec. 5: while the tile's support (the vertices within t hops of its
  * sources) has at most m/14 out-edges, a sweep pushes from the support only
  * (sparse matrix times sparse vector along CSR, Sec. 7.1, FP64 atomics);
@@ -358,7 +360,8 @@ pp_status pp_ppr_run(pp_graph g, pp_dir dir, int32_t k, const int32_t* sources, 
  *   Lambda = dLdX + f P^T Lambda,  (P^T z)(v) = (1/s(v)) sum over out-edges
  * (v,u) of w(v->u) z(u),
  * which is the transposed sweep: PP_PULL gathers along the CSR rows (the rows
- * the forward push scatters along), PP_PUSH scatters along CSC.  PP_SWITCH
+ * the forward push sends along), PP_PUSH sends along CSC (FP64 sums at the
+ * owner, or FP64 atomics, as in pp_ppr_run).  PP_SWITCH
  * (Sec. 5 Generic-Switch): Lambda's support starts at the nonzero rows of
  * dLdX and grows along in-edges; while its in-edges number at most nnz/14
  * the sweeps push from the support only, then dense pulls (a dense dLdX

@@ -15,12 +15,19 @@
 //
 // Columns are processed in tiles of KT (8, 16, 32 or 64) columns; a tile's
 // state is stored tile-major (row u holds its KT values contiguously), so one
-// neighbour costs one coalesced KT-float read.  A group of KT lanes owns a
-// row (lane = column).  Rows are distributed with the degree bins of the
-// graph: short rows one group each, long rows one workgroup each (groups take
-// strided neighbours, reduced through LDS in a fixed order), and the longest
-// rows in chunks finished by a fix-up kernel.  Pull sweeps use no atomics
-// and are deterministic; push sweeps use FP32 atomics.
+// neighbour costs one coalesced KT-float read.  Rows are distributed with the
+// degree bins of the graph: short rows a group of KT/4 lanes each (four columns
+// a lane), longer ones a wavefront or a workgroup each (groups take strided
+// neighbours and add up as a fixed tree), and the longest in chunks finished by
+// a fix-up kernel.
+//
+// Both forms run this way by default: the in-edge list of a row names every
+// update that is pushed to it, so its owner takes them from the senders' rows
+// instead of meeting them at a shared accumulator.  The pulling form sums in
+// FP32, the pushing form in FP64 (as its accumulators always have).  With
+// pp_set_push_bins(0) the pushing form scatters along the sender's row with
+// FP64 atomics: 560 us a sweep at R-MAT 16, k = 32, bound by the atomics (58M a
+// sweep, 104 G/s), ten times the owner's sums.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -78,7 +85,7 @@ struct KArgs {
     const int32_t* list;
     const int32_t* tab;     // bin-5 chunk table (v | begin | end | first)
     int32_t tab_cap;
-    float* part;            // bin-5 partials, entries x KT
+    void* part;             // bin-5 partials, entries x KT sums
     const float* src;       // gathered tile
     // epilogue
     int32_t kind;
@@ -89,10 +96,11 @@ struct KArgs {
     int32_t col0;           // first column of the tile
     const int32_t* src_int; // forward: internal id of each column's source (length k)
     const float* prev;      // previous iterate (residual), tile layout (nullable)
-    float* out_tile;        // new iterate, tile layout
+    float* out_tile;        // new iterate, tile layout (nullable)
     float* out_scaled;      // forward: c = f * x / s (tile layout, nullable)
     const float* g_caller;  // adjoint: dL/dX, caller layout n x k
     float* out_caller;      // last iteration: caller layout n x k (nullable)
+    bool caller4;           // its rows may be written four columns at a time
     float* resid_part;      // per-unit-group residual partials (nullable)
 };
 
@@ -110,68 +118,35 @@ __device__ __forceinline__ float2 kt_epilogue(const KArgs& a, int32_t u, int lan
     } else {
         val = a.inv_s[u] * acc;  // (P^T Lambda)(u)
     }
-    a.out_tile[(size_t)u * KT + lane] = val;
+    if (a.out_tile) a.out_tile[(size_t)u * KT + lane] = val;
     if (a.out_caller && a.col0 + lane < a.k) a.out_caller[(size_t)user_id(a.perm, u) * a.k + a.col0 + lane] = val;
     return a.prev ? make_float2(fabsf(val - a.prev[(size_t)u * KT + lane]), fabsf(val)) : make_float2(0.f, 0.f);
 }
 
-// Fixed-order workgroup sum of (difference, norm) pairs into out[2*slot].
+// Fixed-order workgroup sum of (difference, norm) pairs into out[2*slot]: a
+// tree in every wavefront, then the wavefronts in order (red: 2 floats each).
 __device__ __forceinline__ void resid_flush(float2 r, float* red, float* out, int32_t slot) {
-    red[threadIdx.x] = r.x;
-    red[kBlock + threadIdx.x] = r.y;
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) {
+        r.x += __shfl_xor(r.x, s);
+        r.y += __shfl_xor(r.y, s);
+    }
+    const int w = threadIdx.x / kWave;
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+        red[2 * w] = r.x;
+        red[2 * w + 1] = r.y;
+    }
     __syncthreads();
     if (threadIdx.x == 0) {
         float d = 0.f, m = 0.f;
-        for (int i = 0; i < kBlock; ++i) {
-            d += red[i];
-            m += red[kBlock + i];
+#pragma unroll
+        for (int i = 0; i < kBlock / kWave; ++i) {
+            d += red[2 * i];
+            m += red[2 * i + 1];
         }
         out[2 * slot] = d;
         out[2 * slot + 1] = m;
     }
-}
-
-// One group of KT lanes sums src[idx[j]] (x wt[j]) over j = b + g, b + g + stride, ...
-template <int KT, bool W>
-__device__ __forceinline__ float kt_gather(const KArgs& a, int32_t b, int32_t e, int32_t g, int32_t stride, int lane) {
-    float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
-    int32_t j = b + g;
-    for (; j + 3 * stride < e; j += 4 * stride) {
-        const int32_t v0 = a.idx[j], v1 = a.idx[j + stride], v2 = a.idx[j + 2 * stride], v3 = a.idx[j + 3 * stride];
-        float x0 = a.src[(size_t)v0 * KT + lane], x1 = a.src[(size_t)v1 * KT + lane];
-        float x2 = a.src[(size_t)v2 * KT + lane], x3 = a.src[(size_t)v3 * KT + lane];
-        if (W) {
-            x0 *= a.wt[j];
-            x1 *= a.wt[j + stride];
-            x2 *= a.wt[j + 2 * stride];
-            x3 *= a.wt[j + 3 * stride];
-        }
-        a0 += x0;
-        a1 += x1;
-        a2 += x2;
-        a3 += x3;
-    }
-    for (; j < e; j += stride) {
-        float x = a.src[(size_t)a.idx[j] * KT + lane];
-        if (W) x *= a.wt[j];
-        a0 += x;
-    }
-    return (a0 + a1) + (a2 + a3);
-}
-
-// Sum over the groups of a workgroup, in group order (thread (0, lane) holds it).
-template <int KT>
-__device__ __forceinline__ float kt_block_sum(float v, float* red) {
-    constexpr int G = kBlock / KT;
-    red[threadIdx.x] = v;
-    __syncthreads();
-    float t = 0.f;
-    if (threadIdx.x < KT) {
-#pragma unroll
-        for (int g = 0; g < G; ++g) t += red[g * KT + threadIdx.x];
-    }
-    __syncthreads();
-    return t;
 }
 
 // The pull sweep moves float4s: a row is owned by KT/4 lanes, lane q holding
@@ -180,66 +155,110 @@ __device__ __forceinline__ float kt_block_sum(float v, float* red) {
 template <int KT>
 constexpr int kq_lanes() { return KT / 4; }
 
-__device__ __forceinline__ float4 f4_add(float4 x, float4 y) {
-    return make_float4(x.x + y.x, x.y + y.y, x.z + y.z, x.w + y.w);
+// Four columns' sums in the form's precision.
+template <typename T>
+struct Sum4 {
+    T x, y, z, w;
+};
+template <typename T>
+__device__ __forceinline__ Sum4<T> s4_add(const Sum4<T>& p, const Sum4<T>& q) {
+    return {p.x + q.x, p.y + q.y, p.z + q.z, p.w + q.w};
+}
+template <typename T>
+__device__ __forceinline__ Sum4<T> s4_of(float4 v) {
+    return {(T)v.x, (T)v.y, (T)v.z, (T)v.w};
+}
+template <typename T>
+__device__ __forceinline__ float4 s4_float(const Sum4<T>& v) {
+    return make_float4((float)v.x, (float)v.y, (float)v.z, (float)v.w);
 }
 
 __device__ __forceinline__ float4 f4_scale(float4 x, float s) { return make_float4(x.x * s, x.y * s, x.z * s, x.w * s); }
 
 // One group of KT/4 lanes sums src[idx[j]] (x wt[j]) over j = b + g,
-// b + g + stride, ...: U index loads, then U float4 gathers in flight, summed
-// pairwise before they join the running sum (fixed order, and a hub row of
+// b + g + stride, ...: U float4 gathers in flight, beside the U index (and
+// weight) loads of the next round, summed pairwise before they join the running sum (fixed order, and a hub row of
 // thousands of slots keeps its FP32 rounding error near log2(U) + slots/U
 // steps).  Loads past the row's end are exec-masked, not clamped: a clamped
 // gather would still move KT floats.
-template <int KT, int U, bool W>
-__device__ __forceinline__ float4 kt_gather4(const KArgs& a, int32_t b, int32_t e, int32_t g, int32_t stride,
-                                             int q) {
+template <int KT, int U, bool W, typename T>
+__device__ __forceinline__ Sum4<T> kt_gather4(const KArgs& a, int32_t b, int32_t e, int32_t g, int32_t stride,
+                                              int q) {
     const float4* __restrict__ src4 = reinterpret_cast<const float4*>(a.src);
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int32_t j0 = b + g; j0 < e; j0 += U * stride) {
-        int32_t vv[U];
+    Sum4<T> acc{0, 0, 0, 0};
+    const int32_t step = U * stride;
+    int32_t j0 = b + g;
+    if (j0 >= e) return acc;
+    int32_t vv[U];
+    float ww[W ? U : 1];
+    auto fetch = [&](int32_t at) {
 #pragma unroll
-        for (int k = 0; k < U; ++k) vv[k] = a.idx[min(j0 + k * stride, e - 1)];
+        for (int k = 0; k < U; ++k) {
+            const int32_t j = min(at + k * stride, e - 1);
+            vv[k] = a.idx[j];
+            if (W) ww[k] = a.wt[j];
+        }
+    };
+    fetch(j0);
+    for (; j0 < e; j0 += step) {
         float4 x[U];
 #pragma unroll
         for (int k = 0; k < U; ++k) {
             x[k] = make_float4(0.f, 0.f, 0.f, 0.f);
             if (j0 + k * stride < e) x[k] = src4[(size_t)vv[k] * kq_lanes<KT>() + q];
         }
+        float wk[W ? U : 1];
+        if (W) {
+#pragma unroll
+            for (int k = 0; k < U; ++k) wk[k] = ww[k];
+        }
+        if (j0 + step < e) fetch(j0 + step);  // the next round's indices load beside this round's rows
         if (W) {
 #pragma unroll
             for (int k = 0; k < U; ++k)
-                if (j0 + k * stride < e) x[k] = f4_scale(x[k], a.wt[j0 + k * stride]);
+                if (j0 + k * stride < e) x[k] = f4_scale(x[k], wk[k]);
         }
+        // widening is kept apart from the masked loads: inside the masks each
+        // would be waited for by itself (6.0 against 4.3 ms at R-MAT 18, k = 64)
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+            if (sizeof(T) == 8) asm("" : "+v"(x[k].x), "+v"(x[k].y), "+v"(x[k].z), "+v"(x[k].w));
+        Sum4<T> y[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) y[k] = s4_of<T>(x[k]);
 #pragma unroll
         for (int w = 1; w < U; w <<= 1) {
 #pragma unroll
-            for (int k = 0; k + w < U; k += 2 * w) x[k] = f4_add(x[k], x[k + w]);
+            for (int k = 0; k + w < U; k += 2 * w) y[k] = s4_add(y[k], y[k + w]);
         }
-        acc = f4_add(acc, x[0]);
+        acc = s4_add(acc, y[0]);
     }
     return acc;
+}
+
+// Sum over the groups of a wavefront as a fixed binary tree (in every lane).
+template <int KT, typename T>
+__device__ __forceinline__ Sum4<T> kt_wave_sum4(Sum4<T> v) {
+#pragma unroll
+    for (int s = kq_lanes<KT>(); s < kWave; s <<= 1)
+        v = s4_add(v, Sum4<T>{__shfl_xor(v.x, s), __shfl_xor(v.y, s), __shfl_xor(v.z, s), __shfl_xor(v.w, s)});
+    return v;
 }
 
 // Sum over the groups of a workgroup as a fixed binary tree (thread q < KT/4
 // holds it): log2(G) rounding steps instead of G - 1 for a row spread over all
 // G groups.
-template <int KT>
-__device__ __forceinline__ float4 kt_block_sum4(float4 v, float4* red) {
+template <int KT, typename T>
+__device__ __forceinline__ Sum4<T> kt_block_sum4(Sum4<T> v, Sum4<T>* red) {
     constexpr int Q = kq_lanes<KT>();
-    constexpr int G = kBlock / Q;
-    static_assert((G & (G - 1)) == 0, "group count must be a power of two");
-    const int grp = threadIdx.x / Q;
-    red[threadIdx.x] = v;
+    v = kt_wave_sum4<KT, T>(v);
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    if (lane < Q) red[w * Q + lane] = v;
     __syncthreads();
-#pragma unroll
-    for (int s = G / 2; s >= 1; s >>= 1) {
-        if (grp < s) red[threadIdx.x] = f4_add(red[threadIdx.x], red[threadIdx.x + s * Q]);
-        __syncthreads();
-    }
-    const float4 t = (threadIdx.x < Q) ? red[threadIdx.x] : make_float4(0.f, 0.f, 0.f, 0.f);
-    __syncthreads();
+    static_assert(kBlock / kWave == 4, "two tree steps over the wavefronts");
+    Sum4<T> t{0, 0, 0, 0};
+    if (threadIdx.x < Q)
+        t = s4_add(s4_add(red[lane], red[Q + lane]), s4_add(red[2 * Q + lane], red[3 * Q + lane]));
     return t;
 }
 
@@ -270,12 +289,18 @@ __device__ __forceinline__ float2 kt_epilogue4(const KArgs& a, int32_t u, int q,
 #pragma unroll
         for (int c = 0; c < 4; ++c) val[c] = is * in[c];  // (P^T Lambda)(u)
     }
-    reinterpret_cast<float4*>(a.out_tile)[(size_t)u * kq_lanes<KT>() + q] = make_float4(val[0], val[1], val[2], val[3]);
+    if (a.out_tile)
+        reinterpret_cast<float4*>(a.out_tile)[(size_t)u * kq_lanes<KT>() + q] =
+            make_float4(val[0], val[1], val[2], val[3]);
     if (a.out_caller) {
-        const int32_t uc = user_id(a.perm, u);
+        float* o = a.out_caller + (size_t)user_id(a.perm, u) * a.k + c0;
+        if (a.caller4) {
+            if (c0 < a.k) *reinterpret_cast<float4*>(o) = make_float4(val[0], val[1], val[2], val[3]);
+        } else {
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
-            if (c0 + c < a.k) a.out_caller[(size_t)uc * a.k + c0 + c] = val[c];
+            for (int c = 0; c < 4; ++c)
+                if (c0 + c < a.k) o[c] = val[c];
+        }
     }
     float2 r = make_float2(0.f, 0.f);
     if (a.prev) {
@@ -296,14 +321,16 @@ static int32_t kplan_bin_units(const KPlan& kp, int b) {
     return (b == 0 ? kp.units : kp.unit_off[b - 1]) - kp.unit_off[b];
 }
 
-// Units of the float4 pull over the row-unit plan kp: bins 0-2 put
-// kBlock/(KT/4) rows in a unit, bins 3-4 one row, bin 5 one chunk.
+// Units of the float4 sweep over the row-unit plan kp: bins 0-2 put
+// kBlock/(KT/4) rows in a unit, bin 3 one row a wavefront, bin 4 one row, bin 5
+// one chunk.
 static KPlan kplan_pull4(const KPlan& kp, int kt) {
     KPlan k = kp;
     int32_t at = 0;
     for (int b = PP_NUM_BINS - 1; b >= 0; --b) {
         const int32_t rows = kp.list_off[b + 1] - kp.list_off[b];
-        const int32_t units = (b <= 2) ? ceil_div(rows, kBlock / (kt / 4)) : kplan_bin_units(kp, b);
+        const int32_t units = (b <= 2) ? ceil_div(rows, kBlock / (kt / 4)) : (b == 3) ? ceil_div(rows, kBlock / kWave)
+                                                                                    : kplan_bin_units(kp, b);
         k.unit_off[b] = at;
         at += units;
     }
@@ -322,11 +349,20 @@ static bool kplan_valid(const KPlan& kp) {
     return at == kp.units && kp.unit_off[PP_NUM_BINS] == kp.units;
 }
 
-template <int KT, bool W>
-__global__ __launch_bounds__(kBlock) void k_kcol_pull(KArgs a) {
-    __shared__ float4 red4[kBlock];
+// One sweep of a tile.  What bounds it: the KT-float rows it gathers (9-12
+// TB/s out of the caches).  T: float for the pulling form, double for the
+// pushing form.  A wavefront per row of bin 3 (65-1,024 slots by default, most
+// of a skewed graph's edges) needs no barrier; as a workgroup each, with its
+// barriers and a serial residual sum at the end of every workgroup, R-MAT 18,
+// k = 64 took 168 us a sweep, this takes 124.  Loading the next round's indices
+// ahead is worth most on small graphs, where the longest rows' chains of round
+// trips set the time: R-MAT 16, k = 32 weighted 53 -> 27 us.
+template <int KT, bool W, typename T>
+__global__ __launch_bounds__(kBlock) void k_kcol_sweep(KArgs a) {
     constexpr int Q = kq_lanes<KT>();
     constexpr int G = kBlock / Q;
+    __shared__ Sum4<T> red4[Q * (kBlock / kWave)];
+    __shared__ float redf[2 * (kBlock / kWave)];
     const int q = threadIdx.x % Q;
     const int grp = threadIdx.x / Q;
     const int32_t unit = blockIdx.x;
@@ -337,43 +373,52 @@ __global__ __launch_bounds__(kBlock) void k_kcol_pull(KArgs a) {
         const int32_t i = lu * G + grp;
         if (i < a.kp.list_off[bin + 1] - a.kp.list_off[bin]) {
             const int32_t u = a.list[a.kp.list_off[bin] + i];
-            const float4 acc = (bin == 0) ? kt_gather4<KT, 4, W>(a, a.off[u], a.off[u + 1], 0, 1, q)
-                                          : kt_gather4<KT, 8, W>(a, a.off[u], a.off[u + 1], 0, 1, q);
-            res = kt_epilogue4<KT>(a, u, q, acc);
+            const Sum4<T> acc = (bin == 0) ? kt_gather4<KT, 4, W, T>(a, a.off[u], a.off[u + 1], 0, 1, q)
+                                           : kt_gather4<KT, 8, W, T>(a, a.off[u], a.off[u + 1], 0, 1, q);
+            res = kt_epilogue4<KT>(a, u, q, s4_float(acc));
         }
-    } else if (bin <= 4) {
+    } else if (bin == 3) {
+        const int32_t i = lu * (kBlock / kWave) + threadIdx.x / kWave;
+        if (i < a.kp.list_off[4] - a.kp.list_off[3]) {
+            const int32_t u = a.list[a.kp.list_off[3] + i];
+            constexpr int GW = kWave / Q;
+            Sum4<T> acc = kt_gather4<KT, 8, W, T>(a, a.off[u], a.off[u + 1], grp % GW, GW, q);
+            acc = kt_wave_sum4<KT, T>(acc);
+            if (grp % GW == 0) res = kt_epilogue4<KT>(a, u, q, s4_float(acc));
+        }
+    } else if (bin == 4) {
         const int32_t u = a.list[a.kp.list_off[bin] + lu];
-        float4 acc = kt_gather4<KT, 8, W>(a, a.off[u], a.off[u + 1], grp, G, q);
-        acc = kt_block_sum4<KT>(acc, red4);
-        if (threadIdx.x < Q) res = kt_epilogue4<KT>(a, u, q, acc);
+        Sum4<T> acc = kt_gather4<KT, 8, W, T>(a, a.off[u], a.off[u + 1], grp, G, q);
+        acc = kt_block_sum4<KT, T>(acc, red4);
+        if (threadIdx.x < Q) res = kt_epilogue4<KT>(a, u, q, s4_float(acc));
     } else {
         const int32_t b = a.tab[a.tab_cap + lu], e = a.tab[2 * a.tab_cap + lu];
-        float4 acc = kt_gather4<KT, 8, W>(a, b, e, grp, G, q);
-        acc = kt_block_sum4<KT>(acc, red4);
-        if (threadIdx.x < Q) reinterpret_cast<float4*>(a.part)[(size_t)lu * Q + q] = acc;
+        Sum4<T> acc = kt_gather4<KT, 8, W, T>(a, b, e, grp, G, q);
+        acc = kt_block_sum4<KT, T>(acc, red4);
+        if (threadIdx.x < Q) reinterpret_cast<Sum4<T>*>(a.part)[(size_t)lu * Q + q] = acc;
     }
-    if (a.resid_part) resid_flush(res, reinterpret_cast<float*>(red4), a.resid_part, unit);
+    if (a.resid_part) resid_flush(res, redf, a.resid_part, unit);
 }
 
 // Finishes the chunked rows: partials in chunk order, then the epilogue.
-template <int KT>
+template <int KT, typename T>
 __global__ __launch_bounds__(kBlock) void k_kcol_fix(KArgs a, int32_t nsplit, float* resid_fix) {
     const int lane = threadIdx.x % KT;
     const int32_t i = blockIdx.x * (kBlock / KT) + threadIdx.x / KT;
     float2 res = make_float2(0.f, 0.f);
     if (i < nsplit) {
         const int32_t* first = a.tab + 3 * a.tab_cap;
-        float acc = 0.f;
-        for (int32_t e = first[i]; e < first[i + 1]; ++e) acc += a.part[(size_t)e * KT + lane];
-        res = kt_epilogue<KT>(a, a.tab[first[i]], lane, acc);
+        T acc = 0;
+        for (int32_t e = first[i]; e < first[i + 1]; ++e) acc += reinterpret_cast<const T*>(a.part)[(size_t)e * KT + lane];
+        res = kt_epilogue<KT>(a, a.tab[first[i]], lane, (float)acc);
     }
     if (resid_fix) {
-        __shared__ float red[2 * kBlock];
+        __shared__ float red[2 * (kBlock / kWave)];
         resid_flush(res, red, resid_fix, blockIdx.x);
     }
 }
 
-// ------------------------------------------------------------------ push
+// ------------------------------------------------- push by global atomics
 struct KPushArgs {
     KPlan kp;
     const int32_t* off;
@@ -425,7 +470,7 @@ __global__ __launch_bounds__(kBlock) void k_kcol_push(KPushArgs a) {
 // forward, nothing: the teleport is added by the epilogue).
 template <int KT>
 __global__ __launch_bounds__(kBlock) void k_kcol_push_epi(KArgs a, int32_t n, double* accum) {
-    __shared__ float red[2 * kBlock];
+    __shared__ float red[2 * (kBlock / kWave)];
     const int lane = threadIdx.x % KT;
     const int32_t u = blockIdx.x * (kBlock / KT) + threadIdx.x / KT;
     float2 res = make_float2(0.f, 0.f);
@@ -593,7 +638,13 @@ __global__ __launch_bounds__(kBlock) void k_kcol_grad(GradArgs a) {
             const int32_t v = a.list[a.kp.list_off[bin] + i];
             grad_row<KT>(a, v, a.off[v], a.off[v + 1], 0, 1, q);
         }
-    } else if (bin <= 4) {
+    } else if (bin == 3) {
+        const int32_t i = lu * (kBlock / kWave) + threadIdx.x / kWave;
+        if (i < a.kp.list_off[4] - a.kp.list_off[3]) {
+            const int32_t v = a.list[a.kp.list_off[3] + i];
+            grad_row<KT>(a, v, a.off[v], a.off[v + 1], grp % (kWave / Q), kWave / Q, q);
+        }
+    } else if (bin == 4) {
         const int32_t v = a.list[a.kp.list_off[bin] + lu];
         grad_row<KT>(a, v, a.off[v], a.off[v + 1], grp, G, q);
     } else {
@@ -715,7 +766,7 @@ __global__ __launch_bounds__(kBlock) void k_sw_scatter(SwState w, const int32_t*
 // Epilogue of a sparse sweep over the support (count read on the device).
 template <int KT>
 __global__ __launch_bounds__(kBlock) void k_sw_epi(KArgs a, SwState w, double* accum) {
-    __shared__ float red[2 * kBlock];
+    __shared__ float red[2 * (kBlock / kWave)];
     constexpr int G = kBlock / KT;
     const int lane = threadIdx.x % KT;
     const int32_t count = w.cnt[0];
@@ -758,7 +809,7 @@ static PprLayout ppr_layout(int32_t n, int64_t nnz, int32_t split_cap, int32_t k
     L.t2 = take(tile);
     L.t3 = take(tile);
     L.t4 = take(2 * tile);  // FP64 push accumulator
-    L.part = take((size_t)split_cap * kt * 4);
+    L.part = take((size_t)split_cap * kt * 8);  // chunk sums, FP64 in the pushing form
     // residual pairs: one per work unit of a dense sweep, or one per
     // workgroup of the sparse epilogue (at most kSwEpiBlocks)
     L.resid = take((size_t)(std::max<int64_t>((int64_t)max_units + ceil_div(n, 4), kSwEpiBlocks) + 64) * 8);
@@ -782,23 +833,30 @@ static int32_t max_units(pp_graph g, int kt) {
 
 static bool valid_kt(int32_t kt) { return kt == 8 || kt == 16 || kt == 32 || kt == 64; }
 
-// Launches a pull sweep over the row-unit plan a.kp; returns the residual
-// slots written (units, then the fix-up's blocks) when a.resid_part is set.
+// Launches a sweep over the row-unit plan a.kp (push: FP64 sums); returns the
+// residual slots written (units, then the fix-up's blocks) when a.resid_part
+// is set.
+template <int KT, typename T>
+static int32_t launch_sweep_t(const KArgs& a, int32_t nsplit, hipStream_t st, bool weighted) {
+    if (a.kp.units > 0) {
+        if (weighted) hipLaunchKernelGGL((k_kcol_sweep<KT, true, T>), dim3(a.kp.units), dim3(kBlock), 0, st, a);
+        else hipLaunchKernelGGL((k_kcol_sweep<KT, false, T>), dim3(a.kp.units), dim3(kBlock), 0, st, a);
+    }
+    float* resid_fix = a.resid_part ? a.resid_part + 2 * (size_t)a.kp.units : nullptr;
+    if (nsplit > 0)
+        hipLaunchKernelGGL((k_kcol_fix<KT, T>), dim3(ceil_div(nsplit, kBlock / KT)), dim3(kBlock), 0, st, a, nsplit,
+                           resid_fix);
+    return a.kp.units + (nsplit > 0 ? ceil_div(nsplit, kBlock / KT) : 0);
+}
+
 template <int KT>
-static int32_t launch_kpull(const KArgs& a_rows, int32_t nsplit, hipStream_t st, bool weighted) {
+static int32_t launch_sweep(pp_graph g, const KArgs& a_rows, int32_t nsplit, hipStream_t st, bool push = false) {
     KArgs a = a_rows;
     a.kp = kplan_pull4(a_rows.kp, KT);
     if (!kplan_valid(a_rows.kp) || !kplan_valid(a.kp) || kplan_bin_units(a.kp, 5) != kplan_bin_units(a_rows.kp, 5))
         return -1;  // never launch over an inconsistent plan
-    if (a.kp.units > 0) {
-        if (weighted) hipLaunchKernelGGL((k_kcol_pull<KT, true>), dim3(a.kp.units), dim3(kBlock), 0, st, a);
-        else hipLaunchKernelGGL((k_kcol_pull<KT, false>), dim3(a.kp.units), dim3(kBlock), 0, st, a);
-    }
-    float* resid_fix = a.resid_part ? a.resid_part + 2 * (size_t)a.kp.units : nullptr;
-    if (nsplit > 0)
-        hipLaunchKernelGGL((k_kcol_fix<KT>), dim3(ceil_div(nsplit, kBlock / KT)), dim3(kBlock), 0, st, a, nsplit,
-                           resid_fix);
-    return a.kp.units + (nsplit > 0 ? ceil_div(nsplit, kBlock / KT) : 0);
+    return push ? launch_sweep_t<KT, double>(a, nsplit, st, g->weighted)
+                : launch_sweep_t<KT, float>(a, nsplit, st, g->weighted);
 }
 
 template <int KT>
@@ -853,7 +911,8 @@ __global__ void k_tile_to_caller(int32_t n, int32_t k, int32_t col0, const int32
 }
 
 // Runs one tile for `iters` sweeps, or until the L1 change of a sweep falls
-// below tol.  Forward state: t0/t1 iterates, t2/t3 scaled contributions;
+// below tol (tol = 0, forward: the last sweep writes `out`, the caller's n x k
+// matrix, and *latest is NULL).  Forward state: t0/t1 iterates, t2/t3 scaled contributions;
 // adjoint state: t0/t1 Lambda; t4 is the push accumulator.  On return
 // *latest points at the newest iterate and *done holds the sweeps run.
 // Sparse sweeps of a tile while the support is small (PP_SWITCH).  Forward:
@@ -950,8 +1009,8 @@ static pp_status sparse_phase(pp_graph g, bool adjoint, int32_t k, int32_t col0,
 
 template <int KT>
 static pp_status run_tile(pp_graph g, bool adjoint, pp_dir dir, int32_t k, int32_t col0, int32_t iters, float tol,
-                          float f, const int32_t* src_int, const float* g_caller, char* base, const PprLayout& L,
-                          float** latest, int32_t* done, hipStream_t st) {
+                          float f, const int32_t* src_int, const float* g_caller, float* out, char* base,
+                          const PprLayout& L, float** latest, int32_t* done, hipStream_t st) {
     const int32_t n = g->d.n;
     float* t0 = reinterpret_cast<float*>(base + L.t0);
     float* t1 = reinterpret_cast<float*>(base + L.t1);
@@ -963,8 +1022,12 @@ static pp_status run_tile(pp_graph g, bool adjoint, pp_dir dir, int32_t k, int32
     float* scal = reinterpret_cast<float*>(base + L.scal);
     const int64_t cells = (int64_t)n * KT;
     const dim3 cb(ceil_div(cells, 256)), ct(256);
-    if (adjoint) hipLaunchKernelGGL(k_kcol_adjoint_init<KT>, cb, ct, 0, st, n, k, col0, g->d.perm, g_caller, t0, t4);
-    else hipLaunchKernelGGL(k_kcol_forward_init<KT>, cb, ct, 0, st, n, src_int, col0, f, g->d.inv_s, t0, t2, t4);
+    // updates meet at shared FP64 accumulators (cleared here) only when they
+    // are sent as atomics, and in the sparse sweeps of PP_SWITCH
+    const bool atomics = dir == PP_PUSH && !g->tune.push_bins;
+    double* acc0 = (atomics || dir == PP_SWITCH) ? t4 : nullptr;
+    if (adjoint) hipLaunchKernelGGL(k_kcol_adjoint_init<KT>, cb, ct, 0, st, n, k, col0, g->d.perm, g_caller, t0, acc0);
+    else hipLaunchKernelGGL(k_kcol_forward_init<KT>, cb, ct, 0, st, n, src_int, col0, f, g->d.inv_s, t0, t2, acc0);
     PP_LAUNCH_CHECK("ppr tile init");
     float* prev = t0;   // current iterate
     float* next = t1;
@@ -987,8 +1050,12 @@ static pp_status run_tile(pp_graph g, bool adjoint, pp_dir dir, int32_t k, int32
             return PP_OK;
         }
     }
-    const bool pull = (dir != PP_PUSH);
+    // with a fixed number of sweeps a forward iterate is read by nobody (the
+    // next sweep gathers the scaled contributions): only the last one is
+    // written, straight to the caller's layout
+    const bool direct = !adjoint && tol == 0.f;
     for (int32_t t = t0_dense; t < iters; ++t) {
+        const bool last = t == iters - 1, check = tol > 0.f && !last;
         KArgs a{};
         a.kind = adjoint ? kEpiAdjoint : kEpiForward;
         a.inv_s = g->d.inv_s;
@@ -997,15 +1064,16 @@ static pp_status run_tile(pp_graph g, bool adjoint, pp_dir dir, int32_t k, int32
         a.k = k;
         a.col0 = col0;
         a.src_int = src_int;
-        a.prev = prev;
-        a.out_tile = next;
-        a.out_scaled = adjoint ? nullptr : c_nxt;
+        a.prev = check ? prev : nullptr;
+        a.out_tile = direct ? nullptr : next;
+        a.out_scaled = (adjoint || last) ? nullptr : c_nxt;
         a.g_caller = g_caller;
-        a.out_caller = nullptr;
-        a.resid_part = resid;
+        a.out_caller = (direct && last) ? out : nullptr;
+        a.caller4 = k % 4 == 0 && reinterpret_cast<uintptr_t>(out) % 16 == 0;
+        a.resid_part = check ? resid : nullptr;
         const float* moved = adjoint ? prev : c_cur;
         int32_t nres = 0;
-        if (pull) {
+        if (!atomics) {
             // forward pull gathers along CSC; the adjoint pull gathers along CSR
             const Walk w = adjoint ? walk_csr(g, KT) : walk_csc(g, KT);
             a.kp = w.kp;
@@ -1017,7 +1085,7 @@ static pp_status run_tile(pp_graph g, bool adjoint, pp_dir dir, int32_t k, int32
             a.tab_cap = g->split_cap;
             a.part = part;
             a.src = moved;
-            nres = launch_kpull<KT>(a, w.nsplit, st, g->weighted);
+            nres = launch_sweep<KT>(g, a, w.nsplit, st, dir == PP_PUSH);
             if (nres < 0) return set_error(PP_E_GRAPH, "inconsistent k-column sweep plan");
         } else {
             // forward push scatters along CSR; the adjoint push scatters along CSC
@@ -1040,7 +1108,7 @@ static pp_status run_tile(pp_graph g, bool adjoint, pp_dir dir, int32_t k, int32
         ++*done;
         std::swap(prev, next);
         std::swap(c_cur, c_nxt);
-        if (tol > 0.f && t + 1 < iters) {
+        if (check) {
             float r[2] = {0.f, 0.f};
             hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(1024), 0, st, nres, (const float*)resid, scal);
             PP_HIP(hipMemcpyAsync(r, scal, sizeof(r), hipMemcpyDeviceToHost, st));
@@ -1048,7 +1116,7 @@ static pp_status run_tile(pp_graph g, bool adjoint, pp_dir dir, int32_t k, int32
             if (r[0] <= tol * r[1]) break;  // L1 change relative to the L1 norm of the tile
         }
     }
-    *latest = prev;
+    *latest = (direct && iters > t0_dense) ? nullptr : prev;
     return PP_OK;
 }
 
@@ -1076,7 +1144,7 @@ static pp_status adjoint_grad(pp_graph g, int32_t k, int32_t col0, float f, cons
     a.tab_cap = g->split_cap;
     a.part = part;
     a.src = lam;
-    if (launch_kpull<KT>(a, w.nsplit, st, g->weighted) < 0)
+    if (launch_sweep<KT>(g, a, w.nsplit, st) < 0)
         return set_error(PP_E_GRAPH, "inconsistent k-column sweep plan");
     GradArgs ga{};
     ga.kp = kplan_pull4(w.kp, KT);
@@ -1144,7 +1212,7 @@ static pp_status unrolled_tile(pp_graph g, int32_t k, int32_t col0, int32_t T, f
             a.tab_cap = g->split_cap;
             a.part = part;
             a.src = c_cur;
-            if (launch_kpull<KT>(a, w.nsplit, st, g->weighted) < 0)
+            if (launch_sweep<KT>(g, a, w.nsplit, st) < 0)
                 return set_error(PP_E_GRAPH, "inconsistent k-column sweep plan");
             std::swap(c_cur, c_nxt);
         }
@@ -1228,12 +1296,13 @@ static pp_status ppr_call(const PprCall& c, int32_t* iters_done) {
     for (int32_t col0 = 0; col0 < c.k; col0 += KT) {
         float* latest = nullptr;
         int32_t done = 0;
-        pp_status s = run_tile<KT>(c.g, c.adjoint, c.dir, c.k, col0, c.iters, c.tol, c.f, src_int, c.g_caller, c.base,
-                                   c.L, &latest, &done, c.st);
+        pp_status s = run_tile<KT>(c.g, c.adjoint, c.dir, c.k, col0, c.iters, c.tol, c.f, src_int, c.g_caller, c.out,
+                                   c.base, c.L, &latest, &done, c.st);
         if (s != PP_OK) return s;
         most = std::max(most, done);
-        hipLaunchKernelGGL(k_tile_to_caller<KT>, dim3(ceil_div((int64_t)n * KT, 256)), dim3(256), 0, c.st, n, c.k,
-                           col0, c.g->d.perm, (const float*)latest, c.out);
+        if (latest)  // else the last sweep wrote the caller's columns
+            hipLaunchKernelGGL(k_tile_to_caller<KT>, dim3(ceil_div((int64_t)n * KT, 256)), dim3(256), 0, c.st, n, c.k,
+                               col0, c.g->d.perm, (const float*)latest, c.out);
         PP_LAUNCH_CHECK("ppr tile copy-out");
         if (c.adjoint) {
             float* t0 = reinterpret_cast<float*>(c.base + c.L.t0);

@@ -461,3 +461,40 @@ def test_adjoint_generic_switch_sparse_then_dense(name):
             lp, _, _ = pp.ppr_adjoint(g, X, ct, iters=12, f=F, k_tile=8, direction=pp.PP_PULL)
             assert (ls - lp).abs().max().item() <= 1e-5 * lp.abs().max().item()
         g.close()
+
+
+@pytest.mark.parametrize("kt", [8, 16, 32, 64])
+@pytest.mark.parametrize("weighted", [False, True])
+def test_rows_of_every_length_class_all_forms(kt, weighted):
+    # rows at the edges of the classes (a group, a wavefront, a workgroup, a
+    # chunk) in one graph; k leaves a partial tile and an unaligned row; pull
+    # and push (owner sums and atomics) against the oracle
+    rng = np.random.default_rng(kt + weighted)
+    n = 6000
+    s, t = [], []
+    for i, d in enumerate((1, 3, 4, 5, 16, 17, 63, 64, 65, 66, 300, 1023, 1024, 1025, 4095, 4096, 4097, 5500)):
+        s.append(rng.choice(n, d, replace=False))
+        t.append(np.full(d, 100 + 7 * i))
+    s.append(rng.integers(0, n, 20000))
+    t.append(rng.integers(1000, n, 20000))
+    host = gg.from_edges(n, np.concatenate(s), np.concatenate(t), False, name=f"classes{kt}")
+    host.ensure_transpose()
+    if weighted:
+        gg.with_weights(host, seed=3)
+    src = gg.pick_vertices(host, kt + 3, seed=7)
+    want, _ = oracle.ppr(host.off, host.idx, src, F, T=9, weights=host.weights)
+    got = {}
+    for on in (1, 0):
+        pp._lib.pp_set_push_bins(on)
+        try:
+            g = pp.Graph(host)
+        finally:
+            pp._lib.pp_set_push_bins(1)
+        for d in (pp.PP_PULL, pp.PP_PUSH):
+            announce(f"classes kt={kt} weighted={weighted} bins={on} dir={d}")
+            X, done = pp.ppr(g, src, iters=9, f=F, k_tile=kt, direction=d)
+            assert done == 9
+            got[on, d] = X.cpu().numpy().astype(np.float64)
+            assert np.abs(got[on, d] - want).sum(axis=0).max() <= 1e-6, (on, d)
+        g.close()
+    assert np.array_equal(got[1, pp.PP_PULL], got[0, pp.PP_PULL])
