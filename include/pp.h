@@ -342,8 +342,8 @@ size_t pp_ppr_scratch_bytes(pp_graph g, int32_t k, int32_t k_tile);
  * (sparse matrix times sparse vector along CSR, Sec. 7.1, FP64 atomics);
  * afterwards the tile continues with pulling sweeps.  Runs `iters` sweeps per
  * tile, or stops a tile early once the L1 change of its iterate in one sweep
- * is at most tol times the iterate's L1 norm (tol = 0: exactly iters; each
- * check synchronises the stream; PP_SWITCH also synchronises after each
+ * is at most tol times the iterate's L1 norm (tol = 0: exactly iters; the
+ * checks run on the device and the stream is synchronised every few sweeps; PP_SWITCH also synchronises after each
  * sparse sweep).  iters_done (host, nullable): most sweeps any tile ran.
  * k_tile = 1 runs the columns one after another with the single-vector
  * PageRank sweeps of pp_pr_run (PP_PUSH or PP_PULL, tol = 0 only; it uses

@@ -102,7 +102,10 @@ struct KArgs {
     float* out_caller;      // last iteration: caller layout n x k (nullable)
     bool caller4;           // its rows may be written four columns at a time
     float* resid_part;      // per-unit-group residual partials (nullable)
+    const int32_t* stop;    // nonzero once the tile has converged: nothing to do (nullable)
 };
+
+__device__ __forceinline__ bool kt_stopped(const int32_t* stop) { return stop && *stop != 0; }
 
 // Returns (|new - previous|, |new|) for the relative convergence test.
 template <int KT>
@@ -363,6 +366,7 @@ __global__ __launch_bounds__(kBlock) void k_kcol_sweep(KArgs a) {
     constexpr int G = kBlock / Q;
     __shared__ Sum4<T> red4[Q * (kBlock / kWave)];
     __shared__ float redf[2 * (kBlock / kWave)];
+    if (kt_stopped(a.stop)) return;
     const int q = threadIdx.x % Q;
     const int grp = threadIdx.x / Q;
     const int32_t unit = blockIdx.x;
@@ -403,6 +407,7 @@ __global__ __launch_bounds__(kBlock) void k_kcol_sweep(KArgs a) {
 // Finishes the chunked rows: partials in chunk order, then the epilogue.
 template <int KT, typename T>
 __global__ __launch_bounds__(kBlock) void k_kcol_fix(KArgs a, int32_t nsplit, float* resid_fix) {
+    if (kt_stopped(a.stop)) return;
     const int lane = threadIdx.x % KT;
     const int32_t i = blockIdx.x * (kBlock / KT) + threadIdx.x / KT;
     float2 res = make_float2(0.f, 0.f);
@@ -429,6 +434,7 @@ struct KPushArgs {
     int32_t tab_cap;
     const float* src;   // tile being scattered
     double* acc;        // accumulator tile, FP64 so the unordered atomic sum keeps FP32 accuracy
+    const int32_t* stop;
 };
 
 template <int KT, bool W>
@@ -444,6 +450,7 @@ __device__ __forceinline__ void kt_scatter(const KPushArgs& a, int32_t v, int32_
 
 template <int KT, bool W>
 __global__ __launch_bounds__(kBlock) void k_kcol_push(KPushArgs a) {
+    if (kt_stopped(a.stop)) return;
     constexpr int G = kBlock / KT;
     const int lane = threadIdx.x % KT;
     const int grp = threadIdx.x / KT;
@@ -470,6 +477,7 @@ __global__ __launch_bounds__(kBlock) void k_kcol_push(KPushArgs a) {
 // forward, nothing: the teleport is added by the epilogue).
 template <int KT>
 __global__ __launch_bounds__(kBlock) void k_kcol_push_epi(KArgs a, int32_t n, double* accum) {
+    if (kt_stopped(a.stop)) return;
     __shared__ float red[2 * (kBlock / kWave)];
     const int lane = threadIdx.x % KT;
     const int32_t u = blockIdx.x * (kBlock / KT) + threadIdx.x / KT;
@@ -530,26 +538,45 @@ __global__ void k_sources_internal(int32_t k, int32_t k_pad, const int32_t* __re
 }
 
 // Fixed-order sum of m (difference, norm) partial pairs (one workgroup).
-__global__ __launch_bounds__(1024) void k_sum_partials(int32_t m, const float* __restrict__ p, float* __restrict__ out) {
-    __shared__ float red[2][1024];
+__global__ __launch_bounds__(1024) void k_sum_partials(int32_t m, const float* __restrict__ p, float* __restrict__ out,
+                                                       float tol, int32_t sweeps, int32_t* __restrict__ stop) {
+    __shared__ float red[2][1024 / kWave];
+    if (kt_stopped(stop)) return;
+    const float2* p2 = reinterpret_cast<const float2*>(p);
     float d = 0.f, q = 0.f;
-    for (int32_t i = threadIdx.x; i < m; i += 1024) {
-        d += p[2 * i];
-        q += p[2 * i + 1];
+    constexpr int U = 4;
+    for (int32_t i0 = threadIdx.x; i0 < m; i0 += U * 1024) {
+        float2 v[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) v[k] = p2[min(i0 + k * 1024, m - 1)];
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+            if (i0 + k * 1024 < m) {
+                d += v[k].x;
+                q += v[k].y;
+            }
     }
-    red[0][threadIdx.x] = d;
-    red[1][threadIdx.x] = q;
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) {
+        d += __shfl_xor(d, s);
+        q += __shfl_xor(q, s);
+    }
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    if (lane == 0) {
+        red[0][w] = d;
+        red[1][w] = q;
+    }
     __syncthreads();
-    for (int s = 512; s > 0; s >>= 1) {
-        if (threadIdx.x < s) {
-            red[0][threadIdx.x] += red[0][threadIdx.x + s];
-            red[1][threadIdx.x] += red[1][threadIdx.x + s];
-        }
-        __syncthreads();
-    }
     if (threadIdx.x == 0) {
-        out[0] = red[0][0];
-        out[1] = red[1][0];
+        d = q = 0.f;
+#pragma unroll
+        for (int i = 0; i < 1024 / kWave; ++i) {
+            d += red[0][i];
+            q += red[1][i];
+        }
+        out[0] = d;
+        out[1] = q;
+        if (stop && d <= tol * q) *stop = sweeps;  // the L1 change relative to the L1 norm of the tile
     }
 }
 
@@ -993,7 +1020,8 @@ static pp_status sparse_phase(pp_graph g, bool adjoint, int32_t k, int32_t col0,
         std::swap(prev, next);
         std::swap(c_cur, c_nxt);
         if (tol > 0.f && t + 1 < iters)
-            hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(1024), 0, st, eb, (const float*)resid, scal);
+            hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(1024), 0, st, eb, (const float*)resid, scal,
+                               tol, 0, (int32_t*)nullptr);
         PP_HIP(hipMemcpyAsync(h, w.cnt, sizeof(h), hipMemcpyDeviceToHost, st));
         float r[2] = {0.f, 0.f};
         if (tol > 0.f && t + 1 < iters) PP_HIP(hipMemcpyAsync(r, scal, sizeof(r), hipMemcpyDeviceToHost, st));
@@ -1054,6 +1082,14 @@ static pp_status run_tile(pp_graph g, bool adjoint, pp_dir dir, int32_t k, int32
     // next sweep gathers the scaled contributions): only the last one is
     // written, straight to the caller's layout
     const bool direct = !adjoint && tol == 0.f;
+    // with a tolerance the test is made on the device and the sweeps behind a
+    // converged one do nothing, so the host looks only every kCheckEvery sweeps
+    // (a look at every one left the GPU idle for about 15 us each)
+    constexpr int32_t kCheckEvery = 8;
+    int32_t* stop = tol > 0.f ? reinterpret_cast<int32_t*>(scal) + 4 : nullptr;
+    if (stop) hipLaunchKernelGGL(k_zero_f32, dim3(1), dim3(64), 0, st, (int64_t)1, reinterpret_cast<float*>(stop));
+    float* const first = prev;
+    float* const second = next;
     for (int32_t t = t0_dense; t < iters; ++t) {
         const bool last = t == iters - 1, check = tol > 0.f && !last;
         KArgs a{};
@@ -1071,6 +1107,7 @@ static pp_status run_tile(pp_graph g, bool adjoint, pp_dir dir, int32_t k, int32
         a.out_caller = (direct && last) ? out : nullptr;
         a.caller4 = k % 4 == 0 && reinterpret_cast<uintptr_t>(out) % 16 == 0;
         a.resid_part = check ? resid : nullptr;
+        a.stop = stop;
         const float* moved = adjoint ? prev : c_cur;
         int32_t nres = 0;
         if (!atomics) {
@@ -1100,6 +1137,7 @@ static pp_status run_tile(pp_graph g, bool adjoint, pp_dir dir, int32_t k, int32
             p.tab_cap = g->split_cap;
             p.src = moved;
             p.acc = t4;
+            p.stop = stop;
             launch_kpush<KT>(p, st, g->weighted);
             hipLaunchKernelGGL(k_kcol_push_epi<KT>, dim3(ceil_div(n, kBlock / KT)), dim3(kBlock), 0, st, a, n, t4);
             nres = ceil_div(n, kBlock / KT);
@@ -1109,11 +1147,19 @@ static pp_status run_tile(pp_graph g, bool adjoint, pp_dir dir, int32_t k, int32
         std::swap(prev, next);
         std::swap(c_cur, c_nxt);
         if (check) {
-            float r[2] = {0.f, 0.f};
-            hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(1024), 0, st, nres, (const float*)resid, scal);
-            PP_HIP(hipMemcpyAsync(r, scal, sizeof(r), hipMemcpyDeviceToHost, st));
+            hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(1024), 0, st, nres, (const float*)resid, scal, tol, *done,
+                               stop);
+            PP_LAUNCH_CHECK("ppr residual");
+        }
+        if (stop && (last || (t + 1 - t0_dense) % kCheckEvery == 0)) {
+            int32_t at = 0;
+            PP_HIP(hipMemcpyAsync(&at, stop, sizeof(at), hipMemcpyDeviceToHost, st));
             PP_HIP(hipStreamSynchronize(st));
-            if (r[0] <= tol * r[1]) break;  // L1 change relative to the L1 norm of the tile
+            if (at != 0) {
+                *done = at;
+                prev = ((at - t0_dense) & 1) ? second : first;
+                break;
+            }
         }
     }
     *latest = (direct && iters > t0_dense) ? nullptr : prev;
