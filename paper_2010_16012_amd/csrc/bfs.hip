@@ -72,6 +72,20 @@ constexpr int32_t kSumMax = 1024;
 // Visited words the chunk kernel's top-down items test in LDS (120 KB; one
 // workgroup of it per compute unit).
 constexpr int32_t kChunkStage = 15360;
+// Levels of low-degree graphs on a few cooperating workgroups (k_bfs_deep):
+// workgroups, threads, and frontier vertices each holds in LDS.  Grids of
+// 1000 x 1031 / 2000 x 2001 from the corner: 16 workgroups 10.9 ms, 24 8.0 /
+// 22.3, 32 8.1 / 22.7-25.0, 64 8.1 / 20.5 (a level is bound by the misses a
+// compute unit keeps in flight, about 13 lines a frontier vertex).
+constexpr int32_t kDeepGroups = 64;
+constexpr int32_t kDeepBlock = 256;
+constexpr int32_t kDeepCap = 512;
+// Frontier vertices one workgroup runs alone (100 x 4000 grid: 12.9 ms at 128
+// and 256, 14.1 at 64; 300 x 301: 2.0 at 256, 3.0 at 128).
+constexpr int32_t kSoloMax = 256;
+constexpr int32_t kDeepPages = kDeepCap / kPage;  // queue pages a workgroup hands its share back in
+constexpr int32_t kDeepMaxDeg = 16;               // longest out-row of the graphs it runs on
+constexpr int32_t kDeepOffer = 8;                 // levels of a batch between two launches of it (even)
 
 struct BfsSlot {
     int32_t n;         // frontier size (accumulated by the level that builds it)
@@ -106,8 +120,18 @@ struct BfsHdr {
     int32_t log_n[PP_BFS_MAX_LOG];
 };
 
+// Rendezvous words of k_bfs_deep, a cache line each.
+struct DeepSync {
+    int32_t arrived, pad0[31];
+    int32_t verdict, pad1[31];   // 0: undecided, 1: run, 2: leave the level to the level kernels
+    struct {
+        uint64_t word;           // see deep_pack
+        uint64_t pad[15];
+    } level[3];
+};
+
 struct BfsLayout {
-    size_t hdr, queue0, queue1, fill0, fill1, fb0, fb1, fb2, visited, items, total;
+    size_t hdr, queue0, queue1, fill0, fill1, fb0, fb1, fb2, visited, items, deep, total;
     int32_t words, blocks, page_cap, item_cap, stage_words, sum_words;
 };
 
@@ -134,7 +158,8 @@ static BfsLayout bfs_layout(pp_graph g) {
     // the reserved pages (one per level-kernel wavefront); full pages hold at
     // most n entries; each wavefront of the level kernel and of the chunk
     // kernel (at most twice as many wavefronts) leaves at most one partial page
-    L.page_cap = waves + ceil_div(n, kPage) + 3 * waves + 2;
+    // (and a cooperating launch hands back in pages reserved per workgroup)
+    L.page_cap = waves + ceil_div(n, kPage) + 3 * waves + 2 + kDeepGroups * kDeepPages;
     // a row cut into chunks of c edges (longer than c) gives at most 2 len / c
     // items: a level queues at most 2 nnz / min(kBigRow, kBigInRow), and a
     // top-down level with m < nnz / 32 at most 2 m / 32 < nnz / 512 of
@@ -150,6 +175,7 @@ static BfsLayout bfs_layout(pp_graph g) {
     L.fb2 = take((size_t)L.words * 8);
     L.visited = take((size_t)L.words * 8);
     L.items = take((size_t)L.item_cap * 3 * 4);
+    L.deep = take(sizeof(DeepSync));
     L.total = p;
     return L;
 }
@@ -189,6 +215,7 @@ struct BfsArgs {
     uint64_t* fb[3];
     uint64_t* visited;
     int32_t* items;         // (v, begin, end) chunk items of long rows
+    DeepSync* deep;
     pp_bfs_level* log;      // per-level log (caller device memory; nullable)
     int32_t log_cap;        // entries of log
 };
@@ -232,6 +259,7 @@ static BfsArgs bfs_args(pp_graph g, void* state, int32_t* level, int32_t* parent
     a.fb[2] = reinterpret_cast<uint64_t*>(s + L.fb2);
     a.visited = reinterpret_cast<uint64_t*>(s + L.visited);
     a.items = reinterpret_cast<int32_t*>(s + L.items);
+    a.deep = reinterpret_cast<DeepSync*>(s + L.deep);
     a.log = nullptr;
     a.log_cap = 0;
     return a;
@@ -1417,6 +1445,287 @@ __global__ __launch_bounds__(kBfsBlock) void k_bfs_multi(BfsArgs a, int32_t poli
     }
 }
 
+// Top-down levels of low-degree graphs (grids, meshes, road networks: every
+// out-row at most kDeepMaxDeg edges) on kDeepGroups cooperating workgroups, many
+// levels in one launch.  A level of a few hundred to some ten thousand vertices
+// is a chain of round trips; as a level kernel of its own it pays for the
+// launch, the header, the queue pages and their counters as well (12 us a
+// level on a 1000 x 1031 grid).  Here a workgroup keeps its share of the
+// frontier in LDS -- whoever claims a vertex expands it -- and a level is the
+// claims and one rendezvous, which also sums the next frontier's size and
+// out-edges; while the others arrive, the next level's neighbours and what
+// their claims need are loaded.  3.9 us a level (3.1 alone, without the
+// rendezvous); the grid 21.1 -> 8.1 ms.
+//
+// Between workgroups nothing is passed but device-scope atomics (the visited
+// words, the rendezvous words), so no cache is flushed.  A launch whose
+// workgroups are not all on the chip cannot hang: the first rendezvous gives up
+// after kDeepWait looks, before anything was changed, and the level kernels
+// take the level; once all have met they all are resident.
+constexpr int32_t kDeepWait = 1 << 13;
+constexpr int32_t kDeepSpin = 1 << 22;  // looks at a later rendezvous before the run is given up as faulty
+
+// One rendezvous word: workgroups arrived (bits 56-63), workgroups whose share
+// would not fit (48-55), next frontier's vertices (28-47) and out-edges (0-27).
+constexpr int kDeepCntShift = 28, kDeepFullShift = 48, kDeepArriveShift = 56;
+static_assert((int64_t)kDeepGroups * kDeepCap * kDeepMaxDeg < (1 << kDeepCntShift) &&
+                  (int64_t)kDeepGroups * kDeepCap < (1 << (kDeepFullShift - kDeepCntShift)) && kDeepGroups < 256,
+              "rendezvous word fields");
+
+struct DeepEntry {
+    int32_t v;    // vertex
+    int32_t uid;  // its caller id
+    int32_t b, d; // out-row
+};
+
+// SOLO: one workgroup, frontiers of up to solo_max vertices (and as many
+// out-edges times kDeepMaxDeg): no rendezvous, and claims resolve in the local
+// L2.
+template <bool SOLO>
+__global__ __launch_bounds__(kDeepBlock) void k_bfs_deep(BfsArgs a, int32_t policy, float alpha, float beta,
+                                                         int32_t solo_max) {
+    constexpr int32_t kGroups = SOLO ? 1 : kDeepGroups;
+    extern __shared__ __align__(16) DeepEntry s_set[];  // two frontiers of kDeepCap entries
+    __shared__ int32_t s_cnt[2];
+    __shared__ int32_t s_deg;
+    __shared__ uint64_t s_word;
+    BfsHdr* h = a.hdr;
+    DeepSync* ds = a.deep;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    int32_t lvl = h->lv[0];
+    const SlotView in = view(h->slot[lvl % 3]);
+    // the same test in every workgroup: nothing it reads changes before all agree
+    if (h->finished || in.n <= 0 || (SOLO ? in.n > solo_max : in.m > kDeepGroups * kDeepCap / 2) || in.dir_prev != PP_PUSH ||
+        in.n_prev > a.words ||
+        !multi_push(policy, alpha, beta, a.n, lvl, in.n, in.m, in.mu_base, in.dir_prev, in.n_prev))
+        return;
+    if (tid < 2) s_cnt[tid] = 0;
+    if (tid == 0) s_deg = 0;
+    __syncthreads();
+    // this workgroup's pages of the frontier
+    {
+        const int32_t* q = a.queue[lvl & 1];
+        const int32_t* fill = a.fill[lvl & 1];
+        const int32_t pages = min(in.pages, a.page_cap);
+        const int32_t stride = kGroups * (kDeepBlock / kWave);
+        for (int32_t p = a.static_pages + blockIdx.x + kGroups * (tid / kWave); p < pages; p += stride) {
+            const int32_t f = min(fill[p], kPage);
+            int32_t base = 0;
+            if (lane == 0 && f > 0) base = atomicAdd(&s_cnt[0], f);
+            base = __shfl(base, 0);
+            for (int32_t i = lane; i < f; i += kWave)
+                if (base + i < kDeepCap) s_set[base + i].v = q[(size_t)p * kPage + i];
+        }
+    }
+    __syncthreads();
+    int32_t nloc = s_cnt[0];
+    int32_t share = 0;  // out-edges: as many claims must fit
+    for (int32_t i = tid; i < min(nloc, kDeepCap); i += kDeepBlock) {
+        DeepEntry e = s_set[i];
+        e.b = a.csr_off[e.v];
+        e.d = a.csr_off[e.v + 1] - e.b;
+        e.uid = user_id(a.perm, e.v);
+        s_set[i] = e;
+        share += e.d;
+    }
+    share = wave_sum(share);
+    if (lane == 0 && share) atomicAdd(&s_deg, share);
+    __syncthreads();
+    // all here, and every share fits?
+    if (tid == 0) {
+        int32_t go = 0;
+        if (SOLO) {
+            go = nloc == in.n && s_deg <= kDeepCap ? 1 : 2;
+        } else if (nloc > kDeepCap || s_deg > kDeepCap) {
+            atomicCAS(&ds->verdict, 0, 2);
+        } else if (atomicAdd(&ds->arrived, 1) == kDeepGroups - 1) {
+            atomicCAS(&ds->verdict, 0, 1);
+        }
+        for (int32_t i = 0; go == 0 && i < kDeepWait; ++i) {
+            go = __hip_atomic_load(&ds->verdict, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (go == 0) __builtin_amdgcn_s_sleep(1);
+        }
+        if (go == 0) {
+            go = atomicCAS(&ds->verdict, 0, 2);
+            if (go == 0) go = 2;
+        }
+        s_word = (uint64_t)go;
+        s_deg = 0;
+    }
+    __syncthreads();
+    if (s_word != 1) return;
+    // the frontier's bitmap words cleared, as a queue-driven level clears them
+    // (past the caches: they are set again on hand-back, by other workgroups)
+    uint64_t sunk = 0;
+    for (int32_t i = tid; i < nloc; i += kDeepBlock)
+        sunk |= atomicExch(reinterpret_cast<unsigned long long*>(&a.fb[lvl % 3][s_set[i].v >> 6]), 0ull);
+    asm volatile("" ::"v"((uint32_t)sunk), "v"((uint32_t)(sunk >> 32)));  // waited for
+    int32_t nf = in.n, n_prev = in.n_prev;
+    int64_t m = in.m, mu_base = in.mu_base, reached = 0, edges = 0;
+    int cur = 0;
+    bool full = false;
+    // the neighbours of one entry, four at a time, with what a claim of each needs
+    constexpr int U = 4;
+    struct Ahead {
+        int32_t u[U], rb[U], re[U], uid[U];
+    };
+    auto look = [&](const DeepEntry& e, int32_t j0, Ahead& x) {
+#pragma unroll
+        for (int k = 0; k < U; ++k) x.u[k] = j0 + k < e.d ? a.csr_idx[e.b + j0 + k] : -1;
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int32_t u = max(x.u[k], 0);
+            x.rb[k] = a.csr_off[u];
+            x.re[k] = a.csr_off[u + 1];
+            x.uid[k] = user_id(a.perm, u);
+        }
+    };
+    DeepEntry mine{-1, 0, 0, 0};  // this thread's first entry of the frontier
+    Ahead ahead;
+    __syncthreads();
+    if (tid < nloc) mine = s_set[tid];
+    look(mine, 0, ahead);
+    for (int32_t run = 0; nf != 0 && !full && run < kMultiLevels && (!SOLO || nf <= solo_max) &&
+                          multi_push(policy, alpha, beta, a.n, lvl, nf, m, mu_base, PP_PUSH, n_prev);
+         ++run) {
+        if (blockIdx.x == 0 && tid == 0) {
+            if (lvl < PP_BFS_MAX_LOG) {
+                h->log_dir[lvl] = (int8_t)PP_PUSH;
+                h->log_n[lvl] = nf;
+            }
+            if (lvl < a.log_cap) a.log[lvl] = pp_bfs_level{PP_PUSH, nf, m};
+        }
+        reached += nf;
+        edges += m;
+        const DeepEntry* A = s_set + cur * kDeepCap;
+        DeepEntry* B = s_set + (cur ^ 1) * kDeepCap;
+        int32_t deg = 0;
+        auto claim = [&](const DeepEntry& e, const Ahead& x) {
+            uint32_t old[U];
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                old[k] = ~0u;
+                if (x.u[k] >= 0)
+                    old[k] = __hip_atomic_fetch_or(reinterpret_cast<uint32_t*>(a.visited) + (x.u[k] >> 5),
+                                                   1u << (x.u[k] & 31), __ATOMIC_RELAXED,
+                                                   SOLO ? __HIP_MEMORY_SCOPE_WORKGROUP : __HIP_MEMORY_SCOPE_AGENT);
+            }
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const bool won = x.u[k] >= 0 && !((old[k] >> (x.u[k] & 31)) & 1u);
+                const uint64_t bal = __ballot(won);
+                if (!bal) continue;
+                int32_t base = 0;
+                if (lane == 0) base = atomicAdd(&s_cnt[cur ^ 1], __popcll(bal));
+                base = __shfl(base, 0);
+                if (won) {
+                    a.level[x.uid[k]] = lvl + 1;
+                    a.parent[x.uid[k]] = e.uid;
+                    deg += x.re[k] - x.rb[k];
+                    const int32_t at = base + __popcll(bal & lanes_below(lane));
+                    if (at < kDeepCap) B[at] = DeepEntry{x.u[k], x.uid[k], x.rb[k], x.re[k] - x.rb[k]};
+                    else atomicOr(&h->overflow, 4);  // cannot happen: a share with more out-edges stops the run
+                }
+            }
+        };
+        for (int32_t i0 = 0; i0 < nloc; i0 += kDeepBlock) {
+            if (i0 > 0) {
+                mine = i0 + tid < nloc ? A[i0 + tid] : DeepEntry{-1, 0, 0, 0};
+                look(mine, 0, ahead);
+            }
+            claim(mine, ahead);
+            for (int32_t j0 = U; __ballot(j0 < mine.d); j0 += U) {
+                look(mine, j0, ahead);
+                claim(mine, ahead);
+            }
+        }
+        deg = wave_sum(deg);
+        if (lane == 0 && deg) atomicAdd(&s_deg, deg);
+        __syncthreads();
+        unsigned long long* w = reinterpret_cast<unsigned long long*>(&ds->level[lvl % 3].word);
+        if (tid == 0) {
+            const int32_t c = s_cnt[cur ^ 1], d = s_deg;
+            s_cnt[cur] = 0;
+            s_deg = 0;
+            asm volatile("" ::"v"((uint32_t)sunk), "v"((uint32_t)(sunk >> 32)));  // the word cleared last is clear
+            // a share whose out-edges could all be claims must fit
+            s_word = (1ull << kDeepArriveShift) | ((unsigned long long)(d > kDeepCap ? 1 : 0) << kDeepFullShift) |
+                     ((unsigned long long)c << kDeepCntShift) | (unsigned long long)d;
+            if (!SOLO) atomicAdd(w, (unsigned long long)s_word);
+        }
+        // while the others arrive: the next level's entries and their neighbours
+        nloc = s_cnt[cur ^ 1];
+        mine = tid < nloc ? B[tid] : DeepEntry{-1, 0, 0, 0};
+        look(mine, 0, ahead);
+        if (!SOLO && tid == 0) {
+            uint64_t got = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int32_t i = 0; (got >> kDeepArriveShift) != kDeepGroups; ++i) {
+                if (i >= kDeepSpin) {
+                    atomicOr(&h->overflow, 4);
+                    got = (uint64_t)kDeepGroups << kDeepArriveShift;  // an empty frontier: everyone ends
+                    break;
+                }
+                got = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            // everyone has left the rendezvous before this one: its word is
+            // cleared here and next used two levels on
+            if (blockIdx.x == 0)
+                sunk = atomicExch(reinterpret_cast<unsigned long long*>(&ds->level[(lvl + 2) % 3].word), 0ull);
+            s_word = got;
+        }
+        __syncthreads();
+        const uint64_t got = s_word;
+        full = ((got >> kDeepFullShift) & 0xFF) != 0;
+        mu_base -= m;
+        n_prev = nf;
+        nf = (int32_t)((got >> kDeepCntShift) & ((1ull << (kDeepFullShift - kDeepCntShift)) - 1));
+        m = (int64_t)(got & ((1ull << kDeepCntShift) - 1));
+        ++lvl;
+        cur ^= 1;
+    }
+    // hand frontier lvl back: queue pages reserved per workgroup, bitmap bits
+    const DeepEntry* A = s_set + cur * kDeepCap;
+    const int32_t page0 = a.static_pages + (int32_t)blockIdx.x * kDeepPages;
+    int32_t* q = a.queue[lvl & 1];
+    int32_t* fill = a.fill[lvl & 1];
+    for (int32_t i = tid; i < min(nloc, kDeepCap); i += kDeepBlock) {
+        const int32_t v = A[i].v;
+        q[(size_t)page0 * kPage + i] = v;
+        atomicOr(reinterpret_cast<unsigned long long*>(&a.fb[lvl % 3][v >> 6]), 1ull << (v & 63));
+    }
+    if (tid < kDeepPages) fill[page0 + tid] = max(0, min(kPage, nloc - tid * kPage));
+    if (blockIdx.x == 0 && tid == 0) {
+        BfsSlot fresh{};
+        fresh.pages = a.static_pages;
+        BfsSlot o = fresh;
+        o.n = nf;
+        o.dir_prev = PP_PUSH;
+        o.n_prev = n_prev;
+        o.pages = a.static_pages + kGroups * kDeepPages;
+        o.m = m;
+        o.mu_base = mu_base;
+        h->slot[lvl % 3] = o;
+        h->slot[(lvl + 1) % 3] = fresh;
+        h->slot[(lvl + 2) % 3] = fresh;
+        h->lv[0] = lvl;
+        h->lv[1] = lvl;
+        h->c_lvl = -1;
+        h->levels = lvl;
+        h->last = lvl;
+        h->reached += reached;
+        h->edges += edges;
+        if (nf == 0) h->finished = 1;
+    }
+}
+
+// Clears the rendezvous words of the launch that follows.
+__global__ void k_bfs_deep_init(BfsArgs a) {
+    DeepSync* ds = a.deep;
+    if (threadIdx.x < 3) ds->level[threadIdx.x].word = 0;
+    if (threadIdx.x == 0) ds->arrived = 0;
+    if (threadIdx.x == 1) ds->verdict = 0;
+}
+
 static pp_status check_state(pp_graph g, void* state, size_t bytes) {
     if (!g) return set_error(PP_E_NULL, "graph handle is NULL");
     if (!state) return set_error(PP_E_NULL, "state is NULL");
@@ -1450,6 +1759,14 @@ static void multi_caps(pp_graph g, int32_t policy, int32_t* qcap, int32_t* ecap)
     *ecap = (*qcap > 0) ? g->tune.bfs_multi_m : 0;
     if (*ecap <= 0) *qcap = 0;
 }
+
+// Levels on cooperating workgroups: graphs whose out-rows are all short, where
+// the one-workgroup launch is not switched off.
+static bool deep_for(pp_graph g, int32_t policy) {
+    return policy != PP_PULL && g->max_out_deg <= kDeepMaxDeg && g->tune.bfs_multi_n > 0 &&
+           g->tune.bfs_multi_m > 0 && g->num_cu >= 2 * kDeepGroups;
+}
+constexpr unsigned kDeepLds = 2 * kDeepCap * sizeof(DeepEntry);
 
 static size_t multi_lds(int32_t qcap) { return (size_t)(6 * qcap + 2) * 4; }
 
@@ -1495,11 +1812,11 @@ static pp_status bfs_graph(pp_graph g, BfsArgs a, int32_t policy, float alpha, f
     hipGraph_t graph = nullptr;
     PP_HIP(hipGraphCreate(&graph, 0));
     hipGraphNode_t prev = nullptr;
-    auto add = [&](const void* fn, void** args, int32_t grid, unsigned shared) -> hipError_t {
+    auto add = [&](const void* fn, void** args, int32_t grid, unsigned shared, int32_t block = kBfsBlock) -> hipError_t {
         hipKernelNodeParams p{};
         p.func = const_cast<void*>(fn);
         p.gridDim = dim3(grid);
-        p.blockDim = dim3(kBfsBlock);
+        p.blockDim = dim3(block);
         p.sharedMemBytes = shared;
         p.kernelParams = args;
         p.extra = nullptr;
@@ -1509,17 +1826,35 @@ static pp_status bfs_graph(pp_graph g, BfsArgs a, int32_t policy, float alpha, f
         return e;
     };
     hipError_t e = hipSuccess;
-    // small top-down frontiers first go through the one-workgroup launch,
-    // which returns at once when the frontier is not one it takes on
+    // small top-down frontiers first go through a one-workgroup launch, and
+    // what outgrows it on a low-degree graph through the cooperating
+    // workgroups; all return at once when the frontier is not one they take
+    // on.  Where the latter run, a few bottom-up levels in between (the switch
+    // rule) must not leave the rest of a batch to the level kernels: both are
+    // offered the frontier again every kDeepOffer levels.
     int32_t qcap = 0, ecap = 0;
     multi_caps(g, policy, &qcap, &ecap);
-    if (qcap > 0) {
-        allow_dynamic_lds(reinterpret_cast<const void*>(&k_bfs_multi), multi_lds(qcap));
-        void* margs[] = {&a, &policy, &alpha, &beta, &qcap, &ecap};
-        e = add(reinterpret_cast<const void*>(&k_bfs_multi), margs, 1, (unsigned)multi_lds(qcap));
-    }
+    const bool deep = deep_for(g, policy);
+    if (qcap > 0) allow_dynamic_lds(reinterpret_cast<const void*>(&k_bfs_multi), multi_lds(qcap));
     int32_t lvl = -1;
     for (int32_t i = 0; i < batch && e == hipSuccess; ++i) {
+        if (i == 0 || (deep && i % kDeepOffer == 0)) {
+            if (deep) {
+                int32_t solo = std::min(kSoloMax, g->tune.bfs_multi_n);
+                void* dargs[] = {&a, &policy, &alpha, &beta, &solo};
+                void* iargs[] = {&a};
+                e = add(reinterpret_cast<const void*>(&k_bfs_deep<true>), dargs, 1, kDeepLds, kDeepBlock);
+                if (e == hipSuccess)
+                    e = add(reinterpret_cast<const void*>(&k_bfs_deep_init), iargs, 1, 0, kWave);
+                if (e == hipSuccess)
+                    e = add(reinterpret_cast<const void*>(&k_bfs_deep<false>), dargs, kDeepGroups, kDeepLds,
+                            kDeepBlock);
+            } else if (qcap > 0) {
+                void* margs[] = {&a, &policy, &alpha, &beta, &qcap, &ecap};
+                e = add(reinterpret_cast<const void*>(&k_bfs_multi), margs, 1, (unsigned)multi_lds(qcap));
+            }
+            if (e != hipSuccess) break;
+        }
         int32_t parity = i & 1;
         void* largs[] = {&a, &lvl, &parity, &policy, &alpha, &beta};
         e = add(reinterpret_cast<const void*>(&k_bfs_level), largs, blocks, lds);

@@ -384,3 +384,39 @@ def test_small_levels_cut_rows_into_short_chunks(centres):
             assert H.bfs_violations(host, leaf, lv, par) == []
             assert st.levels == nlev
             assert st.reached == host.n
+
+
+def _ring_lattice(n, half, extra, seed):
+    """Every vertex joined to the `half` next ones, and `extra` random pairs."""
+    rng = np.random.default_rng(seed)
+    v = np.arange(n)
+    s = np.concatenate([v] * half + [rng.integers(0, n, extra)])
+    t = np.concatenate([(v + k) % n for k in range(1, half + 1)] + [rng.integers(0, n, extra)])
+    return gg.from_edges(n, s, t, True, f"ring{n}_{half}_{extra}")
+
+
+@pytest.mark.parametrize("maker,roots", [
+    (lambda: gg.grid(700, 611, 0.05, seed=3), (0, 700 * 611 // 2)),   # frontiers past the one-workgroup caps
+    (lambda: gg.grid(40, 9000, 0.0, seed=3), (0, 123456)),            # narrow and deep
+    (lambda: gg.grid(3000, 3000, 0.0, seed=3), (3000 * 1500 + 1500,)),  # shares grow towards their limit
+    (lambda: _ring_lattice(200000, 3, 0, 5), (7,)),
+    (lambda: _ring_lattice(60000, 2, 3000, 6), (7, 59999)),           # shortcuts: frontiers spread, then outgrow it
+    (lambda: H.random_graph(50000, 75000, 8, symmetric=True, connected=True), (3,)),  # outgrows it at once
+], ids=["grid", "strip", "grid_centre", "lattice", "shortcuts", "random"])
+def test_low_degree_levels_on_cooperating_workgroups(maker, roots):
+    host = maker()
+    assert np.diff(host.off).max() <= 16
+    _check(host, roots, policies=[pp.PP_PUSH, pp.PP_SWITCH], fast=True)
+    # the per-level log does not depend on who ran the levels
+    logs = []
+    for caps in ((256, 1024), (0, 0)):
+        pp._lib.pp_set_bfs_multi(*caps)
+        try:
+            g = pp.Graph(host)
+        finally:
+            pp._lib.pp_set_bfs_multi(256, 1024)
+        st, dirs, nf, mf = pp.BfsRun(g).run_logged(int(roots[0]), pp.PP_PUSH)
+        logs.append((st.levels, st.reached, st.edges_reached, dirs, nf, mf))
+        g.close()
+    for a, b in zip(*logs):
+        np.testing.assert_array_equal(a, b)
