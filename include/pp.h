@@ -379,7 +379,7 @@ pp_status pp_ppr_adjoint(pp_graph g, pp_dir dir, int32_t k, const float* X, cons
  * total_vertices vertices together. */
 size_t pp_multi_workspace_bytes(int32_t num_graphs, int64_t total_vertices);
 
-/* PageRank and BFS for many small unweighted graphs in one launch (beyond
+/* PageRank and BFS for many small unweighted graphs in one call (beyond
  * the paper, which sweeps one graph at a time).  Graph i has graph_n[i]
  * vertices (1..16384) and graph_nnz[i] stored edges (HOST arrays).  Arenas
  * (device): off/in_off hold each graph's n+1 local offsets back to back (CSR
@@ -398,10 +398,14 @@ size_t pp_multi_workspace_bytes(int32_t num_graphs, int64_t total_vertices);
  * bfs_root of every graph with policy PP_PUSH / PP_PULL / PP_SWITCH
  * (alpha, beta as in pp_bfs_run).  One workgroup holds one graph's state in
  * LDS: pull gathers and push updates are LDS operations and the barrier
- * between sweeps is a workgroup barrier.  Pull sums every row in FP64 (per
+ * between sweeps is a workgroup barrier.  Where a graph has more than 49,152
+ * edges (and ws holds pp_multi_workspace_bytes), each PageRank step is a launch
+ * that shares the in-rows of all graphs among the compute units, in either
+ * direction (in_off/in_idx must be the transpose for PP_PUSH as well; x is
+ * used between the steps).  Pull sums every row in FP64 (per
  * lane in slot order, then a fixed lane reduction), so results are
- * bit-reproducible; push accumulates in FP64 LDS atomics.  Graphs are taken
- * largest first.  SYNC. */
+ * bit-reproducible; push accumulates in FP64 LDS atomics, or as the pull does
+ * in shared steps.  Graphs are taken largest first.  SYNC. */
 pp_status pp_multi_run(int32_t num_graphs, const int32_t* graph_n, const int64_t* graph_nnz,
                        const int32_t* off, const uint16_t* idx, const int32_t* in_off, const uint16_t* in_idx,
                        pp_dir pr_dir, int32_t pr_iters, float f, float* x,
@@ -423,7 +427,7 @@ pp_status pp_set_multi_tuning(int32_t big, int32_t mid, int32_t pull_group, int3
  * library instead of a caller workspace.  Each device the library runs on
  * holds one such array for the life of the process.  The call allocates
  * nothing; it fails with PP_E_WORKSPACE when
- * pp_multi_workspace_bytes(num_graphs, total vertices) exceeds
+ * the graph table and the push contributions of the call exceed
  * PP_MULTI_STATIC_BYTES (16 MiB: about 4 million vertices in all).  All calls
  * on one device share its array, so calls that overlap on one device (other
  * threads, other streams) race; order them.  Arguments, errors and results

@@ -1,4 +1,4 @@
-// Many small graphs in one launch: PageRank (push or pull) and BFS for every
+// Many small graphs in one call: PageRank (push or pull) and BFS for every
 // graph of a concatenated arena, one workgroup per graph.
 //
 // Parallelism beyond one graph (the paper's sweeps are per graph; Sec. 4
@@ -9,6 +9,13 @@
 // no grid-wide synchronisation, no spin waits.  Workgroups take graphs
 // largest first (longest-processing-time order) so the big graphs start
 // first and small ones fill in.
+//
+// One compute unit sweeps about 3.5 edges a nanosecond, so a batch with large
+// graphs waited for the largest alone (a scale-14 R-MAT graph: 134 us a sweep,
+// 2.7 of the 3.1 ms of a 128-graph batch, most of the chip idle).  Where a graph
+// has more than kStepEdges edges the PageRank steps therefore run as one launch
+// each (k_multi_step), the rows of all graphs shared among one workgroup per
+// compute unit: 40 us a step there, 1.07 ms in all.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -38,6 +45,7 @@ constexpr int32_t kMultiBigCap = 512;
 // wait.  The short pull rows take PG lanes each (tuned; 2 by default; the
 // push and BFS use kMultiGroup).
 constexpr int32_t kMultiMidCap = 4096;
+constexpr int32_t kBfsLong = kWave * kMultiU;  // out-rows a BFS level cuts up for the wavefronts
 
 struct MultiEntry {
     int64_t vbase;  // first vertex of the graph in the vertex arenas (x, level, parent)
@@ -98,18 +106,37 @@ __device__ __forceinline__ void gather_row_slots(const I* __restrict__ ids, cons
 // each of its nnz local ids lies below its n.  Both adjacencies are checked
 // unless they alias.  Every read stays inside the graph's own offsets and
 // slots, so a malformed arena is reported (PP_E_GRAPH), never walked.
+// kCheckParts workgroups share a graph and keep eight loads in flight a lane
+// (one 256-thread workgroup a graph, one load at a time, took 346 us over a
+// scale-14 R-MAT graph).
 constexpr int kCheckBlock = 256;
+constexpr int kCheckParts = 8;
 
-__device__ __forceinline__ bool offsets_ok(const int32_t* off, int32_t n, int32_t nnz) {
+__device__ __forceinline__ bool offsets_ok(const int32_t* off, int32_t n, int32_t nnz, int32_t t0, int32_t step) {
     bool ok = true;
-    for (int32_t v = threadIdx.x; v < n; v += kCheckBlock) ok &= off[v] <= off[v + 1];
-    if (threadIdx.x == 0) ok &= (off[0] == 0) && (off[n] == nnz);
+    constexpr int U = 4;
+    for (int32_t v0 = t0; v0 < n; v0 += U * step) {
+        int32_t a[U], b[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int32_t v = min(v0 + k * step, n - 1);
+            a[k] = off[v];
+            b[k] = off[v + 1];
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) ok &= a[k] <= b[k];
+    }
+    if (t0 == 0) ok &= (off[0] == 0) && (off[n] == nnz);
     return ok;
 }
 
-__device__ __forceinline__ bool ids_ok(const uint16_t* idx, int32_t n, int32_t nnz) {
+__device__ __forceinline__ bool ids_ok(const uint16_t* idx, int32_t n, int32_t nnz, int32_t t0, int32_t step) {
     uint32_t mx = 0;
-    for (int32_t j = threadIdx.x; j < nnz; j += kCheckBlock) mx = max(mx, (uint32_t)idx[j]);
+    constexpr int U = 8;
+    for (int64_t j0 = t0; j0 < nnz; j0 += (int64_t)U * step) {
+#pragma unroll
+        for (int k = 0; k < U; ++k) mx = max(mx, (uint32_t)idx[min(j0 + (int64_t)k * step, (int64_t)nnz - 1)]);
+    }
     return nnz == 0 || mx < (uint32_t)n;
 }
 
@@ -119,10 +146,228 @@ __global__ __launch_bounds__(kCheckBlock) void k_multi_check(const MultiEntry* _
                                                              const int32_t* __restrict__ in_off,
                                                              const uint16_t* __restrict__ in_idx, int32_t* err) {
     const MultiEntry e = table[blockIdx.x];
-    bool ok = offsets_ok(off + e.obase, e.n, e.nnz) && ids_ok(idx + e.ebase, e.n, e.nnz);
+    const int32_t t0 = blockIdx.y * kCheckBlock + threadIdx.x, step = kCheckParts * kCheckBlock;
+    bool ok = offsets_ok(off + e.obase, e.n, e.nnz, t0, step) && ids_ok(idx + e.ebase, e.n, e.nnz, t0, step);
     if (in_off != off || in_idx != idx)
-        ok = ok && offsets_ok(in_off + e.obase, e.n, e.nnz) && ids_ok(in_idx + e.ebase, e.n, e.nnz);
+        ok = ok && offsets_ok(in_off + e.obase, e.n, e.nnz, t0, step) &&
+             ids_ok(in_idx + e.ebase, e.n, e.nnz, t0, step);
     if (!ok) atomicOr(err, 1);
+}
+
+// Rows [r0, r1) of one graph pull: in-rows of at least `big` slots (listed in
+// s_big) a wavefront each, of `mid`..`big`-1 (s_mid) ML lanes each, the others
+// PG lanes each, rows spread over the wavefronts.  Every lane sums in FP64, in
+// slot order; finish(u, sum, out-degree) runs in one lane of the row's owner.
+// The offsets and out-degree of a group's next row load while a row is summed.
+template <int PG, int ML, typename F>
+__device__ __forceinline__ void multi_pull_rows(const int32_t* in_off, const uint16_t* in_idx, const int32_t* off,
+                                                const float* s_c, const float* s_zero, const int32_t* s_big,
+                                                int32_t nbig, const int32_t* s_mid, int32_t nmid, int32_t big,
+                                                int32_t mid, int32_t r0, int32_t r1, F finish) {
+    const int tid = threadIdx.x, wl = tid & (kWave - 1), wv = tid / kWave;
+    constexpr int kWaves = kMultiBlock / kWave;
+    // does row length d belong to the small groups?
+    auto grouped = [=](int32_t d) { return !((nbig > 0 && d >= big) || (nmid > 0 && d >= mid && d < big)); };
+    for (int32_t i = wv; i < nbig; i += kWaves) {
+        const int32_t u = s_big[i];
+        double acc = 0.0;
+        const int32_t rb = in_off[u], re = in_off[u + 1];
+        for (int32_t j0 = rb + wl; j0 < re; j0 += kMultiU * kWave)
+            gather_row_slots<kWave, kMultiU>(in_idx, s_c, s_zero, j0, re, acc);
+#pragma unroll
+        for (int s = kWave / 2; s > 0; s >>= 1) acc += __shfl_xor(acc, s);
+        if (wl == 0) finish(u, acc, off[u + 1] - off[u]);
+    }
+    {
+        const int hl = wl & (ML - 1);  // lane within a middle-row group
+        const int32_t mslot = (kWave / ML) * wv + wl / ML;  // its group
+        constexpr int32_t mgroups = kMultiBlock / ML;
+        int32_t nu = 0, nrb = 0, nre = 0, nob = 0, noe = 0;
+        if (mslot < nmid) {
+            nu = s_mid[mslot];
+            nrb = in_off[nu];
+            nre = in_off[nu + 1];
+            nob = off[nu];
+            noe = off[nu + 1];
+        }
+        for (int32_t i = mslot; i < nmid; i += mgroups) {
+            const int32_t u = nu, rb = nrb, re = nre, ob = nob, oe = noe;
+            if (i + mgroups < nmid) {
+                nu = s_mid[i + mgroups];
+                nrb = in_off[nu];
+                nre = in_off[nu + 1];
+                nob = off[nu];
+                noe = off[nu + 1];
+            }
+            double acc = 0.0;
+            for (int32_t j0 = rb + hl; j0 < re; j0 += kMultiU * ML)
+                gather_row_slots<ML, kMultiU>(in_idx, s_c, s_zero, j0, re, acc);
+#pragma unroll
+            for (int s = ML / 2; s > 0; s >>= 1) acc += __shfl_xor(acc, s);
+            if (hl == 0) finish(u, acc, oe - ob);
+        }
+    }
+    const int plane = tid % PG;
+    const int32_t prow0 = r0 + kWaves * ((tid % kWave) / PG) + wv;
+    constexpr int32_t pgroups = kMultiBlock / PG;
+    int32_t nrb = 0, nre = 0, nob = 0, noe = 0;
+    if (prow0 < r1) {
+        nrb = in_off[prow0];
+        nre = in_off[prow0 + 1];
+        nob = off[prow0];
+        noe = off[prow0 + 1];
+    }
+    for (int32_t u = prow0; u < r1; u += pgroups) {
+        double acc = 0.0;
+        const int32_t rb = nrb, re = nre, ob = nob, oe = noe;
+        if (u + pgroups < r1) {
+            nrb = in_off[u + pgroups];
+            nre = in_off[u + pgroups + 1];
+            nob = off[u + pgroups];
+            noe = off[u + pgroups + 1];
+        }
+        if (!grouped(re - rb)) continue;  // group-uniform
+        for (int32_t j0 = rb + plane; j0 < re; j0 += kMultiPullU * PG)
+            gather_row_slots<PG, kMultiPullU>(in_idx, s_c, s_zero, j0, re, acc);
+#pragma unroll
+        for (int s = PG / 2; s > 0; s >>= 1) acc += __shfl_xor(acc, s);
+        if (plane == 0) finish(u, acc, oe - ob);
+    }
+}
+
+// Lists the long and middle rows of [r0, r1) (roff: the sweep's direction); a
+// list that would overflow counts as empty, its rows stay with the small
+// groups.  Workgroup-collective.
+__device__ __forceinline__ int2 multi_lists(const int32_t* roff, int32_t r0, int32_t r1, int32_t big, int32_t mid,
+                                            int32_t* s_big, int32_t big_cap, int32_t* s_mid, int32_t mid_cap,
+                                            int32_t* s_n) {
+    if (threadIdx.x < 2) s_n[threadIdx.x] = 0;
+    __syncthreads();
+    for (int32_t u = r0 + (int32_t)threadIdx.x; u < r1; u += kMultiBlock) {
+        const int32_t d = roff[u + 1] - roff[u];
+        if (d >= big) {
+            const int32_t at = atomicAdd(&s_n[0], 1);
+            if (at < big_cap) s_big[at] = u;
+        } else if (d >= mid) {
+            const int32_t at = atomicAdd(&s_n[1], 1);
+            if (at < mid_cap) s_mid[at] = u;
+        }
+    }
+    __syncthreads();
+    return make_int2(s_n[0] <= big_cap ? s_n[0] : 0, s_n[1] <= mid_cap ? s_n[1] : 0);
+}
+
+// ------------------------------------------------------- shared PageRank steps
+// A workgroup's part of one graph: rows [r0, r1).  The host gives shares of the
+// graph's cost (kStepGraphCost, kStepRowCost a row and one a slot);
+// k_multi_pieces turns them into rows once per call.
+struct MultiPiece {
+    int32_t entry;   // of the graph table
+    int32_t r0, r1;  // costs, then rows
+};
+constexpr int32_t kStepGroups = 256;  // workgroups of a step, one a compute unit (512: 45 us against 40)
+// A launch costs a step about 14 us whatever is in it, and a workgroup of k_multi
+// sweeps this many edges in that time; four scale-13 graphs (250,000 edges the
+// largest) went from 1.57 to 0.37 ms, 64 of scales 8-12 from 0.83 to 0.38.
+constexpr int32_t kStepEdges = 49152;
+// What a row and the beginning of a graph cost in slots.  Beginning a graph is a
+// chain of loads (its rows' offsets, the stage, the lists, the first ids) some
+// 8 us long: with shares of edges alone the workgroups that got 14 small graphs
+// took the whole step (74 us; 50, 40, 41 and 40 at 4096, 8192, 16384 and 32768;
+// rows at 2, 8 and 16: 80, 74 and 69 without it, 43 and 40 at 8 and 16 with it).
+constexpr int32_t kStepGraphCost = 8192;
+constexpr int32_t kStepRowCost = 16;
+
+// First row before which the graph, rows and slots cost t or more.
+__global__ void k_multi_pieces(const MultiEntry* __restrict__ table, const int32_t* __restrict__ in_off, int32_t count,
+                               MultiPiece* __restrict__ pc, const int32_t* __restrict__ err) {
+    const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= count || *err) return;
+    const MultiEntry e = table[pc[i].entry];
+    const int32_t* off = in_off + e.obase;
+    auto row = [&](int32_t t) {
+        int32_t lo = 0, hi = e.n;
+        while (lo < hi) {
+            const int32_t m = (lo + hi) >> 1;
+            if (kStepGraphCost + (int64_t)off[m] + (int64_t)kStepRowCost * m >= t) hi = m;
+            else lo = m + 1;
+        }
+        return lo;
+    };
+    const int32_t t0 = pc[i].r0, t1 = pc[i].r1;
+    pc[i].r0 = t0 <= 0 ? 0 : row(t0);
+    pc[i].r1 = t1 == INT32_MAX ? e.n : row(t1);
+}
+
+struct StepArgs {
+    const MultiEntry* table;
+    const MultiPiece* pc;
+    const int32_t* wg;       // first piece of every workgroup [kStepGroups + 1]
+    const int32_t* off;
+    const int32_t* in_off;
+    const uint16_t* in_idx;
+    const float* c;          // contributions; NULL: those of x_0 = 1/n
+    float* c_next;           // NULL after the last step
+    float* x;                // last step
+    const int32_t* err;
+    float f;
+    int32_t big, mid;        // row-length thresholds of the wavefront and middle groups
+};
+
+// One PageRank step of every graph: a workgroup stages the contributions of a
+// piece's graph in LDS and pulls the piece's rows as k_multi does (the pushing
+// form too: an FP64 sum over the in-edges is what the FP64 adds of the out-edges
+// come to, rounded once).  Bound by latency: the pieces' rows of a 128-graph batch are 32 MB of
+// ids, 5 us at the rate of memory.  Laying the gathered values down in slot order
+// and summing rows from there took 73 to 100 us a step against 74 of this form,
+// before the shares knew what a graph costs.
+template <int PG, int ML>
+__global__ __launch_bounds__(kMultiBlock) void k_multi_step(StepArgs a) {
+    extern __shared__ __align__(16) float s_c[];  // [largest n]
+    __shared__ int32_t s_big[kMultiBigCap];
+    __shared__ int32_t s_mid[kMultiMidCap];
+    __shared__ int32_t s_n[2];
+    __shared__ float s_zero;
+    if (*a.err) return;
+    const int tid = threadIdx.x;
+    if (tid == 0) s_zero = 0.f;
+    const int32_t p1 = a.wg[blockIdx.x + 1];
+    int32_t staged = -1;
+    for (int32_t p = a.wg[blockIdx.x]; p < p1; ++p) {
+        const MultiPiece pc = a.pc[p];
+        const MultiEntry e = a.table[pc.entry];
+        const int32_t* off = a.off + e.obase;
+        const int32_t* in_off = a.in_off + e.obase;
+        const int32_t n = e.n;
+        if (pc.r0 >= pc.r1) continue;
+        __syncthreads();  // the previous piece is done with the stage and the lists
+        if (pc.entry != staged) {
+            constexpr int V = 8;
+            for (int32_t u0 = tid; u0 < n; u0 += V * kMultiBlock) {
+                float v[V];
+                int32_t d[V];
+#pragma unroll
+                for (int k = 0; k < V; ++k) {
+                    const int32_t u = min(u0 + k * kMultiBlock, n - 1);
+                    if (a.c) v[k] = a.c[e.vbase + u];
+                    else d[k] = off[u + 1] - off[u];
+                }
+#pragma unroll
+                for (int k = 0; k < V; ++k)
+                    if (u0 + k * kMultiBlock < n)
+                        s_c[u0 + k * kMultiBlock] = a.c ? v[k] : d[k] > 0 ? a.f * (1.0f / (float)n) / (float)d[k] : 0.f;
+            }
+            staged = pc.entry;
+        }
+        const float base = (1.0f - a.f) / (float)n;
+        const int2 cnt = multi_lists(in_off, pc.r0, pc.r1, a.big, a.mid, s_big, kMultiBigCap, s_mid, kMultiMidCap, s_n);
+        multi_pull_rows<PG, ML>(in_off, a.in_idx + e.ebase, off, s_c, &s_zero, s_big, cnt.x, s_mid, cnt.y, a.big, a.mid,
+                                pc.r0, pc.r1, [&](int32_t u, double acc, int32_t d) {
+                                    const float y = (float)((double)base + acc);
+                                    if (a.c_next) a.c_next[e.vbase + u] = d > 0 ? a.f * y / (float)d : 0.f;
+                                    else a.x[e.vbase + u] = y;
+                                });
+    }
 }
 
 template <int PG, int ML>
@@ -152,35 +397,16 @@ __global__ __launch_bounds__(kMultiBlock) void k_multi(MultiArgs a) {
 
     // ---------------------------------------------------------------- PageRank
     __shared__ int32_t s_big[kMultiBigCap];
-    __shared__ int32_t s_nbig;
     __shared__ int32_t s_mid[kMultiMidCap];
-    __shared__ int32_t s_nmid;
+    __shared__ int32_t s_n[2];
     __shared__ float s_zero;
     if (a.pr_iters > 0) {
         const float base = (1.0f - a.f) / (float)n;
         // the long rows of the sweep's direction (in-rows pull, out-rows push)
         const int32_t* roff = (a.pr_dir == PP_PULL) ? in_off : off;
-        if (tid == 0) {
-            s_nbig = 0;
-            s_nmid = 0;
-            s_zero = 0.f;
-        }
-        __syncthreads();
-        for (int32_t u = tid; u < n; u += kMultiBlock) {
-            const int32_t d = roff[u + 1] - roff[u];
-            if (d >= big) {
-                const int32_t at = atomicAdd(&s_nbig, 1);
-                if (at < kMultiBigCap) s_big[at] = u;
-            } else if (d >= mid) {
-                const int32_t at = atomicAdd(&s_nmid, 1);
-                if (at < kMultiMidCap) s_mid[at] = u;
-            }
-        }
-        __syncthreads();
-        // more long (middle) rows than a list holds: those rows stay with the
-        // small groups
-        const int32_t nbig = (s_nbig <= kMultiBigCap) ? s_nbig : 0;
-        const int32_t nmid = (s_nmid <= kMultiMidCap) ? s_nmid : 0;
+        if (tid == 0) s_zero = 0.f;
+        const int2 cnt = multi_lists(roff, 0, n, big, mid, s_big, kMultiBigCap, s_mid, kMultiMidCap, s_n);
+        const int32_t nbig = cnt.x, nmid = cnt.y;
         // does row length d belong to the small groups?
         auto grouped = [=](int32_t d) {
             return !((nbig > 0 && d >= big) || (nmid > 0 && d >= mid && d < big));
@@ -198,90 +424,12 @@ __global__ __launch_bounds__(kMultiBlock) void k_multi(MultiArgs a) {
             __syncthreads();
             for (int32_t t = 0; t < a.pr_iters; ++t) {
                 const bool last = (t == a.pr_iters - 1);
-                // long in-rows: a whole wavefront each (FP64 sum per lane)
-                for (int32_t i = wv; i < nbig; i += kWaves) {
-                    const int32_t u = s_big[i];
-                    double acc = 0.0;
-                    const int32_t rb = in_off[u], re = in_off[u + 1];
-                    for (int32_t j0 = rb + wl; j0 < re; j0 += kMultiU * kWave)
-                        gather_row_slots<kWave, kMultiU>(in_idx, s_c, &s_zero, j0, re, acc);
-#pragma unroll
-                    for (int s = kWave / 2; s > 0; s >>= 1) acc += __shfl_xor(acc, s);
-                    if (wl == 0) {
-                        const float y = (float)((double)base + acc);
-                        const int32_t d = off[u + 1] - off[u];
-                        s_y[u] = d > 0 ? a.f * y / (float)d : 0.f;
-                        if (last) a.x[e.vbase + u] = y;
-                    }
-                }
-                // middle in-rows: 16 lanes each; the next row's offsets load
-                // while this one is summed
-                {
-                    int32_t nu = 0, nrb = 0, nre = 0, nob = 0, noe = 0;
-                    if (mslot < nmid) {
-                        nu = s_mid[mslot];
-                        nrb = in_off[nu];
-                        nre = in_off[nu + 1];
-                        nob = off[nu];
-                        noe = off[nu + 1];
-                    }
-                    for (int32_t i = mslot; i < nmid; i += mgroups) {
-                        const int32_t u = nu, rb = nrb, re = nre, ob = nob, oe = noe;
-                        if (i + mgroups < nmid) {
-                            nu = s_mid[i + mgroups];
-                            nrb = in_off[nu];
-                            nre = in_off[nu + 1];
-                            nob = off[nu];
-                            noe = off[nu + 1];
-                        }
-                        double acc = 0.0;
-                        for (int32_t j0 = rb + hl; j0 < re; j0 += kMultiU * ML)
-                            gather_row_slots<ML, kMultiU>(in_idx, s_c, &s_zero, j0, re, acc);
-#pragma unroll
-                        for (int s = ML / 2; s > 0; s >>= 1) acc += __shfl_xor(acc, s);
-                        if (hl == 0) {
-                            const float y = (float)((double)base + acc);
-                            const int32_t d = oe - ob;
-                            s_y[u] = d > 0 ? a.f * y / (float)d : 0.f;
-                            if (last) a.x[e.vbase + u] = y;
-                        }
-                    }
-                }
-                // other rows: the group owning u gathers over its in-row (FP64
-                // sum per lane, PG lanes per row, rows spread over
-                // the wavefronts as above); the offsets and out-degree of the
-                // group's next row load while this row is summed
-                const int plane = tid % PG;
-                const int32_t prow0 = kWaves * ((tid % kWave) / PG) + wv;
-                constexpr int32_t pgroups = kMultiBlock / PG;
-                int32_t nrb = 0, nre = 0, nob = 0, noe = 0;
-                if (prow0 < n) {
-                    nrb = in_off[prow0];
-                    nre = in_off[prow0 + 1];
-                    nob = off[prow0];
-                    noe = off[prow0 + 1];
-                }
-                for (int32_t u = prow0; u < n; u += pgroups) {
-                    double acc = 0.0;
-                    const int32_t rb = nrb, re = nre, ob = nob, oe = noe;
-                    if (u + pgroups < n) {
-                        nrb = in_off[u + pgroups];
-                        nre = in_off[u + pgroups + 1];
-                        nob = off[u + pgroups];
-                        noe = off[u + pgroups + 1];
-                    }
-                    if (!grouped(re - rb)) continue;  // group-uniform
-                    for (int32_t j0 = rb + plane; j0 < re; j0 += kMultiPullU * PG)
-                        gather_row_slots<PG, kMultiPullU>(in_idx, s_c, &s_zero, j0, re, acc);
-#pragma unroll
-                    for (int s = PG / 2; s > 0; s >>= 1) acc += __shfl_xor(acc, s);
-                    if (plane == 0) {
-                        const float y = (float)((double)base + acc);
-                        const int32_t d = oe - ob;
-                        s_y[u] = d > 0 ? a.f * y / (float)d : 0.f;
-                        if (last) a.x[e.vbase + u] = y;
-                    }
-                }
+                multi_pull_rows<PG, ML>(in_off, in_idx, off, s_c, &s_zero, s_big, nbig, s_mid, nmid, big, mid, 0, n,
+                                        [&](int32_t u, double acc, int32_t d) {
+                                            const float y = (float)((double)base + acc);
+                                            s_y[u] = d > 0 ? a.f * y / (float)d : 0.f;
+                                            if (last) a.x[e.vbase + u] = y;
+                                        });
                 __syncthreads();
                 float* tmp = s_c;
                 s_c = s_y;
@@ -459,36 +607,65 @@ __global__ __launch_bounds__(kMultiBlock) void k_multi(MultiArgs a) {
         int32_t my_new = 0;
         int64_t my_deg = 0;
         if (dir == PP_PUSH) {
-            // frontier vertices claim unvisited out-neighbours (LDS atomic OR)
+            // frontier vertices claim unvisited out-neighbours (LDS atomic OR):
+            // slots j0, j0 + stride, ... of v's row, which ends at re
+            auto scatter = [&](int32_t v, int32_t j0, int32_t stride, int32_t re) {
+                // index loads clamped to the row's last slot, then every
+                // visited probe issued before the first claim (a probe only
+                // filters: the atomic OR decides)
+                int32_t ii[kMultiU];
+#pragma unroll
+                for (int k = 0; k < kMultiU; ++k) ii[k] = idx[(uint32_t)min(j0 + k * stride, re - 1)];
+                uint32_t seen[kMultiU];
+#pragma unroll
+                for (int k = 0; k < kMultiU; ++k) seen[k] = s_vis[min(ii[k], n - 1) >> 5];
+#pragma unroll
+                for (int k = 0; k < kMultiU; ++k) {
+                    const int32_t u = ii[k];
+                    if (j0 + k * stride >= re || u >= n) continue;  // ids past the graph are ignored
+                    const uint32_t b = 1u << (u & 31);
+                    if (seen[k] & b) continue;
+                    const uint32_t old = atomicOr(&s_vis[u >> 5], b);
+                    if (!(old & b)) {
+                        atomicOr(&s_next[u >> 5], b);
+                        a.level[e.vbase + u] = lvl + 1;
+                        a.parent[e.vbase + u] = v;
+                        my_new += 1;
+                        my_deg += off[u + 1] - off[u];
+                    }
+                }
+            };
+            // rows of kBfsLong or more are cut into pieces of as many edges for
+            // the wavefronts (four lanes on the root's row of thousands held
+            // up the whole level); a full list leaves the rest to the groups
+            if (tid == 0) s_n[0] = 0;
+            __syncthreads();
             for (int32_t v = grp; v < n; v += groups) {
                 if (!bit_of(s_front, v)) continue;
                 const int32_t rb = off[v], re = off[v + 1];
-                for (int32_t j0 = rb + lane; j0 < re; j0 += kMultiU * kMultiGroup) {
-                    // index loads clamped to the row's last slot, then every
-                    // visited probe issued before the first claim (a probe only
-                    // filters: the atomic OR decides)
-                    int32_t ii[kMultiU];
-#pragma unroll
-                    for (int k = 0; k < kMultiU; ++k) ii[k] = idx[(uint32_t)min(j0 + k * kMultiGroup, re - 1)];
-                    uint32_t seen[kMultiU];
-#pragma unroll
-                    for (int k = 0; k < kMultiU; ++k) seen[k] = s_vis[min(ii[k], n - 1) >> 5];
-#pragma unroll
-                    for (int k = 0; k < kMultiU; ++k) {
-                        const int32_t u = ii[k];
-                        if (j0 + k * kMultiGroup >= re || u >= n) continue;  // ids past the graph are ignored
-                        const uint32_t b = 1u << (u & 31);
-                        if (seen[k] & b) continue;
-                        const uint32_t old = atomicOr(&s_vis[u >> 5], b);
-                        if (!(old & b)) {
-                            atomicOr(&s_next[u >> 5], b);
-                            a.level[e.vbase + u] = lvl + 1;
-                            a.parent[e.vbase + u] = v;
-                            my_new += 1;
-                            my_deg += off[u + 1] - off[u];
-                        }
+                if (re - rb >= kBfsLong) {
+                    int32_t at = 0;
+                    if (lane == 0) at = atomicAdd(&s_n[0], 1);
+                    at = __shfl(at, (tid & (kWave - 1)) - lane);
+                    if (at < kMultiMidCap) {
+                        if (lane == 0) s_mid[at] = v;
+                        continue;
                     }
                 }
+                for (int32_t j0 = rb + lane; j0 < re; j0 += kMultiU * kMultiGroup) scatter(v, j0, kMultiGroup, re);
+            }
+            __syncthreads();
+            const int32_t nlong = min(s_n[0], kMultiMidCap);
+            int32_t turn = wv;  // pieces until this wavefront's next one
+            for (int32_t i = 0; i < nlong; ++i) {
+                const int32_t v = s_mid[i];
+                const int32_t rb = off[v], re = off[v + 1];
+                const int32_t np = (re - rb + kBfsLong - 1) / kBfsLong;
+                for (; turn < np; turn += kWaves) {
+                    const int32_t b = rb + turn * kBfsLong, pe = min(re, b + kBfsLong);
+                    if (b + wl < pe) scatter(v, b + wl, kWave, pe);
+                }
+                turn -= np;
             }
         } else {
             // unvisited vertices look for a frontier in-neighbour, first in stored order
@@ -555,14 +732,14 @@ static void launch_multi_k(const MultiArgs& a, int32_t grid, size_t lds, hipStre
     hipLaunchKernelGGL((k_multi<PG, ML>), dim3(grid), dim3(kMultiBlock), lds, st, a);
 }
 
-// The instantiation for the tuned group widths (false: none).
-static bool launch_multi(int32_t pg, int32_t ml, const MultiArgs& a, int32_t grid, size_t lds, hipStream_t st) {
+// Calls fn with the tuned group widths as types (false: no such kernel).
+template <typename F>
+static bool with_widths(int32_t pg, int32_t ml, F fn) {
     auto by_ml = [&](auto pg_tag) {
-        constexpr int P = decltype(pg_tag)::value;
         switch (ml) {
-            case 8: launch_multi_k<P, 8>(a, grid, lds, st); return true;
-            case 16: launch_multi_k<P, 16>(a, grid, lds, st); return true;
-            case 32: launch_multi_k<P, 32>(a, grid, lds, st); return true;
+            case 8: fn(pg_tag, std::integral_constant<int, 8>{}); return true;
+            case 16: fn(pg_tag, std::integral_constant<int, 16>{}); return true;
+            case 32: fn(pg_tag, std::integral_constant<int, 32>{}); return true;
             default: return false;
         }
     };
@@ -574,10 +751,18 @@ static bool launch_multi(int32_t pg, int32_t ml, const MultiArgs& a, int32_t gri
     }
 }
 
+static bool launch_multi(int32_t pg, int32_t ml, const MultiArgs& a, int32_t grid, size_t lds, hipStream_t st) {
+    return with_widths(pg, ml, [&](auto p, auto m) {
+        launch_multi_k<decltype(p)::value, decltype(m)::value>(a, grid, lds, st);
+    });
+}
+
 // Workspace: the graph table (LPT order) and the validation error word, both
 // written by one host copy, then the push contributions (one float per vertex).
+// After those, where it fits, what the shared steps need: the pieces and every
+// workgroup's first one.
 struct MultiLayout {
-    size_t table, err, cbuf, total;
+    size_t table, err, cbuf, base, pieces, wg, total;
 };
 
 static MultiLayout multi_layout(int32_t count, int64_t total_n) {
@@ -585,7 +770,10 @@ static MultiLayout multi_layout(int32_t count, int64_t total_n) {
     L.table = 0;
     L.err = (size_t)std::max(count, 1) * sizeof(MultiEntry);
     L.cbuf = align_up(L.err + sizeof(int32_t), 256);
-    L.total = L.cbuf + align_up((size_t)std::max<int64_t>(total_n, 1) * 4, 256);
+    L.base = L.cbuf + align_up((size_t)std::max<int64_t>(total_n, 1) * 4, 256);
+    L.pieces = L.base;
+    L.wg = L.pieces + align_up(((size_t)std::max(count, 1) + kStepGroups) * sizeof(MultiPiece), 256);
+    L.total = L.wg + align_up((kStepGroups + 1) * sizeof(int32_t), 256);
     return L;
 }
 
@@ -668,8 +856,8 @@ static pp_status multi_run(int32_t num_graphs, const int32_t* graph_n, const int
     }
     if (total_nnz > 0 && (!idx || !in_idx)) return set_error(PP_E_NULL, "idx and in_idx are required");
     const MultiLayout ML = multi_layout(num_graphs, vb);
-    if (static_ws && ML.total > kMultiStaticBytes)
-        return set_error(PP_E_WORKSPACE, "pp_multi_run_static: the graphs need " + std::to_string(ML.total) +
+    if (static_ws && ML.base > kMultiStaticBytes)
+        return set_error(PP_E_WORKSPACE, "pp_multi_run_static: the graphs need " + std::to_string(ML.base) +
                                              " bytes of scratch, more than its " + std::to_string(kMultiStaticBytes) +
                                              " (use pp_multi_run with a caller workspace)");
     if (static_ws) {
@@ -677,7 +865,7 @@ static pp_status multi_run(int32_t num_graphs, const int32_t* graph_n, const int
         if (st_ptr != PP_OK) return st_ptr;
         ws_bytes = kMultiStaticBytes;
     }
-    if (ws_bytes < ML.total) return set_error(PP_E_WORKSPACE, "workspace too small");
+    if (ws_bytes < ML.base) return set_error(PP_E_WORKSPACE, "workspace too small");
     // largest graphs first (workgroups are dispatched roughly in index order)
     std::vector<int32_t> order(num_graphs);
     std::iota(order.begin(), order.end(), 0);
@@ -699,7 +887,7 @@ static pp_status multi_run(int32_t num_graphs, const int32_t* graph_n, const int
     PP_HIP(hipMemcpyAsync(table, head.data(), head.size(), hipMemcpyHostToDevice, st));
     const uint16_t* idx_chk = idx ? idx : in_idx;  // both NULL only when no graph has edges
     const uint16_t* in_idx_chk = in_idx ? in_idx : idx;
-    hipLaunchKernelGGL(k_multi_check, dim3(num_graphs), dim3(kCheckBlock), 0, st, (const MultiEntry*)table, off,
+    hipLaunchKernelGGL(k_multi_check, dim3(num_graphs, kCheckParts), dim3(kCheckBlock), 0, st, (const MultiEntry*)table, off,
                        idx_chk, in_off, in_idx_chk, err);
     PP_LAUNCH_CHECK("k_multi_check");
     MultiArgs a;
@@ -724,7 +912,72 @@ static pp_status multi_run(int32_t num_graphs, const int32_t* graph_n, const int
     const Tuning& t = tuning();
     a.big = t.multi_big;
     a.mid = t.multi_mid;
-    if (!launch_multi(t.multi_pull_group, t.multi_mid_lanes, a, num_graphs, lds, st))
+    // a batch with large graphs: the steps shared among all workgroups first,
+    // then (with no steps left to it) the launch below for the searches.
+    // (The costs of a graph of 2^30 edges or more do not fit a piece.)
+    std::vector<MultiPiece> pieces;
+    std::vector<int32_t> wg;
+    if (pr_iters > 0 && dev[0].nnz > kStepEdges && dev[0].nnz < (1 << 30) && ws_bytes >= ML.total) {
+        auto cost_of = [&](int32_t i) { return kStepGraphCost + dev[i].nnz + kStepRowCost * (int64_t)dev[i].n; };
+        int64_t total = 0, run = 0;
+        for (int32_t i = 0; i < num_graphs; ++i) total += cost_of(i);
+        const int64_t quota = std::max<int64_t>(1, (total + kStepGroups - 1) / kStepGroups);
+        wg.push_back(0);
+        for (int32_t i = 0; i < num_graphs; ++i) {
+            const int64_t cost = cost_of(i);
+            int64_t at = 0;
+            while (at < cost) {
+                const int64_t take = std::min(cost - at, quota * (int64_t)wg.size() - run);
+                const int64_t end = at + take;
+                pieces.push_back(MultiPiece{i, (int32_t)at, end >= cost ? INT32_MAX : (int32_t)end});
+                at = end;
+                run += take;
+                if (run >= quota * (int64_t)wg.size() && (int32_t)wg.size() < kStepGroups)
+                    wg.push_back((int32_t)pieces.size());
+            }
+        }
+        while ((int32_t)wg.size() <= kStepGroups) wg.push_back((int32_t)pieces.size());
+    }
+    if (!pieces.empty()) {
+        char* base = static_cast<char*>(ws);
+        StepArgs sa{};
+        MultiPiece* pc = reinterpret_cast<MultiPiece*>(base + ML.pieces);
+        PP_HIP(hipMemcpyAsync(pc, pieces.data(), pieces.size() * sizeof(MultiPiece), hipMemcpyHostToDevice, st));
+        PP_HIP(hipMemcpyAsync(base + ML.wg, wg.data(), wg.size() * sizeof(int32_t), hipMemcpyHostToDevice, st));
+        hipLaunchKernelGGL(k_multi_pieces, dim3(ceil_div((int64_t)pieces.size(), 64)), dim3(64), 0, st,
+                           (const MultiEntry*)table, in_off, (int32_t)pieces.size(), pc, (const int32_t*)err);
+        sa.table = table;
+        sa.pc = pc;
+        sa.wg = reinterpret_cast<const int32_t*>(base + ML.wg);
+        sa.off = off;
+        sa.in_off = in_off;
+        sa.in_idx = in_idx;
+        sa.err = err;
+        sa.f = f;
+        sa.big = a.big;
+        sa.mid = a.mid;
+        const size_t step_lds = (size_t)max_n * sizeof(float);
+        bool known = true;
+        // the contributions go back and forth between the scratch and x, so
+        // that the last step, which writes x, reads the scratch
+        float* buf[2] = {a.c_scratch, x};
+        for (int32_t i = 0; i < pr_iters; ++i) {
+            const int32_t to_end = pr_iters - 1 - i;
+            sa.c = i == 0 ? nullptr : buf[to_end & 1];
+            sa.c_next = to_end == 0 ? nullptr : buf[(to_end - 1) & 1];
+            sa.x = x;
+            known = with_widths(t.multi_pull_group, t.multi_mid_lanes, [&](auto p, auto m) {
+                auto kern = &k_multi_step<decltype(p)::value, decltype(m)::value>;
+                if (i == 0) allow_dynamic_lds(reinterpret_cast<const void*>(kern), step_lds);
+                hipLaunchKernelGGL(kern, dim3(kStepGroups), dim3(kMultiBlock), step_lds, st, sa);
+            });
+        }
+        if (!known) return set_error(PP_E_RANGE, "many-graph tuning: unsupported group widths");
+        PP_LAUNCH_CHECK("k_multi_step");
+        a.pr_iters = 0;
+    }
+    const size_t lds_run = a.pr_iters > 0 ? lds : (size_t)3 * ((max_n + 31) / 32) * 4;
+    if ((a.pr_iters > 0 || bfs_policy >= 0) && !launch_multi(t.multi_pull_group, t.multi_mid_lanes, a, num_graphs, lds_run, st))
         return set_error(PP_E_RANGE, "many-graph tuning: unsupported group widths");
     PP_LAUNCH_CHECK("k_multi");
     int32_t herr = 0;

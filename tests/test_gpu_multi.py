@@ -169,3 +169,47 @@ def test_every_tuned_mapping_matches_the_oracle(big, mid, pg, ml):
         _check(gs, policies=(pp.PP_SWITCH,))
     finally:
         _lib.pp_set_multi_tuning(512, 64, 2, 16)
+
+
+@pytest.mark.parametrize("d", [pp.PP_PULL, pp.PP_PUSH])
+@pytest.mark.parametrize("directed", [False, True])
+@pytest.mark.parametrize("iters", [1, 2, 5])
+def test_steps_shared_among_workgroups(d, directed, iters):
+    # a graph of more than 49,152 edges: each step is a launch whose workgroups
+    # take rows of all graphs.  Rows longer than a workgroup's share, graphs of
+    # one vertex and of no edges, and many tiny graphs in one share; a workspace
+    # one byte short of what the steps need takes the one-launch form instead.
+    announce(f"multi steps dir={d} directed={directed} iters={iters}")
+    n = 16384
+    gs = [gg.rmat(14, 16, seed=3), H.star(n), gg.from_edges(1, [], [], True), gg.from_edges(700, [], [], True)]
+    gs += [H.path(k) for k in range(2, 302)] + [H.complete(300)]
+    if directed:
+        gs += [H.random_graph(n, 60_000, 5, symmetric=False), H.random_graph(63, 200, 6, symmetric=False)]
+        for h in gs:
+            h.ensure_transpose()
+    mg = pp.MultiGraph(gs)
+    want = [oracle.pagerank(h.off, h.idx, F, iters) for h in gs]
+    for ws in (mg.ws, mg.ws[:-1]):
+        x = torch.full((mg.total_n,), -7.0, device="cuda")
+        lv = torch.empty(mg.total_n, dtype=torch.int32, device="cuda")
+        par = torch.empty_like(lv)
+        _lib.pp_multi_run(mg.n, mg.nnz, mg.off, mg.idx, mg.in_off, mg.in_idx, d, iters, F, x, pp.PP_SWITCH, 0, 14.0,
+                          24.0, lv, par, ws)
+        for h, xi, wi, li in zip(gs, mg.split(x.cpu().numpy()), want, mg.split(lv.cpu().numpy())):
+            assert np.abs(xi.astype(np.float64) - wi).sum() <= PR_L1_TOL, h.name
+            assert np.array_equal(li, oracle.bfs(h.off, h.idx, 0)[0]), h.name
+
+
+def test_malformed_large_graph_leaves_the_outputs():
+    # the steps use x between them; a bad id keeps every launch off it
+    h = gg.rmat(13, 16, seed=3)
+    mg = pp.MultiGraph([h])
+    mg.idx[h.nnz - 1] = h.n  # in_idx aliases it
+    for d in (pp.PP_PULL, pp.PP_PUSH):
+        x = torch.full((mg.total_n,), -7.0, device="cuda")
+        lv = torch.full((mg.total_n,), -9, dtype=torch.int32, device="cuda")
+        with pytest.raises(pp.PPError) as ei:
+            _lib.pp_multi_run(mg.n, mg.nnz, mg.off, mg.idx, mg.in_off, mg.in_idx, d, 3, F, x, pp.PP_SWITCH, 0, 14.0,
+                              24.0, lv, lv.clone(), mg.ws)
+        assert ei.value.status == _lib.PP_E_GRAPH
+        assert bool((x == -7.0).all()) and bool((lv == -9).all())
