@@ -479,7 +479,9 @@ pp_status pp_tc_run(pp_graph g, pp_dir dir, int64_t* tc, void* ws, size_t ws_byt
 /* Workspace bytes of pp_bc_run for graph g (device, caller-owned, 256-byte
  * aligned): per source of a batch of up to 32, its distances, path counts,
  * dependencies, BFS order and level offsets (about 28 n bytes each).  A
- * smaller workspace (at least one source's share) runs smaller batches. */
+ * smaller workspace (at least one source's share) runs smaller batches.  With
+ * both directions PP_PULL the batch's values lie source-minor instead, where
+ * they fit. */
 size_t pp_bc_workspace_bytes(pp_graph g);
 
 /* Betweenness centrality over a set of sources (Sec. 3.5; Brandes' scheme as
@@ -495,7 +497,8 @@ size_t pp_bc_workspace_bytes(pp_graph g);
  * atomics; PP_PULL: vertices sum over their successors (owner writes).
  * sources: HOST int32[num_sources] (caller ids); bc: double[n] device,
  * caller ids, overwritten.  Sources run up to 32 at a time (they are
- * independent), each level kernel covering all sources of the batch; the
+ * independent), each level kernel covering all sources of the batch (with
+ * both directions PP_PULL they share one walk of the adjacency); the
  * level bookkeeping is on the device.  The call synchronises the stream once
  * per batch of forward levels (usually once per batch of sources) to read
  * the depths, then queues the backward levels. */

@@ -101,3 +101,28 @@ def test_source_batches_and_small_workspace():
     with pytest.raises(pp.PPError):
         _lib.pp_bc_run(g.handle, pp.PP_PULL, pp.PP_PULL, src[:2], bc, torch.empty(1024, dtype=torch.uint8,
                                                                                    device=g.device))
+
+
+@pytest.mark.parametrize("count", [1, 4, 5, 8, 9, 16, 17, 32, 33])
+def test_sources_that_share_their_levels(count):
+    # both passes pulling: every width of the batch, full and not, with a source
+    # given twice; rows cut into several pieces, groups of rows at and past the
+    # edge count that a wavefront takes together, more than 32 levels, vertices
+    # that no source reaches, and a workspace that holds a single source's slab
+    hosts = [H.star(1500), H.complete(260), H.path(75), gg.rmat(11, 8, seed=2),
+             gg.from_edges(70, [1, 2, 3, 3], [2, 3, 4, 68], True)]
+    hosts.append(H.random_graph(300, 9000, 7, symmetric=False))
+    hosts[-1].ensure_transpose()
+    # eight rows of 32 edges each (a group of exactly 256), then of 33
+    for d in (32, 33):
+        hosts.append(gg.from_edges(8 + d, np.repeat(np.arange(8), d), np.tile(8 + np.arange(d), 8), True))
+    for h in hosts:
+        src = np.random.default_rng(count).integers(0, h.n, count)
+        src[-1] = src[0]
+        want = _check(h, src, [(pp.PP_PULL, pp.PP_PULL)])
+        g = pp.Graph(h)
+        bc = torch.empty(h.n, dtype=torch.float64, device="cuda")
+        slab = (pp.pp_bc_workspace_bytes(g.handle) - 1024) // 32
+        pp.pp_bc_run(g.handle, pp.PP_PULL, pp.PP_PULL, src, bc,
+                     torch.empty(1024 + slab, dtype=torch.uint8, device="cuda"), None)
+        np.testing.assert_allclose(bc.cpu().numpy(), want, rtol=RTOL, atol=1e-9 * max(1.0, np.abs(want).max()))
