@@ -387,6 +387,22 @@ __device__ __forceinline__ void page_append(const BfsArgs& a, Pager& pg, bool mi
     pg.fill = k - room;
 }
 
+// One page for each of the first `waves` wavefronts of the workgroup, taken
+// together where all of them will want one: 4,096 wavefronts that each took
+// their first page from the one counter kept a level of 140,000 edges waiting
+// for 45 of its 61 us.  Workgroup-collective.
+__device__ __forceinline__ void page_reserve(const BfsArgs& a, Pager& pg, int32_t waves, BfsSlot* nxt) {
+    __shared__ int32_t s_first;
+    if (waves <= 0) return;
+    if (threadIdx.x == 0) {
+        s_first = atomicAdd(&nxt->pages, waves);
+        if (s_first + waves > a.page_cap) atomicOr(&a.hdr->overflow, 1);
+    }
+    __syncthreads();
+    const int w = threadIdx.x / kWave;
+    if (w < waves && s_first + w < a.page_cap) pg = Pager{s_first + w, 0};
+}
+
 __device__ __forceinline__ void page_close(const Pager& pg, int32_t* fill, int lane) {
     if (lane == 0 && pg.page >= 0) fill[pg.page] = pg.fill;
 }
@@ -509,6 +525,9 @@ __device__ __forceinline__ void queue_chunks(const BfsArgs& a, bool huge, int32_
 }
 
 // ------------------------------------------------------------------ top-down
+// RUN: part of a whole run, whose level[] pp_bfs_init wrote (a step may be given
+// any array).
+template <bool RUN>
 struct TdCtx {
     int32_t lvl;
     int32_t* q_next;
@@ -521,11 +540,28 @@ struct TdCtx {
     // which pays on large levels; small levels go straight to the atomic and
     // save a round trip
     bool probe;
-    int32_t big_row;  // out-rows longer than this become chunk items
+    int32_t big_row;   // edges of a chunk item
+    int32_t min_item;  // out-rows longer than this become chunk items
+    uint32_t* s_new = nullptr;  // LDS: bits claimed in 32-bit words [0, agg), handed on at the end
+    int32_t agg = 0;
 };
 
 // Below this many frontier out-edges a level claims without probing first.
 constexpr int64_t kProbeMin = 1 << 16;
+
+// On large levels read from the bitmap the rows of more than kMinItem edges are
+// items too: word by word, the 64 hub rows of one word were the longest chain of
+// the level (R-MAT 21, 48 million edges: 392 + 208 us at 256, 138 + 354 at 64;
+// 32 is level with 64, 128 between).  Rows longer than that, of m edges
+// together, give at most m / kMinItem items.
+constexpr int32_t kMinItem = 64;
+static_assert(kMinItem >= (kBigRow < kBigInRow ? kBigRow : kBigInRow) / 2, "chunk item bound");
+
+// The chunk kernel of a small level collects the bits it claims in the hottest
+// kAggWords words in LDS (7.3 -> 6.6 us a launch at R-MAT 20; levels of few edges
+// are not worth the clearing).
+constexpr int32_t kAggWords = 1024;
+constexpr int64_t kAggMin = 4096;
 
 // Claims the targets u[r] (parents pv[r]; -1 = no edge) of kTdU rounds of
 // 64 edges.  The rounds are independent, so their loads and atomics are
@@ -534,8 +570,8 @@ constexpr int kTdU = 4;
 
 // ONE_PARENT: every edge of the batch leaves one vertex, pv[0] (a row or a
 // chunk of one), so its caller id is looked up once.
-template <bool ONE_PARENT = false>
-__device__ __forceinline__ void td_batch(const BfsArgs& a, const TdCtx& cx, Pager& pg, const int32_t (&u)[kTdU],
+template <bool ONE_PARENT = false, bool RUN>
+__device__ __forceinline__ void td_batch(const BfsArgs& a, const TdCtx<RUN>& cx, Pager& pg, const int32_t (&u)[kTdU],
                                          const int32_t (&pv)[kTdU], int32_t& cnt, int64_t& deg, int lane) {
     // Bits are tested and claimed in the 32-bit half of their 64-bit word
     // (the same bit, little-endian), which halves the registers the loads
@@ -571,16 +607,25 @@ __device__ __forceinline__ void td_batch(const BfsArgs& a, const TdCtx& cx, Page
         claimed[r] = false;
         const uint32_t bit = 1u << (u[r] & 31);
         if (need[r]) {
-            const uint32_t old = atomicOr(&vis32[u[r] >> 5], bit);
-            claimed[r] = !(old & bit);
+            // a run claims by the level entry: the bitmap has 1,024 vertices to
+            // a line, and atomics that return from one line go one by one
+            // (49 hub rows that share their targets: 89 -> 61 us)
+            if (RUN) claimed[r] = atomicCAS(&a.level[uid[r]], -1, cx.lvl + 1) == -1;
+            else claimed[r] = !(atomicOr(&vis32[u[r] >> 5], bit) & bit);
         }
     }
 #pragma unroll
     for (int r = 0; r < kTdU; ++r) {
         if (claimed[r]) {
-            a.level[uid[r]] = cx.lvl + 1;
+            const uint32_t bit = 1u << (u[r] & 31);
+            if (!RUN) a.level[uid[r]] = cx.lvl + 1;
             a.parent[uid[r]] = pid[r];
-            atomicOr(reinterpret_cast<uint32_t*>(cx.fb_next) + (u[r] >> 5), 1u << (u[r] & 31));
+            if ((u[r] >> 5) < cx.agg) {
+                atomicOr(&cx.s_new[u[r] >> 5], bit);
+            } else {
+                if (RUN) atomicOr(&vis32[u[r] >> 5], bit);
+                atomicOr(reinterpret_cast<uint32_t*>(cx.fb_next) + (u[r] >> 5), bit);
+            }
             cnt += 1;
             deg += od[r];
         }
@@ -591,9 +636,29 @@ __device__ __forceinline__ void td_batch(const BfsArgs& a, const TdCtx& cx, Page
     }
 }
 
+// Clears the words that collect claims, and hands them on.  Workgroup-collective.
+template <bool RUN>
+__device__ __forceinline__ void agg_begin(const TdCtx<RUN>& cx) {
+    if (cx.agg == 0) return;
+    for (int32_t w = threadIdx.x; w < cx.agg; w += blockDim.x) cx.s_new[w] = 0u;
+    __syncthreads();
+}
+template <bool RUN>
+__device__ __forceinline__ void agg_end(const BfsArgs& a, const TdCtx<RUN>& cx) {
+    if (cx.agg == 0) return;
+    __syncthreads();
+    for (int32_t w = threadIdx.x; w < cx.agg; w += blockDim.x) {
+        const uint32_t m = cx.s_new[w];
+        if (m == 0) continue;
+        atomicOr(reinterpret_cast<uint32_t*>(a.visited) + w, m);
+        atomicOr(reinterpret_cast<uint32_t*>(cx.fb_next) + w, m);
+    }
+}
+
 // Edges [b, e) of the row of v, 64 x kTdU at a time.  Wave-collective
 // (b, e, v wave-uniform).
-__device__ __forceinline__ void td_row(const BfsArgs& a, const TdCtx& cx, Pager& pg, int32_t v, int32_t b,
+template <bool RUN>
+__device__ __forceinline__ void td_row(const BfsArgs& a, const TdCtx<RUN>& cx, Pager& pg, int32_t v, int32_t b,
                                        int32_t e, int32_t& cnt, int64_t& deg, int lane) {
     for (int32_t jb = b; jb < e; jb += kTdU * kWave) {
         int32_t u[kTdU], pv[kTdU];
@@ -618,7 +683,8 @@ struct WaveLds {
 
 // The 64 frontier vertices v of one unit (-1 = none) expand their out-rows.
 // Wave-collective.
-__device__ __forceinline__ void td_unit(const BfsArgs& a, const TdCtx& cx, WaveLds& sl, Pager& pg, int32_t v,
+template <bool RUN>
+__device__ __forceinline__ void td_unit(const BfsArgs& a, const TdCtx<RUN>& cx, WaveLds& sl, Pager& pg, int32_t v,
                                         int32_t& cnt, int64_t& deg) {
     auto& s_start = sl.a;
     auto& s_rb = sl.b;
@@ -629,7 +695,7 @@ __device__ __forceinline__ void td_unit(const BfsArgs& a, const TdCtx& cx, WaveL
     const int32_t re = (v >= 0) ? a.csr_off[v + 1] : 0;
     int32_t len = re - rb;
     // very long rows: queue chunks for the second kernel
-    const bool huge = len > cx.big_row;
+    const bool huge = len > cx.min_item;
     if (__ballot(huge)) {
         queue_chunks(a, huge, v, rb, re, cx.big_row, cx.nxt, lane);
         if (huge) len = 0;
@@ -680,14 +746,15 @@ __device__ __forceinline__ void td_unit(const BfsArgs& a, const TdCtx& cx, WaveL
 
 // by_bitmap: the frontier is large, so it is read from its bitmap word by
 // word (ascending ids: coalesced offsets, rows in memory order).  Otherwise
-// it is read from the queue in units of 64 slots (a quarter page), one unit
+// it is read from the queue in units of up to 64 slots (a quarter page), one unit
 // per wavefront at a time; a wavefront loads the page fills and entries of up
 // to four of its units in one round trip (entries past a fill are stale but
 // inside the queue).  A queue-driven level never reads the frontier bitmap,
 // so its vertices clear their words there: the bitmap is clean when it is
 // reused two levels on, without a full clear.
 // Queue pages [first, pages) hold the frontier.
-__device__ __forceinline__ void level_top_down(const BfsArgs& a, const TdCtx& cx, WaveLds& sl, const int32_t* q_cur,
+template <bool RUN>
+__device__ __forceinline__ void level_top_down(const BfsArgs& a, const TdCtx<RUN>& cx, WaveLds& sl, const int32_t* q_cur,
                                                const int32_t* fill_cur, int32_t first, int32_t pages,
                                                uint64_t* fb_cur, bool by_bitmap, int32_t& cnt, int64_t& deg,
                                                Pager& pg) {
@@ -702,10 +769,15 @@ __device__ __forceinline__ void level_top_down(const BfsArgs& a, const TdCtx& cx
         }
         return;
     }
-    constexpr int kUnitsPerPage = kPage / kWave;
     constexpr int kAhead = 4;
-    const int32_t nunits = pages * kUnitsPerPage;
-    for (int32_t u0 = first * kUnitsPerPage + gwave; u0 < nunits; u0 += kAhead * nwaves) {
+    // slots of a unit: as few as give every wavefront one unit, so that a compact
+    // queue of hubs does not go to a handful of wavefronts (441 hubs of 1.2 million
+    // edges: 101 -> 16 us)
+    int32_t per = kWave;
+    while (per > 1 && (int64_t)(pages - first) * (kPage / (per >> 1)) <= nwaves) per >>= 1;
+    const int32_t per_page = kPage / per;
+    const int32_t nunits = pages * per_page;
+    for (int32_t u0 = first * per_page + gwave; u0 < nunits; u0 += kAhead * nwaves) {
         int32_t left[kAhead], qv[kAhead];  // entries of each unit (<= 0: none), lane's entry
 #pragma unroll
         for (int j = 0; j < kAhead; ++j) {
@@ -713,9 +785,9 @@ __device__ __forceinline__ void level_top_down(const BfsArgs& a, const TdCtx& cx
             left[j] = 0;
             qv[j] = -1;
             if (unit < nunits) {
-                const int32_t p = unit / kUnitsPerPage, s = (unit % kUnitsPerPage) * kWave;
-                left[j] = min(fill_cur[p], kPage) - s;
-                qv[j] = q_cur[(size_t)p * kPage + s + lane];
+                const int32_t p = unit / per_page, s = (unit % per_page) * per;
+                left[j] = min(min(fill_cur[p], kPage) - s, per);
+                qv[j] = q_cur[(size_t)p * kPage + s + min(lane, per - 1)];
             }
         }
 #pragma unroll 1
@@ -964,6 +1036,7 @@ __device__ __forceinline__ void level_bottom_up_stream(const BfsArgs& a, int32_t
 // PP_PULL or PP_SWITCH (decided here, identically in every workgroup, from
 // the slot statistics).
 // lvl_arg >= 0 names the level; -1 takes it from the header (lv[parity]).
+template <bool RUN>
 __global__ __launch_bounds__(kBfsBlock) void k_bfs_level(BfsArgs a, int32_t lvl_arg, int32_t parity, int32_t policy,
                                                           float alpha, float beta) {
     extern __shared__ __align__(16) uint64_t s_bits[];  // staged with 16-byte stores
@@ -1032,8 +1105,10 @@ __global__ __launch_bounds__(kBfsBlock) void k_bfs_level(BfsArgs a, int32_t lvl_
     const int32_t sw = ((dir == PP_PUSH ? cur.m : mu) >= a.stage_min) ? a.stage_words : 0;
     if (dir == PP_PUSH) {
         if (sw) stage_bits(s_bits, a.visited, sw);
-        TdCtx cx{lvl, q_next, fill_next, a.fb[sn], &h->slot[sn], s_bits, sw, cur.m >= kProbeMin,
-                 (cur.m < (a.nnz >> kSmallLevelShift)) ? a.td_small_row : kBigRow};
+        TdCtx<RUN> cx{lvl, q_next, fill_next, a.fb[sn], &h->slot[sn], s_bits, sw, cur.m >= kProbeMin,
+                 (cur.m < (a.nnz >> kSmallLevelShift)) ? a.td_small_row : kBigRow, 0};
+        cx.min_item = (nf > a.words && cx.big_row == kBigRow && a.td_small_row < kBigRow) ? kMinItem : cx.big_row;
+        if (nf >= (int32_t)gridDim.x * kBfsWaves) page_reserve(a, pg, kBfsWaves, cx.nxt);
         // a frontier built top-down left the reserved pages unused
         level_top_down(a, cx, s_wave, a.queue[lvl & 1], a.fill[lvl & 1], (cur.dir_prev == PP_PULL) ? 0 : a.static_pages,
                        min(cur.pages, a.page_cap), a.fb[sc], nf > a.words, cnt, deg, pg);
@@ -1073,6 +1148,7 @@ __global__ __launch_bounds__(kBfsBlock) void k_bfs_level(BfsArgs a, int32_t lvl_
 // vertex is already claimed is skipped.
 // Two workgroups per compute unit: 32 wavefronts, 8 per SIMD, which caps the
 // kernel at 64 VGPRs (the second bound is the minimum wavefronts per SIMD).
+template <bool RUN>
 __global__ __launch_bounds__(kBfsBlock, 8) void k_bfs_chunks(BfsArgs a) {
     extern __shared__ __align__(16) uint64_t s_bits[];  // staged with 16-byte stores
     BfsHdr* h = a.hdr;
@@ -1108,9 +1184,16 @@ __global__ __launch_bounds__(kBfsBlock, 8) void k_bfs_chunks(BfsArgs a) {
         const int32_t clen = (m < (a.nnz >> kSmallLevelShift)) ? a.td_small_row : kBigRow;
         const int32_t sw = ((int64_t)items * clen >= 2 * (int64_t)gridDim.x * a.chunk_stage) ? a.chunk_stage : 0;
         if (sw) stage_bits(s_bits, a.visited, sw);
-        TdCtx cx{lvl, q_next, fill_next, a.fb[sn], &h->slot[sn], s_bits, sw, true, kBigRow};
+        TdCtx<RUN> cx{lvl, q_next, fill_next, a.fb[sn], &h->slot[sn], s_bits, sw, true, kBigRow, kBigRow};
+        if (RUN && sw == 0 && m >= kAggMin && m < (a.nnz >> kSmallLevelShift)) {
+            cx.s_new = reinterpret_cast<uint32_t*>(s_bits);
+            cx.agg = 2 * min(a.chunk_stage, kAggWords);
+        }
+        agg_begin(cx);
+        page_reserve(a, pg, min(kBfsWaves, items - (int32_t)blockIdx.x * kBfsWaves), cx.nxt);
         for (int32_t it = gwave; it < items; it += nwaves)
             td_row(a, cx, pg, a.items[3 * it], a.items[3 * it + 1], a.items[3 * it + 2], cnt, deg, lane);
+        agg_end(a, cx);
     } else {
         // Hits are collected per wavefront (vertex, slot) and claimed 64 at a
         // time, one lane each, so a claim's round trip is shared.
@@ -1737,8 +1820,9 @@ static pp_status check_state(pp_graph g, void* state, size_t bytes) {
 // Lets the staging kernels take LDS beyond the default 64 KiB.
 static void allow_stage_lds(const BfsArgs& a) {
     const int bytes = (a.stage_words + a.sum_words) * 8;
-    allow_dynamic_lds(reinterpret_cast<const void*>(&k_bfs_level), (size_t)bytes);
-    allow_dynamic_lds(reinterpret_cast<const void*>(&k_bfs_chunks), (size_t)bytes);
+    for (const void* f : {reinterpret_cast<const void*>(&k_bfs_level<false>), reinterpret_cast<const void*>(&k_bfs_level<true>),
+                          reinterpret_cast<const void*>(&k_bfs_chunks<false>), reinterpret_cast<const void*>(&k_bfs_chunks<true>)})
+        allow_dynamic_lds(f, (size_t)bytes);
 }
 
 // Dynamic LDS of the chunk kernel: the bottom-up summary or the top-down
@@ -1782,9 +1866,9 @@ static pp_status launch_level(pp_graph g, const BfsArgs& a, int32_t lvl, int32_t
                               float beta, hipStream_t st) {
     const int32_t blocks = bfs_blocks(g);
     const size_t lds = (size_t)(a.stage_words + a.sum_words) * 8;
-    hipLaunchKernelGGL(k_bfs_level, dim3(blocks), dim3(kBfsBlock), lds, st, a, lvl, parity, policy, alpha, beta);
+    hipLaunchKernelGGL(k_bfs_level<false>, dim3(blocks), dim3(kBfsBlock), lds, st, a, lvl, parity, policy, alpha, beta);
     if (needs_chunks(g, policy))
-        hipLaunchKernelGGL(k_bfs_chunks, dim3(chunk_blocks(g)), dim3(kBfsBlock), chunk_lds(a), st, a);
+        hipLaunchKernelGGL(k_bfs_chunks<false>, dim3(chunk_blocks(g)), dim3(kBfsBlock), chunk_lds(a), st, a);
     PP_LAUNCH_CHECK("k_bfs_level");
     return PP_OK;
 }
@@ -1857,10 +1941,10 @@ static pp_status bfs_graph(pp_graph g, BfsArgs a, int32_t policy, float alpha, f
         }
         int32_t parity = i & 1;
         void* largs[] = {&a, &lvl, &parity, &policy, &alpha, &beta};
-        e = add(reinterpret_cast<const void*>(&k_bfs_level), largs, blocks, lds);
+        e = add(reinterpret_cast<const void*>(&k_bfs_level<true>), largs, blocks, lds);
         if (e == hipSuccess && chunks) {
             void* cargs[] = {&a};
-            e = add(reinterpret_cast<const void*>(&k_bfs_chunks), cargs, chunk_blocks(g), (unsigned)chunk_lds(a));
+            e = add(reinterpret_cast<const void*>(&k_bfs_chunks<true>), cargs, chunk_blocks(g), (unsigned)chunk_lds(a));
         }
     }
     hipGraphExec_t exec = nullptr;

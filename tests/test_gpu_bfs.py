@@ -420,3 +420,36 @@ def test_low_degree_levels_on_cooperating_workgroups(maker, roots):
         g.close()
     for a, b in zip(*logs):
         np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("hubs,deg,leaves", [(49, 3000, 9000), (441, 300, 4000), (9000, 64, 3000), (9000, 65, 3000),
+                                             (2000, 257, 70000)])
+def test_pushing_levels_of_hubs(hubs, deg, leaves):
+    # a root, its hubs, and leaves that the hubs share: a compact queue of hub
+    # rows spread one to a wavefront, claims of shared targets, pages reserved per
+    # workgroup, rows about the lengths at which they become chunk items, and
+    # frontiers read from the queue and from the bitmap
+    rng = np.random.default_rng(hubs + deg)
+    src = np.concatenate([np.zeros(hubs, np.int64), 1 + np.repeat(np.arange(hubs), deg)])
+    picks = np.concatenate([rng.choice(leaves, deg, replace=False) for _ in range(hubs)])
+    h = gg.from_edges(1 + hubs + leaves, src, np.concatenate([1 + np.arange(hubs), 1 + hubs + picks]), True)
+    _check(h, [0, 1, h.n - 1], policies=[pp.PP_PUSH, pp.PP_SWITCH], fast=True)
+
+
+def test_pushing_levels_of_an_rmat_graph():
+    h = gg.rmat(17, 16, seed=9)
+    _check(h, gg.pick_vertices(h, 3, seed=4), policies=[pp.PP_PUSH], fast=True)
+
+
+def test_steps_into_another_array():
+    # a step writes what it finds whatever its arrays hold: only a whole run may
+    # take an entry's content for the vertex's state
+    h = _star_of_stars(60, 90)
+    want, _, nlev = oracle.bfs(h.off, h.idx, 0)
+    r = pp.BfsRun(pp.Graph(h))
+    r.init(0)
+    r.level = torch.full_like(r.level, 77)
+    for lvl in range(nlev):
+        r.step(lvl, pp.PP_PUSH)
+    got = r.level.cpu().numpy()
+    assert np.array_equal(got[want > 0], want[want > 0]) and got[0] == 77
