@@ -3,8 +3,8 @@
 // the per-level direction switch (Sec. 5 Generic-Switch, applied to BFS as in
 // the direction-optimising BFS the paper cites in Sec. 1).
 //
-// One kernel expands one level; a second kernel takes the chunks of very long
-// rows.  Both forms leave the new frontier as a queue AND a bitmap, so any
+// One kernel expands one level; a second one takes the chunks of very long rows
+// (in a run one kernel does whichever comes next, k_bfs_step).  Both forms leave the new frontier as a queue AND a bitmap, so any
 // sequence of directions works without conversions.  A bottom-up level with
 // a sparse frontier streams the whole in-edge array instead of scanning row
 // by row (see level_bottom_up_stream).
@@ -16,10 +16,12 @@
 //    The first `static_pages` pages (one per level-kernel wavefront) are
 //    reserved: in a bottom-up level, which appends a lot, every wavefront
 //    starts on its own reserved page and takes no atomic until it is full;
-//    a top-down level leaves them unused, and its readers skip them;
+//    a top-down level leaves them unused, and its readers skip them (where
+//    most wavefronts will append, a workgroup takes their pages together);
 //  - frontier statistics are summed per workgroup, one atomic each;
-//  - top-down claims use one atomic OR on a 64-vertex visited word, tried,
-//    on large levels, only after a plain read shows the vertex unvisited.
+//  - top-down claims of a run compare-and-swap the vertex's level entry, those
+//    of a single step OR its bit into the visited word; on large levels only
+//    after a plain read shows the vertex unvisited.
 // Per-level statistics (|F|, out-edges of F, out-edges of unvisited
 // vertices) live in three rotating slots so the direction is chosen on the
 // device and the host only polls for termination.
@@ -112,7 +114,8 @@ struct BfsHdr {
     int32_t lv[2];
     int32_t c_lvl;
     int32_t finished;  // an empty frontier was reached
-    int32_t busy;      // level-kernel launches that found a non-empty frontier
+    int32_t busy;      // level-kernel launches that found a non-empty frontier (or chunk items)
+    int32_t pend[2];   // as lv: the level whose chunk items the next step kernel takes first (-1: none)
     int32_t pad;
     int64_t reached;
     int64_t edges;
@@ -480,6 +483,8 @@ __global__ void k_bfs_init(BfsArgs a, int32_t root_user, int64_t nnz) {
         h->lv[0] = 0;
         h->lv[1] = 0;
         h->c_lvl = -1;
+        h->pend[0] = -1;
+        h->pend[1] = -1;
         h->finished = 0;
         h->busy = 0;
         h->root = root;
@@ -809,6 +814,7 @@ __device__ __forceinline__ void level_top_down(const BfsArgs& a, const TdCtx<RUN
 // ------------------------------------------------------------------ bottom-up
 constexpr int kBuB = 4;  // in-edges one lane loads per step of a short row
 constexpr int kBuU = 4;  // rounds of 64 in-edges a wave loads per step of a long row
+constexpr int kBuPre = 8;  // leading in-edges of a long row that one lane tests first (4 and 8 level, 16 4% slower)
 constexpr int32_t kCoopRow = 128;  // in-rows at least this long are scanned by the whole wave
 
 // Position of the first frontier member among csc_idx[b, e) (-1 if none),
@@ -861,11 +867,29 @@ __device__ __forceinline__ void level_bottom_up(const BfsArgs& a, int32_t lvl, c
         const int32_t rest_b = rb + kBigInRow, rest_e = re;
         if (huge) re = rest_b;
         const bool coop = (re - rb) >= kCoopRow;
-        uint64_t big = __ballot(coop);
+        // the first entries of all the word's long rows at once: most rows end
+        // there when the frontier holds many edges, and the 64 hub rows of one
+        // word, one after another, were the longest chain of such a level
+        // (R-MAT 20, a frontier of 12 million edges: 70 -> 26 us)
+        if (__ballot(coop)) {
+            int32_t u[kBuPre];
+#pragma unroll
+            for (int r = 0; r < kBuPre; ++r) u[r] = coop ? a.csc_idx[rb + r] : -1;
+            bool hit[kBuPre];
+#pragma unroll
+            for (int r = 0; r < kBuPre; ++r) hit[r] = (u[r] >= 0) && fb_test(fv, u[r]);
+#pragma unroll
+            for (int r = 0; r < kBuPre; ++r)
+                if (hit[r] && !found) {
+                    found = true;
+                    par = u[r];
+                }
+        }
+        uint64_t big = __ballot(coop && !found);
         while (big) {
             const int src = __ffsll((long long)big) - 1;
             big &= big - 1;
-            const int32_t bb = __shfl(rb, src), be = __shfl(re, src);
+            const int32_t bb = __shfl(rb, src) + kBuPre, be = __shfl(re, src);
             int32_t p = -1;
             bu_scan_row(a, fv, bb, be, lane, p);
             if (lane == src && p >= 0) {
@@ -1032,19 +1056,16 @@ __device__ __forceinline__ void level_bottom_up_stream(const BfsArgs& a, int32_t
     if (nh) resolve();
 }
 
-// Expands frontier `lvl` (slot lvl % 3) into lvl+1.  policy: PP_PUSH,
-// PP_PULL or PP_SWITCH (decided here, identically in every workgroup, from
-// the slot statistics).
-// lvl_arg >= 0 names the level; -1 takes it from the header (lv[parity]).
-template <bool RUN>
-__global__ __launch_bounds__(kBfsBlock) void k_bfs_level(BfsArgs a, int32_t lvl_arg, int32_t parity, int32_t policy,
-                                                          float alpha, float beta) {
+// Expands frontier `lvl` (slot lvl % 3; v0 to v2 are the three slots) into
+// lvl+1.  policy: PP_PUSH, PP_PULL or PP_SWITCH (decided here, identically in
+// every workgroup, from the slot statistics).  STEPS: a step kernel's launch,
+// which leaves the level's chunk items to the next one.
+template <bool RUN, bool STEPS>
+__device__ __forceinline__ void level_pass(const BfsArgs& a, const SlotView& v0, const SlotView& v1,
+                                           const SlotView& v2, int32_t lvl, int32_t parity, int32_t policy,
+                                           float alpha, float beta, WaveLds& s_wave) {
     extern __shared__ __align__(16) uint64_t s_bits[];  // staged with 16-byte stores
-    __shared__ WaveLds s_wave;
     BfsHdr* h = a.hdr;
-    // the three slots are read in the same round trip as the level index
-    const SlotView v0 = view(h->slot[0]), v1 = view(h->slot[1]), v2 = view(h->slot[2]);
-    const int32_t lvl = lvl_arg >= 0 ? lvl_arg : h->lv[parity];
     const int sc = lvl % 3, sn = (lvl + 1) % 3, sz = (lvl + 2) % 3;
     const SlotView cur = (sc == 0) ? v0 : ((sc == 1) ? v1 : v2);
     const int32_t nf = cur.n;
@@ -1053,6 +1074,7 @@ __global__ __launch_bounds__(kBfsBlock) void k_bfs_level(BfsArgs a, int32_t lvl_
         if (lead) {
             h->lv[parity ^ 1] = lvl;  // stays at the empty level
             h->c_lvl = -1;
+            h->pend[parity ^ 1] = -1;
             h->finished = 1;
         }
         return;
@@ -1083,6 +1105,7 @@ __global__ __launch_bounds__(kBfsBlock) void k_bfs_level(BfsArgs a, int32_t lvl_
         h->edges += cur.m;
         h->lv[parity ^ 1] = lvl + 1;
         h->c_lvl = lvl;
+        h->pend[parity ^ 1] = STEPS ? lvl : -1;
         h->busy += 1;
     }
     // the bitmap two levels ahead (frontier lvl - 1) is rewritten next level:
@@ -1146,24 +1169,12 @@ __global__ __launch_bounds__(kBfsBlock) void k_bfs_level(BfsArgs a, int32_t lvl_
 // vertex with an atomic OR on its visited bit (so the parent is a frontier
 // in-neighbour, not necessarily the first in stored order); a chunk whose
 // vertex is already claimed is skipped.
-// Two workgroups per compute unit: 32 wavefronts, 8 per SIMD, which caps the
-// kernel at 64 VGPRs (the second bound is the minimum wavefronts per SIMD).
 template <bool RUN>
-__global__ __launch_bounds__(kBfsBlock, 8) void k_bfs_chunks(BfsArgs a) {
+__device__ __forceinline__ void chunk_pass(const BfsArgs& a, int32_t lvl, const int32_t (&bigs)[3],
+                                           const int32_t (&dirs)[3], const int32_t (&ns)[3], const int64_t (&ms)[3],
+                                           WaveLds& s_wave) {
     extern __shared__ __align__(16) uint64_t s_bits[];  // staged with 16-byte stores
     BfsHdr* h = a.hdr;
-    // slot fields read in the same round trip as the level index
-    int32_t bigs[3], dirs[3], ns[3];
-    int64_t ms[3];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        bigs[i] = h->slot[i].big;
-        dirs[i] = h->slot[i].dir_prev;
-        ns[i] = h->slot[i].n;
-        ms[i] = h->slot[i].m;
-    }
-    const int32_t lvl = h->c_lvl;
-    if (lvl < 0) return;
     const int sc = lvl % 3, sn = (lvl + 1) % 3;
     const int32_t items = min((sn == 0) ? bigs[0] : ((sn == 1) ? bigs[1] : bigs[2]), a.item_cap);
     if (items == 0) return;
@@ -1197,8 +1208,8 @@ __global__ __launch_bounds__(kBfsBlock, 8) void k_bfs_chunks(BfsArgs a) {
     } else {
         // Hits are collected per wavefront (vertex, slot) and claimed 64 at a
         // time, one lane each, so a claim's round trip is shared.
-        __shared__ int32_t s_hv[kBfsWaves][kWave];
-        __shared__ int32_t s_hp[kBfsWaves][kWave];
+        auto& s_hv = s_wave.a;
+        auto& s_hp = s_wave.b;
         const int w = threadIdx.x / kWave;
         int32_t nh = 0;  // wave-uniform
         auto claim_hits = [&]() {
@@ -1253,6 +1264,72 @@ __global__ __launch_bounds__(kBfsBlock, 8) void k_bfs_chunks(BfsArgs a) {
     }
     page_close(pg, fill_next, lane);
     flush_stats(cnt, deg, &h->slot[sn]);
+}
+
+// The slot fields a chunk pass reads.
+__device__ __forceinline__ void chunk_view(const BfsHdr* h, int32_t (&bigs)[3], int32_t (&dirs)[3], int32_t (&ns)[3],
+                                           int64_t (&ms)[3]) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        bigs[i] = h->slot[i].big;
+        dirs[i] = h->slot[i].dir_prev;
+        ns[i] = h->slot[i].n;
+        ms[i] = h->slot[i].m;
+    }
+}
+
+// One level.  lvl_arg >= 0 names it; -1 takes it from the header (lv[parity]).
+template <bool RUN>
+__global__ __launch_bounds__(kBfsBlock) void k_bfs_level(BfsArgs a, int32_t lvl_arg, int32_t parity, int32_t policy,
+                                                          float alpha, float beta) {
+    __shared__ WaveLds s_wave;
+    const BfsHdr* h = a.hdr;
+    // the three slots are read in the same round trip as the level index
+    const SlotView v0 = view(h->slot[0]), v1 = view(h->slot[1]), v2 = view(h->slot[2]);
+    const int32_t lvl = lvl_arg >= 0 ? lvl_arg : h->lv[parity];
+    level_pass<RUN, false>(a, v0, v1, v2, lvl, parity, policy, alpha, beta, s_wave);
+}
+
+// The chunk items of the level that the kernel before expanded.
+// Two workgroups per compute unit: 32 wavefronts, 8 per SIMD, which caps the
+// kernel at 64 VGPRs (the second bound is the minimum wavefronts per SIMD).
+template <bool RUN>
+__global__ __launch_bounds__(kBfsBlock, 8) void k_bfs_chunks(BfsArgs a) {
+    __shared__ WaveLds s_wave;
+    // slot fields read in the same round trip as the level index
+    int32_t bigs[3], dirs[3], ns[3];
+    int64_t ms[3];
+    chunk_view(a.hdr, bigs, dirs, ns, ms);
+    const int32_t lvl = a.hdr->c_lvl;
+    if (lvl < 0) return;
+    chunk_pass<RUN>(a, lvl, bigs, dirs, ns, ms, s_wave);
+}
+
+// A run's launch on graphs with chunk items: those that the level before left,
+// where there are any, else the next level.  Most levels leave none, and a
+// chunk kernel that finds none still takes 4.5 us between its neighbours: eight
+// of them were a seventh of a switching run at R-MAT 20.
+__global__ __launch_bounds__(kBfsBlock) void k_bfs_step(BfsArgs a, int32_t parity, int32_t policy, float alpha,
+                                                         float beta) {
+    __shared__ WaveLds s_wave;
+    BfsHdr* h = a.hdr;
+    const SlotView v0 = view(h->slot[0]), v1 = view(h->slot[1]), v2 = view(h->slot[2]);
+    const int32_t lvl = h->lv[parity], left = h->pend[parity];
+    const int32_t big[3] = {h->slot[0].big, h->slot[1].big, h->slot[2].big};
+    const int sn = (left + 1) % 3;
+    if (left >= 0 && ((sn == 0) ? big[0] : ((sn == 1) ? big[1] : big[2])) > 0) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            h->lv[parity ^ 1] = lvl;
+            h->pend[parity ^ 1] = -1;
+            h->busy += 1;
+        }
+        int32_t bigs[3], dirs[3], ns[3];
+        int64_t ms[3];
+        chunk_view(h, bigs, dirs, ns, ms);
+        chunk_pass<true>(a, left, bigs, dirs, ns, ms, s_wave);
+        return;
+    }
+    level_pass<true, true>(a, v0, v1, v2, lvl, parity, policy, alpha, beta, s_wave);
 }
 
 // ------------------------------------------------------------ deep graphs
@@ -1341,7 +1418,8 @@ __global__ __launch_bounds__(kBfsBlock) void k_bfs_multi(BfsArgs a, int32_t poli
     if (threadIdx.x == 0) {
         const int32_t lvl = h->lv[0];
         const SlotView cur = view(h->slot[lvl % 3]);
-        const bool ok = !h->finished && cur.n > 0 && cur.n <= qcap && cur.m <= ecap && cur.dir_prev == PP_PUSH &&
+        const int32_t left = h->pend[0];  // chunk items come first
+        const bool ok = !h->finished && !(left >= 0 && h->slot[(left + 1) % 3].big > 0) && cur.n > 0 && cur.n <= qcap && cur.m <= ecap && cur.dir_prev == PP_PUSH &&
                         cur.n_prev <= a.words && cur.pages - a.static_pages <= kMultiPages &&
                         multi_push(policy, alpha, beta, a.n, lvl, cur.n, cur.m, cur.mu_base, cur.dir_prev, cur.n_prev);
         s_hdr[0] = ok;
@@ -1520,6 +1598,8 @@ __global__ __launch_bounds__(kBfsBlock) void k_bfs_multi(BfsArgs a, int32_t poli
         h->lv[0] = lvl;
         h->lv[1] = lvl;
         h->c_lvl = -1;
+        h->pend[0] = -1;
+        h->pend[1] = -1;
         h->levels = lvl;
         h->last = lvl;
         h->reached += reached;
@@ -1793,6 +1873,8 @@ __global__ __launch_bounds__(kDeepBlock) void k_bfs_deep(BfsArgs a, int32_t poli
         h->lv[0] = lvl;
         h->lv[1] = lvl;
         h->c_lvl = -1;
+        h->pend[0] = -1;
+        h->pend[1] = -1;
         h->levels = lvl;
         h->last = lvl;
         h->reached += reached;
@@ -1821,7 +1903,8 @@ static pp_status check_state(pp_graph g, void* state, size_t bytes) {
 static void allow_stage_lds(const BfsArgs& a) {
     const int bytes = (a.stage_words + a.sum_words) * 8;
     for (const void* f : {reinterpret_cast<const void*>(&k_bfs_level<false>), reinterpret_cast<const void*>(&k_bfs_level<true>),
-                          reinterpret_cast<const void*>(&k_bfs_chunks<false>), reinterpret_cast<const void*>(&k_bfs_chunks<true>)})
+                          reinterpret_cast<const void*>(&k_bfs_chunks<false>), reinterpret_cast<const void*>(&k_bfs_chunks<true>),
+                          reinterpret_cast<const void*>(&k_bfs_step)})
         allow_dynamic_lds(f, (size_t)bytes);
 }
 
@@ -1859,6 +1942,18 @@ static bool needs_chunks(pp_graph g, int32_t policy) {
     return (policy != PP_PULL && g->max_out_deg > kBigRow) || (policy != PP_PUSH && g->max_in_deg > kBigInRow);
 }
 
+// Do a run's launches take chunk items and levels in one kernel?  (Not where
+// the cooperating workgroups run: they take over between levels.)
+static bool steps_for(pp_graph g, int32_t policy) { return needs_chunks(g, policy) && !deep_for(g, policy); }
+
+static pp_status launch_step(pp_graph g, const BfsArgs& a, int32_t parity, int32_t policy, float alpha, float beta,
+                             hipStream_t st) {
+    hipLaunchKernelGGL(k_bfs_step, dim3(bfs_blocks(g)), dim3(kBfsBlock), (size_t)(a.stage_words + a.sum_words) * 8, st, a,
+                       parity, policy, alpha, beta);
+    PP_LAUNCH_CHECK("k_bfs_step");
+    return PP_OK;
+}
+
 // One level: the expansion kernel, then (when long rows can occur) the chunk
 // kernel.  lvl >= 0 names the level; lvl = -1 takes it from the header, the
 // level kernel reading lv[parity].
@@ -1892,7 +1987,7 @@ static pp_status bfs_graph(pp_graph g, BfsArgs a, int32_t policy, float alpha, f
     }
     const int32_t blocks = bfs_blocks(g);
     const unsigned lds = (unsigned)(a.stage_words + a.sum_words) * 8;
-    const bool chunks = needs_chunks(g, policy);
+    const bool chunks = needs_chunks(g, policy), steps = steps_for(g, policy);
     hipGraph_t graph = nullptr;
     PP_HIP(hipGraphCreate(&graph, 0));
     hipGraphNode_t prev = nullptr;
@@ -1940,6 +2035,11 @@ static pp_status bfs_graph(pp_graph g, BfsArgs a, int32_t policy, float alpha, f
             if (e != hipSuccess) break;
         }
         int32_t parity = i & 1;
+        if (steps) {
+            void* sargs[] = {&a, &parity, &policy, &alpha, &beta};
+            e = add(reinterpret_cast<const void*>(&k_bfs_step), sargs, blocks, lds);
+            continue;
+        }
         void* largs[] = {&a, &lvl, &parity, &policy, &alpha, &beta};
         e = add(reinterpret_cast<const void*>(&k_bfs_level<true>), largs, blocks, lds);
         if (e == hipSuccess && chunks) {
@@ -2043,7 +2143,11 @@ static void bfs_record(pp_graph g, int32_t policy, int32_t busy) {
 }
 // The run is over when the newest frontier is empty (or a level kernel found
 // it so).
-static bool bfs_done(const BfsHdr& h) { return h.finished || h.slot[h.last % 3].n == 0; }
+static bool bfs_done(const BfsHdr& h) {
+    // (an even number of launches: the next one has parity 0)
+    if (h.pend[0] >= 0 && h.slot[(h.pend[0] + 1) % 3].big > 0) return false;
+    return h.finished || h.slot[h.last % 3].n == 0;
+}
 static void bfs_fill_stats(const BfsHdr& h, pp_bfs_stats* stats) {
     stats->levels = h.levels;
     stats->reached = (int32_t)h.reached;
@@ -2081,8 +2185,11 @@ PP_EXPORT pp_status pp_bfs_run_log(pp_graph g, int32_t root, pp_dir policy, floa
     const int32_t predicted = bfs_predicted(g, policy);
     int32_t batch = predicted > 0 ? bfs_even(predicted) : 4;
     int32_t extra = 2;
-    int32_t launched = 0;
-    const int32_t max_levels = g->d.n + 1;  // at most n non-empty frontiers, then an empty one
+    int64_t launched = 0;
+    const bool steps = steps_for(g, policy);
+    // at most n non-empty frontiers, then an empty one; chunk items may take a
+    // step kernel's launch as well
+    const int64_t max_levels = ((int64_t)g->d.n + 1) * (steps ? 2 : 1);
     BfsHdr h;
     for (;;) {
         if (launched + batch <= max_levels) {  // a whole batch: replay its graph (launched stays even)
@@ -2093,7 +2200,8 @@ PP_EXPORT pp_status pp_bfs_run_log(pp_graph g, int32_t root, pp_dir policy, floa
             launched += batch;
         } else {
             for (; launched < max_levels; ++launched) {
-                s = launch_level(g, a, -1, launched & 1, policy, alpha, beta, st);
+                s = steps ? launch_step(g, a, (int32_t)(launched & 1), policy, alpha, beta, st)
+                          : launch_level(g, a, -1, (int32_t)(launched & 1), policy, alpha, beta, st);
                 if (s != PP_OK) return s;
             }
         }
@@ -2101,7 +2209,7 @@ PP_EXPORT pp_status pp_bfs_run_log(pp_graph g, int32_t root, pp_dir policy, floa
         if (s != PP_OK) return s;
         if (bfs_done(h) || launched >= max_levels) break;
         if (launched < predicted) {
-            batch = bfs_even(predicted - launched);
+            batch = bfs_even((int32_t)(predicted - launched));
         } else {
             batch = bfs_even(extra);
             extra = std::min(extra * 2, kBfsMaxBatch);

@@ -453,3 +453,24 @@ def test_steps_into_another_array():
         r.step(lvl, pp.PP_PUSH)
     got = r.level.cpu().numpy()
     assert np.array_equal(got[want > 0], want[want > 0]) and got[0] == 77
+
+
+@pytest.mark.parametrize("first", [0, 1, 7, 8, 9, 127, 128, 200, 299])
+def test_bottom_up_long_rows_hit_at_any_entry(first):
+    # in-rows of 300 entries of which only entry `first` is in the frontier: the
+    # entries one lane tests, the rest of the leading 128, and the chunk items
+    n_top, n_rows, d = 3000, 100, 300
+    src, dst = [], []
+    for k in range(n_rows):
+        row = 10 + n_top + k
+        others = 10 + (k * 31 + np.arange(d - 1)) % n_top + 0
+        others = np.sort(others)
+        hub = others[first - 1] if first else 1
+        src += [others, [0]]
+        dst += [np.full(d - 1, row), [hub if first else 1]]
+        if not first:
+            src.append([1])
+            dst.append([row])
+    h = gg.from_edges(10 + n_top + n_rows, np.concatenate(src), np.concatenate(dst), False)
+    h.ensure_transpose()
+    _check(h, [0], policies=[pp.PP_PULL, pp.PP_SWITCH], fast=True)
