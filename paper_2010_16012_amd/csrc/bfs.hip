@@ -139,8 +139,14 @@ struct BfsLayout {
 };
 
 // One workgroup per compute unit (the staged bitmap takes most of its LDS),
-// fewer on small graphs.
-static int32_t bfs_blocks(pp_graph g) { return std::max(1, std::min(ceil_div(g->d.n, 4096), g->num_cu)); }
+// fewer on small graphs: one to 4,096 vertices or 8,192 edges.  (By vertices
+// alone R-MAT 16 ran on 16 of 256 compute units: push 317 -> 187 us a root, pull
+// 109 -> 87, switch 88 -> 77; R-MAT 12 246 -> 150, 85 -> 71, 78 -> 65.  One to
+// 4,096 edges is level, one to 32,768 up to 60% slower.)
+static int32_t bfs_blocks(pp_graph g) {
+    const int64_t want = std::max<int64_t>(ceil_div(g->d.n, 4096), g->d.nnz / 8192);
+    return (int32_t)std::max<int64_t>(1, std::min<int64_t>(want, g->num_cu));
+}
 
 static BfsLayout bfs_layout(pp_graph g) {
     const int32_t n = g->d.n;
@@ -1915,7 +1921,7 @@ static size_t chunk_lds(const BfsArgs& a) { return (size_t)std::max(a.sum_words,
 // Workgroups of the chunk kernel: one per compute unit.  Two per unit, each
 // staging half as many visited words, ran top-down runs about 1.4% slower at
 // R-MAT scale 22; half a workgroup per unit about 18% slower.
-static int32_t chunk_blocks(pp_graph g) { return std::max(1, std::min(ceil_div(g->d.n, 4096), g->num_cu)); }
+static int32_t chunk_blocks(pp_graph g) { return bfs_blocks(g); }
 
 // Frontier sets of the one-workgroup launch: vertices per set (qcap) and
 // out-edges per level (ecap) it takes on; 0 when it is off for this policy.
