@@ -183,12 +183,12 @@ __device__ __forceinline__ float4 f4_scale(float4 x, float s) { return make_floa
 // weight) loads of the next round, summed pairwise before they join the running sum (fixed order, and a hub row of
 // thousands of slots keeps its FP32 rounding error near log2(U) + slots/U
 // steps).  Loads past the row's end are exec-masked, not clamped: a clamped
-// gather would still move KT floats.
-template <int KT, int U, bool W, typename T>
-__device__ __forceinline__ Sum4<T> kt_gather4(const KArgs& a, int32_t b, int32_t e, int32_t g, int32_t stride,
+// gather would still move KT floats.  A: precision of the running sum.
+template <int KT, int U, bool W, typename T, typename A = T>
+__device__ __forceinline__ Sum4<A> kt_gather4(const KArgs& a, int32_t b, int32_t e, int32_t g, int32_t stride,
                                               int q) {
     const float4* __restrict__ src4 = reinterpret_cast<const float4*>(a.src);
-    Sum4<T> acc{0, 0, 0, 0};
+    Sum4<A> acc{0, 0, 0, 0};
     const int32_t step = U * stride;
     int32_t j0 = b + g;
     if (j0 >= e) return acc;
@@ -234,7 +234,7 @@ __device__ __forceinline__ Sum4<T> kt_gather4(const KArgs& a, int32_t b, int32_t
 #pragma unroll
             for (int k = 0; k + w < U; k += 2 * w) y[k] = s4_add(y[k], y[k + w]);
         }
-        acc = s4_add(acc, y[0]);
+        acc = s4_add(acc, Sum4<A>{y[0].x, y[0].y, y[0].z, y[0].w});
     }
     return acc;
 }
@@ -265,8 +265,10 @@ __device__ __forceinline__ Sum4<T> kt_block_sum4(Sum4<T> v, Sum4<T>* red) {
     return t;
 }
 
-// kt_epilogue for columns 4q..4q+3 of row u.
-template <int KT>
+// kt_epilogue for columns 4q..4q+3 of row u.  (f val) / s is rounded as the
+// scalar form does in the pushing form; f / s first would make one rounding of
+// it the same in every sweep.
+template <int KT, typename T>
 __device__ __forceinline__ float2 kt_epilogue4(const KArgs& a, int32_t u, int q, float4 acc) {
     const float in[4] = {acc.x, acc.y, acc.z, acc.w};
     float val[4];
@@ -275,9 +277,11 @@ __device__ __forceinline__ float2 kt_epilogue4(const KArgs& a, int32_t u, int q,
 #pragma unroll
         for (int c = 0; c < 4; ++c) val[c] = in[c] + ((a.src_int[c0 + c] == u) ? 1.0f - a.f : 0.f);
         if (a.out_scaled) {
-            const float sc = a.f * a.inv_s[u];
-            reinterpret_cast<float4*>(a.out_scaled)[(size_t)u * kq_lanes<KT>() + q] =
-                make_float4(sc * val[0], sc * val[1], sc * val[2], sc * val[3]);
+            const float is = a.inv_s[u], sc = a.f * is;
+            float c[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) c[k] = sizeof(T) == 8 ? a.f * val[k] * is : sc * val[k];
+            reinterpret_cast<float4*>(a.out_scaled)[(size_t)u * kq_lanes<KT>() + q] = make_float4(c[0], c[1], c[2], c[3]);
         }
     } else if (a.kind == kEpiAdjoint) {
         const int32_t uc = user_id(a.perm, u);
@@ -379,22 +383,24 @@ __global__ __launch_bounds__(kBlock) void k_kcol_sweep(KArgs a) {
             const int32_t u = a.list[a.kp.list_off[bin] + i];
             const Sum4<T> acc = (bin == 0) ? kt_gather4<KT, 4, W, T>(a, a.off[u], a.off[u + 1], 0, 1, q)
                                            : kt_gather4<KT, 8, W, T>(a, a.off[u], a.off[u + 1], 0, 1, q);
-            res = kt_epilogue4<KT>(a, u, q, s4_float(acc));
+            res = kt_epilogue4<KT, T>(a, u, q, s4_float(acc));
         }
     } else if (bin == 3) {
         const int32_t i = lu * (kBlock / kWave) + threadIdx.x / kWave;
         if (i < a.kp.list_off[4] - a.kp.list_off[3]) {
             const int32_t u = a.list[a.kp.list_off[3] + i];
             constexpr int GW = kWave / Q;
-            Sum4<T> acc = kt_gather4<KT, 8, W, T>(a, a.off[u], a.off[u + 1], grp % GW, GW, q);
-            acc = kt_wave_sum4<KT, T>(acc);
-            if (grp % GW == 0) res = kt_epilogue4<KT>(a, u, q, s4_float(acc));
+            // up to 128 rounds a group, a workgroup's groups had a quarter of
+            // them: the running sums are FP64 in either form
+            Sum4<double> acc = kt_gather4<KT, 8, W, T, double>(a, a.off[u], a.off[u + 1], grp % GW, GW, q);
+            acc = kt_wave_sum4<KT, double>(acc);
+            if (grp % GW == 0) res = kt_epilogue4<KT, T>(a, u, q, s4_float(acc));
         }
     } else if (bin == 4) {
         const int32_t u = a.list[a.kp.list_off[bin] + lu];
         Sum4<T> acc = kt_gather4<KT, 8, W, T>(a, a.off[u], a.off[u + 1], grp, G, q);
         acc = kt_block_sum4<KT, T>(acc, red4);
-        if (threadIdx.x < Q) res = kt_epilogue4<KT>(a, u, q, s4_float(acc));
+        if (threadIdx.x < Q) res = kt_epilogue4<KT, T>(a, u, q, s4_float(acc));
     } else {
         const int32_t b = a.tab[a.tab_cap + lu], e = a.tab[2 * a.tab_cap + lu];
         Sum4<T> acc = kt_gather4<KT, 8, W, T>(a, b, e, grp, G, q);
