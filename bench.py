@@ -239,7 +239,7 @@ def cpu_leg(args, host, roots, root_edges, runs, policy, alpha, beta, parts):
         achieved = tot_bytes / (tot_ms * 1e-3) / 1e9
         out[name] = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None,
-                     "kernel": f"k_bfs_level+k_bfs_chunks, {name} runs",
+                     "kernel": f"k_bfs_step, {name} runs",
                      "algorithmic_bytes_per_run": round(tot_bytes / 2), "run_ms": round(tot_ms / 2, 4),
                      "roots": 2, "bytes_from": "oracle replay of the GPU direction schedule"}
     return cpu, out
@@ -441,7 +441,7 @@ def main():
         achieved = tot / (part_ms["bfs_push"] * 1e-3) / 1e9
         roofline_bfs["push"] = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None,
-                                "kernel": "k_bfs_level+k_bfs_chunks, top-down runs",
+                                "kernel": "k_bfs_step, top-down runs",
                                 "algorithmic_bytes_per_run": round(tot / len(roots)),
                                 "run_ms": round(part_ms["bfs_push"] / len(roots), 4), "roots": len(roots)}
 
