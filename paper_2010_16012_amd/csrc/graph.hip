@@ -95,38 +95,48 @@ __global__ __launch_bounds__(kTile) void k_part_count(int32_t n, int nkeys, cons
     if (threadIdx.x < nkeys) tile_counts[blockIdx.x * nkeys + threadIdx.x] = cnt[threadIdx.x];
 }
 
-// ... an exclusive scan of the tile counts, key-major (one workgroup) ...
+// ... an exclusive scan of the tile counts, key-major (one workgroup: a lane a
+// key, half a wavefront a share of the tiles, so that rows of counts are read
+// whole; all threads on one key after another, with twenty barriers each, took
+// 25 us on the smallest graph and 430 at n = 2^22, this 3 and 99, three times a
+// registration) ...
 __global__ __launch_bounds__(1024) void k_part_scan(int32_t tiles, int nkeys, int32_t* __restrict__ tile_counts,
                                                     int32_t* __restrict__ totals) {
-    __shared__ int32_t part[1024];
-    __shared__ int32_t carry;
-    if (threadIdx.x == 0) carry = 0;
+    constexpr int kShares = 1024 / kMaxKeys, U = 8;
+    __shared__ int32_t s_sum[kShares][kMaxKeys], s_total[kMaxKeys];
+    const int key = threadIdx.x % kMaxKeys, share = threadIdx.x / kMaxKeys;
+    const int32_t per = (tiles + kShares - 1) / kShares;
+    const int32_t t0 = min(tiles, share * per), t1 = min(tiles, t0 + per);
+    const bool on = key < nkeys;
+    int32_t sum = 0;
+    for (int32_t t = t0; on && t < t1; t += U) {
+        int32_t c[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) c[k] = tile_counts[(size_t)min(t + k, t1 - 1) * nkeys + key];
+#pragma unroll
+        for (int k = 0; k < U; ++k) sum += t + k < t1 ? c[k] : 0;
+    }
+    s_sum[share][key] = sum;
     __syncthreads();
-    const int per = (tiles + 1023) / 1024;
-    for (int b = 0; b < nkeys; ++b) {
-        const int t0 = threadIdx.x * per;
-        int32_t s = 0;
-        for (int t = t0; t < t0 + per && t < tiles; ++t) s += tile_counts[t * nkeys + b];
-        part[threadIdx.x] = s;
-        __syncthreads();
-        for (int d = 1; d < 1024; d <<= 1) {
-            int32_t add = (threadIdx.x >= d) ? part[threadIdx.x - d] : 0;
-            __syncthreads();
-            part[threadIdx.x] += add;
-            __syncthreads();
+    if (share == 0) {
+        int32_t run = 0;
+        for (int i = 0; i < kShares; ++i) run += s_sum[i][key];
+        s_total[key] = run;
+        if (on) totals[key] = run;
+    }
+    __syncthreads();
+    int32_t at = 0;
+    for (int i = 0; i < key; ++i) at += s_total[i];
+    for (int i = 0; i < share; ++i) at += s_sum[i][key];
+    for (int32_t t = t0; on && t < t1; t += U) {
+        int32_t c[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) c[k] = tile_counts[(size_t)min(t + k, t1 - 1) * nkeys + key];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            if (t + k < t1) tile_counts[(size_t)(t + k) * nkeys + key] = at;
+            at += c[k];
         }
-        int32_t run = carry + part[threadIdx.x] - s;
-        for (int t = t0; t < t0 + per && t < tiles; ++t) {
-            const int32_t c = tile_counts[t * nkeys + b];
-            tile_counts[t * nkeys + b] = run;
-            run += c;
-        }
-        __syncthreads();
-        if (threadIdx.x == 1023) {
-            totals[b] = part[1023];
-            carry += part[1023];
-        }
-        __syncthreads();
     }
 }
 

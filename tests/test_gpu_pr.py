@@ -543,3 +543,12 @@ def test_small_graph_in_one_launch(n, rows, deg, weighted):
                 if want_x is not None:
                     assert np.abs(pr_gpu(g, d, iters).astype(np.float64) - want_x).sum() <= PR_L1_TOL, (iters, rl, d)
             g.close()
+
+
+@pytest.mark.parametrize("n", [1, 1023, 1025, 32 * 1024, 33 * 1024 + 7, 257 * 1024 + 1])
+def test_renumbering_over_few_and_many_tiles(n):
+    # vertices are sorted by degree through counts per tile of 1,024 vertices:
+    # one tile, fewer and more than the shares they are scanned in, partial last ones
+    h = H.random_graph(n, 3 * n, n % 97, symmetric=True) if n > 1 else gg.from_edges(1, [], [], True)
+    got = pp.pagerank(pp.Graph(h), iters=3, f=F).cpu().numpy().astype(np.float64)
+    assert np.abs(got - oracle.pagerank(h.off, h.idx, F, 3)).sum() <= PR_L1_TOL
