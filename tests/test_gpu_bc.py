@@ -126,3 +126,13 @@ def test_sources_that_share_their_levels(count):
         pp.pp_bc_run(g.handle, pp.PP_PULL, pp.PP_PULL, src, bc,
                      torch.empty(1024 + slab, dtype=torch.uint8, device="cuda"), None)
         np.testing.assert_allclose(bc.cpu().numpy(), want, rtol=RTOL, atol=1e-9 * max(1.0, np.abs(want).max()))
+
+
+@pytest.mark.parametrize("leaves", [63, 64, 65, 127, 128, 129, 5000])
+def test_pushed_levels_of_one_vertex(leaves):
+    # a wavefront's appends collect 128 vertices before they go to the order: a
+    # hub's row that ends short of that, at it and past it, with a second level
+    # that all of them share, hot ids and others
+    h = gg.from_edges(2 + leaves, np.concatenate([np.zeros(leaves, np.int64), np.ones(leaves, np.int64)]),
+                      np.concatenate([2 + np.arange(leaves)] * 2), True)
+    _check(h, [0, 1, 2, leaves + 1], [(pp.PP_PUSH, pp.PP_PUSH), (pp.PP_PUSH, pp.PP_PULL)])
