@@ -400,9 +400,10 @@ size_t pp_multi_workspace_bytes(int32_t num_graphs, int64_t total_vertices);
  * LDS: pull gathers and push updates are LDS operations and the barrier
  * between sweeps is a workgroup barrier.  Where a graph has more than 49,152
  * edges (and ws holds pp_multi_workspace_bytes), each PageRank step is a launch
- * that shares the in-rows of all graphs among the compute units, in either
- * direction (in_off/in_idx must be the transpose for PP_PUSH as well; x is
- * used between the steps).  Pull sums every row in FP64 (per
+ * that shares the in-rows of all graphs among the compute units (x is used
+ * between the steps); PP_PUSH does so only after a device pass has found that
+ * in_off/in_idx hold the transpose of every graph, and otherwise never walks
+ * them.  Pull sums every row in FP64 (per
  * lane in slot order, then a fixed lane reduction), so results are
  * bit-reproducible; push accumulates in FP64 LDS atomics, or as the pull does
  * in shared steps.  Graphs are taken largest first.  SYNC. */

@@ -280,8 +280,10 @@ constexpr int32_t kStepRowCost = 16;
 
 // First row before which the graph, rows and slots cost t or more.
 __global__ void k_multi_pieces(const MultiEntry* __restrict__ table, const int32_t* __restrict__ in_off, int32_t count,
-                               MultiPiece* __restrict__ pc, const int32_t* __restrict__ err) {
+                               MultiPiece* __restrict__ pc, const int32_t* __restrict__ err,
+                               unsigned long long* __restrict__ marks) {
     const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == 0) *marks = 0ull;
     if (i >= count || *err) return;
     const MultiEntry e = table[pc[i].entry];
     const int32_t* off = in_off + e.obase;
@@ -297,6 +299,99 @@ __global__ void k_multi_pieces(const MultiEntry* __restrict__ table, const int32
     const int32_t t0 = pc[i].r0, t1 = pc[i].r1;
     pc[i].r0 = t0 <= 0 ? 0 : row(t0);
     pc[i].r1 = t1 == INT32_MAX ? e.n : row(t1);
+}
+
+// 64 bits that mark an edge, in one of a pair's two directions: the finalizer of
+// MurmurHash3 (Appleby) on the ids, 28 bits, under two seeds of the graph.  Two lists
+// hold the same edges when the sums of their marks agree, and other lists agree
+// with probability 2^-64.
+__device__ __forceinline__ uint32_t mix32(uint32_t h) {
+    h ^= h >> 16;
+    h *= 0x85EBCA6Bu;
+    h ^= h >> 13;
+    h *= 0xC2B2AE35u;
+    return h ^ (h >> 16);
+}
+__device__ __forceinline__ uint64_t edge_mark(uint32_t s0, uint32_t s1, int32_t v, int32_t u) {
+    const uint32_t key = ((uint32_t)v << 14) | (uint32_t)u;
+    return ((uint64_t)mix32(key ^ s0) << 32) | mix32(key + s1);
+}
+
+// Sum of mark(row, id) over the slots of rows [r0, r1): a thread takes eight
+// consecutive slots and finds the first one's row among the offsets, staged in
+// s_off (sixteen lanes a row, offsets and ids loaded row by row, took ten times
+// as long).  Workgroup-collective.
+template <typename F>
+__device__ __forceinline__ uint64_t sum_marks(const int32_t* off, const uint16_t* idx, int32_t r0, int32_t r1,
+                                              int32_t* s_off, F mark) {
+    constexpr int U = 8;
+    __syncthreads();  // the previous rows are done with
+    for (int32_t i = threadIdx.x; i <= r1 - r0; i += kMultiBlock) s_off[i] = off[r0 + i];
+    __syncthreads();
+    uint64_t h = 0;
+    const int32_t first = s_off[0], count = s_off[r1 - r0] - first;
+    for (int64_t j0 = (int64_t)threadIdx.x * U; j0 < count; j0 += (int64_t)kMultiBlock * U) {
+        const int32_t live = (int32_t)min((int64_t)U, count - j0), j = first + (int32_t)j0;
+        int32_t id[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) id[k] = idx[j + min(k, live - 1)];
+        int32_t lo = 0, hi = r1 - r0;  // the last row that begins at or before slot j
+        while (hi - lo > 1) {
+            const int32_t m = (lo + hi) >> 1;
+            if (s_off[m] <= j) lo = m;
+            else hi = m;
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            if (k >= live) break;
+            while (s_off[lo + 1] <= j + k) ++lo;
+            h += mark(r0 + lo, id[k]);
+        }
+    }
+    return h;
+}
+
+// Whether the in-arrays hold the transpose of every graph: *marks ends at zero
+// where they do.  Steps that sum what a push sends where it arrives need it; a
+// caller who pushes directed graphs may have no in-arrays and pass the out-arrays
+// twice.  128 R-MAT graphs of scales 8-14: 1,058 -> 1,114 us a pushed call, 15 of it the host's look.
+__global__ __launch_bounds__(kMultiBlock) void k_multi_match(const MultiEntry* __restrict__ table,
+                                                             const MultiPiece* __restrict__ pieces,
+                                                             const int32_t* __restrict__ wg,
+                                                             const int32_t* __restrict__ off,
+                                                             const uint16_t* __restrict__ idx,
+                                                             const int32_t* __restrict__ in_off,
+                                                             const uint16_t* __restrict__ in_idx,
+                                                             unsigned long long* marks, const int32_t* err) {
+    extern __shared__ int32_t s_rows[];  // [largest n + 1]
+    __shared__ unsigned long long s_h;
+    if (*err) return;
+    if (threadIdx.x == 0) s_h = 0ull;
+    __syncthreads();
+    uint64_t h = 0;
+    const bool same = in_off == off && in_idx == idx;
+    for (int32_t p = wg[blockIdx.x]; p < wg[blockIdx.x + 1]; ++p) {
+        const MultiPiece pc = pieces[p];
+        const MultiEntry e = table[pc.entry];
+        if (pc.r0 >= pc.r1) continue;
+        const uint32_t s0 = mix32(2u * (uint32_t)pc.entry + 1u), s1 = mix32(2u * (uint32_t)pc.entry + 2u);
+        if (same) {  // as often v -> u as u -> v
+            h += sum_marks(off + e.obase, idx + e.ebase, pc.r0, pc.r1, s_rows, [=](int32_t v, int32_t u) {
+                const uint64_t m = edge_mark(s0, s1, min(v, u), max(v, u));
+                return v < u ? m : v > u ? ~m + 1u : 0u;
+            });
+        } else {
+            h += sum_marks(off + e.obase, idx + e.ebase, pc.r0, pc.r1, s_rows,
+                           [=](int32_t v, int32_t u) { return edge_mark(s0, s1, v, u); });
+            h -= sum_marks(in_off + e.obase, in_idx + e.ebase, pc.r0, pc.r1, s_rows,
+                           [=](int32_t u, int32_t v) { return edge_mark(s0, s1, v, u); });
+        }
+    }
+#pragma unroll
+    for (int s = kWave / 2; s > 0; s >>= 1) h += __shfl_xor((unsigned long long)h, s);
+    if ((threadIdx.x & (kWave - 1)) == 0) atomicAdd(&s_h, (unsigned long long)h);
+    __syncthreads();
+    if (threadIdx.x == 0 && s_h) atomicAdd(marks, s_h);
 }
 
 struct StepArgs {
@@ -316,8 +411,8 @@ struct StepArgs {
 
 // One PageRank step of every graph: a workgroup stages the contributions of a
 // piece's graph in LDS and pulls the piece's rows as k_multi does (the pushing
-// form too: an FP64 sum over the in-edges is what the FP64 adds of the out-edges
-// come to, rounded once).  Bound by latency: the pieces' rows of a 128-graph batch are 32 MB of
+// form too, where the in-arrays are the transpose: an FP64 sum over the in-edges
+// is what the FP64 adds of the out-edges come to, rounded once).  Bound by latency: the pieces' rows of a 128-graph batch are 32 MB of
 // ids, 5 us at the rate of memory.  Laying the gathered values down in slot order
 // and summing rows from there took 73 to 100 us a step against 74 of this form,
 // before the shares knew what a graph costs.
@@ -759,10 +854,10 @@ static bool launch_multi(int32_t pg, int32_t ml, const MultiArgs& a, int32_t gri
 
 // Workspace: the graph table (LPT order) and the validation error word, both
 // written by one host copy, then the push contributions (one float per vertex).
-// After those, where it fits, what the shared steps need: the pieces and every
-// workgroup's first one.
+// After those, where it fits, what the shared steps need: the pieces, every
+// workgroup's first one and the marks' sum.
 struct MultiLayout {
-    size_t table, err, cbuf, base, pieces, wg, total;
+    size_t table, err, cbuf, base, pieces, wg, marks, total;
 };
 
 static MultiLayout multi_layout(int32_t count, int64_t total_n) {
@@ -773,7 +868,8 @@ static MultiLayout multi_layout(int32_t count, int64_t total_n) {
     L.base = L.cbuf + align_up((size_t)std::max<int64_t>(total_n, 1) * 4, 256);
     L.pieces = L.base;
     L.wg = L.pieces + align_up(((size_t)std::max(count, 1) + kStepGroups) * sizeof(MultiPiece), 256);
-    L.total = L.wg + align_up((kStepGroups + 1) * sizeof(int32_t), 256);
+    L.marks = align_up(L.wg + (kStepGroups + 1) * sizeof(int32_t), 8);
+    L.total = align_up(L.marks + sizeof(unsigned long long), 256);
     return L;
 }
 
@@ -938,17 +1034,34 @@ static pp_status multi_run(int32_t num_graphs, const int32_t* graph_n, const int
         }
         while ((int32_t)wg.size() <= kStepGroups) wg.push_back((int32_t)pieces.size());
     }
-    if (!pieces.empty()) {
-        char* base = static_cast<char*>(ws);
-        StepArgs sa{};
-        MultiPiece* pc = reinterpret_cast<MultiPiece*>(base + ML.pieces);
+    MultiPiece* const pc = reinterpret_cast<MultiPiece*>(static_cast<char*>(ws) + ML.pieces);
+    int32_t* const wg_dev = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + ML.wg);
+    bool shared = !pieces.empty();
+    if (shared) {
+        unsigned long long* marks = reinterpret_cast<unsigned long long*>(static_cast<char*>(ws) + ML.marks);
         PP_HIP(hipMemcpyAsync(pc, pieces.data(), pieces.size() * sizeof(MultiPiece), hipMemcpyHostToDevice, st));
-        PP_HIP(hipMemcpyAsync(base + ML.wg, wg.data(), wg.size() * sizeof(int32_t), hipMemcpyHostToDevice, st));
+        PP_HIP(hipMemcpyAsync(wg_dev, wg.data(), wg.size() * sizeof(int32_t), hipMemcpyHostToDevice, st));
         hipLaunchKernelGGL(k_multi_pieces, dim3(ceil_div((int64_t)pieces.size(), 64)), dim3(64), 0, st,
-                           (const MultiEntry*)table, in_off, (int32_t)pieces.size(), pc, (const int32_t*)err);
+                           (const MultiEntry*)table, in_off, (int32_t)pieces.size(), pc, (const int32_t*)err, marks);
+        PP_LAUNCH_CHECK("k_multi_pieces");
+        if (pr_dir == PP_PUSH) {
+            const size_t rows_lds = ((size_t)max_n + 1) * sizeof(int32_t);
+            allow_dynamic_lds(reinterpret_cast<const void*>(&k_multi_match), rows_lds);
+            hipLaunchKernelGGL(k_multi_match, dim3(kStepGroups), dim3(kMultiBlock), rows_lds, st, (const MultiEntry*)table,
+                               (const MultiPiece*)pc, (const int32_t*)wg_dev, off, idx, in_off, in_idx, marks,
+                               (const int32_t*)err);
+            PP_LAUNCH_CHECK("k_multi_match");
+            unsigned long long left = 0;
+            PP_HIP(hipMemcpyAsync(&left, marks, sizeof(left), hipMemcpyDeviceToHost, st));
+            PP_HIP(hipStreamSynchronize(st));
+            shared = left == 0;
+        }
+    }
+    if (shared) {
+        StepArgs sa{};
         sa.table = table;
         sa.pc = pc;
-        sa.wg = reinterpret_cast<const int32_t*>(base + ML.wg);
+        sa.wg = wg_dev;
         sa.off = off;
         sa.in_off = in_off;
         sa.in_idx = in_idx;

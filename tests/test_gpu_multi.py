@@ -213,3 +213,24 @@ def test_malformed_large_graph_leaves_the_outputs():
                               24.0, lv, lv.clone(), mg.ws)
         assert ei.value.status == _lib.PP_E_GRAPH
         assert bool((x == -7.0).all()) and bool((lv == -9).all())
+
+
+def test_pushing_reads_the_out_arrays_alone():
+    # PageRank pushed on directed graphs whose caller passes the out-arrays for
+    # the in-arrays as well (they are only checked): graphs below and above the
+    # size from which steps are shared, some of them in one workgroup's share
+    gs = [H.random_graph(n, m, 31 + n, symmetric=False) for n, m in ((9000, 120_000), (500, 3000), (63, 200))]
+    gs.append(gg.from_edges(1, [], [], False, name="one"))
+    gs.append(gg.from_edges(16384, np.repeat(np.arange(4), 16383), np.tile(np.arange(1, 16384), 4), False, name="hubs"))
+    for h in gs:
+        h.ensure_transpose()
+    mg = pp.MultiGraph(gs)
+    off, idx = mg.off, mg.idx
+    for iters in (1, 4):
+        announce(f"multi pushed without in-arrays T={iters}")
+        x = torch.full((mg.total_n,), -7.0, device="cuda")
+        _lib.pp_multi_run(mg.n, mg.nnz, off, idx, off, idx, pp.PP_PUSH, iters, F, x, -1, 0, 14.0, 24.0, None, None,
+                          mg.ws)
+        for h, xi in zip(gs, mg.split(x.cpu().numpy())):
+            want = oracle.pagerank(h.off, h.idx, F, iters)
+            assert np.abs(xi.astype(np.float64) - want).sum() <= PR_L1_TOL, (h.name, iters)
