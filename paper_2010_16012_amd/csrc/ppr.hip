@@ -1057,8 +1057,9 @@ static pp_status run_tile(pp_graph g, bool adjoint, pp_dir dir, int32_t k, int32
     const int64_t cells = (int64_t)n * KT;
     const dim3 cb(ceil_div(cells, 256)), ct(256);
     // updates meet at shared FP64 accumulators (cleared here) only when they
-    // are sent as atomics, and in the sparse sweeps of PP_SWITCH
-    const bool atomics = dir == PP_PUSH && !g->tune.push_bins;
+    // are sent as atomics (asked for, or the other adjacency does not list them),
+    // and in the sparse sweeps of PP_SWITCH
+    const bool atomics = dir == PP_PUSH && !(g->tune.push_bins && g->transposed);
     double* acc0 = (atomics || dir == PP_SWITCH) ? t4 : nullptr;
     if (adjoint) hipLaunchKernelGGL(k_kcol_adjoint_init<KT>, cb, ct, 0, st, n, k, col0, g->d.perm, g_caller, t0, acc0);
     else hipLaunchKernelGGL(k_kcol_forward_init<KT>, cb, ct, 0, st, n, src_int, col0, f, g->d.inv_s, t0, t2, acc0);

@@ -421,10 +421,11 @@ pp_status build_route(pp_graph g, void* edges, void* tables, hipStream_t st) {
 }
 
 // Which sweeps take the routed path: pulls without a tiled plan where it pays,
-// pushes whose remote updates are buffered (pp_set_push_bins).
+// pushes whose remote updates are buffered (pp_set_push_bins).  No plan is made
+// where the in-adjacency is not the transpose.
 bool route_for(pp_graph g, pp_dir dir) {
     if (g->route.blocks == 0) return false;
-    return dir == PP_PULL ? (g->route.pull && g->slices.rows == 0) : (g->tune.push_bins && g->tune.hot > 0);
+    return dir == PP_PULL ? (g->route.pull && g->slices.rows == 0) : (g->tune.push_bins && g->tune.hot > 0 && g->transposed);
 }
 
 // One routed sweep: y and / or the next contributions from c.

@@ -226,7 +226,7 @@ bool small_for(pp_graph g, pp_dir dir) {
     const GraphDev& d = g->d;
     if (d.n > kSmallN || d.nnz < 1 || small_lds(d.n) > (size_t)g->max_lds - 1024) return false;
     if (small_pieces(g) > (int64_t)kSmallMaxWaves * kWave * (g->weighted ? kSmallQW : kSmallQ)) return false;
-    return dir == PP_PULL || (dir == PP_PUSH && g->tune.push_bins && g->tune.hot > 0);
+    return dir == PP_PULL || (dir == PP_PUSH && g->tune.push_bins && g->tune.hot > 0 && g->transposed);
 }
 
 // All steps of a run: x_0 = x (caller ids; NULL: the unit vector of

@@ -552,3 +552,47 @@ def test_renumbering_over_few_and_many_tiles(n):
     h = H.random_graph(n, 3 * n, n % 97, symmetric=True) if n > 1 else gg.from_edges(1, [], [], True)
     got = pp.pagerank(pp.Graph(h), iters=3, f=F).cpu().numpy().astype(np.float64)
     assert np.abs(got - oracle.pagerank(h.off, h.idx, F, 3)).sum() <= PR_L1_TOL
+
+
+@pytest.mark.parametrize("n,m,weighted", [(700, 5000, False), (700, 5000, True), (30000, 200000, False),
+                                          (30000, 200000, True)])
+def test_pushing_a_directed_graph_given_its_out_arrays_twice(n, m, weighted):
+    # a caller who only pushes may have no in-arrays: the pushes keep to the
+    # out-rows, in one workgroup's range and past it, and in k-column tiles
+    host = H.random_graph(n, m, 41, symmetric=False, connected=True)
+    if weighted:
+        gg.with_weights(host, seed=3)
+    host.ensure_transpose()
+    src = gg.pick_vertices(host, 3, seed=5)
+    want, _ = oracle.ppr(host.off, host.idx, src, F, T=8, weights=host.weights)
+    want_x = oracle.pagerank(host.off, host.idx, F, 8) if not weighted else None
+    host.in_off, host.in_idx = host.off, host.idx
+    if weighted:
+        host.in_to_out = np.arange(host.nnz, dtype=np.int32)
+    for rl in (True, False):
+        g = pp.Graph(host, relabel=rl)
+        announce(f"out-arrays twice n={n} weighted={weighted} relabel={rl}")
+        for kt in (1, 8):
+            X = pp.ppr(g, src, iters=8, f=F, k_tile=kt, direction=pp.PP_PUSH)[0].cpu().numpy().astype(np.float64)
+            assert np.abs(X - want).sum(axis=0).max() <= PR_L1_TOL, (rl, kt)
+        if want_x is not None:
+            assert np.abs(pr_gpu(g, pp.PP_PUSH, 8).astype(np.float64) - want_x).sum() <= PR_L1_TOL, rl
+            x0 = torch.full((n,), 1.0 / n, device="cuda")
+            y = torch.empty_like(x0)
+            _lib.pp_pr_push(g.handle, x0, y, F)
+            assert np.abs(y.cpu().numpy().astype(np.float64) - oracle.pagerank(host.off, host.idx, F, 1)).sum() <= PR_L1_TOL
+        g.close()
+
+
+def test_a_wrong_slot_map_leaves_the_pushes_alone():
+    # a symmetric weighted graph whose in-slots are mapped to themselves: the
+    # weights of the out-slots are the ones that a push sends
+    host = H.random_graph(20000, 90000, 43, symmetric=True, connected=True)
+    gg.with_weights(host, seed=3)
+    src = gg.pick_vertices(host, 2, seed=5)
+    want, _ = oracle.ppr(host.off, host.idx, src, F, T=8, weights=host.weights)
+    host.in_off, host.in_idx, host.in_to_out = host.off, host.idx, np.arange(host.nnz, dtype=np.int32)
+    g = pp.Graph(host)
+    for kt in (1, 8):
+        X = pp.ppr(g, src, iters=8, f=F, k_tile=kt, direction=pp.PP_PUSH)[0].cpu().numpy().astype(np.float64)
+        assert np.abs(X - want).sum(axis=0).max() <= PR_L1_TOL, kt
