@@ -184,7 +184,8 @@ __device__ __forceinline__ void for_each_edge(const int32_t* verts, int32_t coun
             const int src = __ffsll((long long)big) - 1;
             big &= big - 1;
             const int32_t bv = __shfl(v, src), bb = __shfl(rb, src), be = __shfl(re, src);
-            for (int32_t j = bb + lane; j - lane < be; j += kWave) fn(j < be, bv, j < be ? idx[j] : -1);
+            for (slot_t j = (slot_t)bb + lane; j - lane < (slot_t)be; j += kWave)
+                fn(j < (slot_t)be, bv, j < (slot_t)be ? idx[j] : -1);
         }
         const int32_t mine = len < kWave ? len : 0;
         int32_t incl = mine;
@@ -237,10 +238,10 @@ __device__ __forceinline__ double row_sum(bool own, int32_t rb, int32_t re, cons
         big &= big - 1;
         const int32_t bb = __shfl(rb, src), be = __shfl(re, src);
         double t = 0.0;
-        for (int32_t j0 = bb + lane; j0 < be; j0 += kBcU * kWave) {
+        for (slot_t j0 = (slot_t)bb + lane; j0 < (slot_t)be; j0 += kBcU * kWave) {
             int32_t ii[kBcU];
 #pragma unroll
-            for (int k = 0; k < kBcU; ++k) ii[k] = (j0 + k * kWave < be) ? idx[j0 + k * kWave] : -1;
+            for (int k = 0; k < kBcU; ++k) ii[k] = slot_in(j0, k * kWave, be) ? idx[j0 + k * kWave] : -1;
 #pragma unroll
             for (int k = 0; k < kBcU; ++k)
                 if (ii[k] >= 0) t += val(ii[k]);
@@ -250,10 +251,10 @@ __device__ __forceinline__ double row_sum(bool own, int32_t rb, int32_t re, cons
         if (lane == src) acc = t;
     }
     if (own && !coop) {
-        for (int32_t j0 = rb; j0 < re; j0 += kBcU) {
+        for (slot_t j0 = rb; j0 < (slot_t)re; j0 += kBcU) {
             int32_t ii[kBcU];
 #pragma unroll
-            for (int k = 0; k < kBcU; ++k) ii[k] = (j0 + k < re) ? idx[j0 + k] : -1;
+            for (int k = 0; k < kBcU; ++k) ii[k] = slot_in(j0, k, re) ? idx[j0 + k] : -1;
 #pragma unroll
             for (int k = 0; k < kBcU; ++k)
                 if (ii[k] >= 0) acc += val(ii[k]);

@@ -505,7 +505,7 @@ __global__ void k_bfs_init(BfsArgs a, int32_t root_user, int64_t nnz) {
 // counter atomic per call.
 __device__ __forceinline__ void queue_chunks(const BfsArgs& a, bool huge, int32_t v, int32_t rb, int32_t re,
                                              int32_t chunk, BfsSlot* nxt, int lane) {
-    const int32_t nch = huge ? (re - rb + chunk - 1) / chunk : 0;
+    const int32_t nch = huge ? (int32_t)(((slot_t)(re - rb) + chunk - 1) / chunk) : 0;
     int32_t incl = nch;
 #pragma unroll
     for (int d = 1; d < kWave; d <<= 1) {
@@ -527,7 +527,7 @@ __device__ __forceinline__ void queue_chunks(const BfsArgs& a, bool huge, int32_
             if (it < a.item_cap) {
                 a.items[3 * it] = hv;
                 a.items[3 * it + 1] = hb + k * chunk;
-                a.items[3 * it + 2] = min(he, hb + (k + 1) * chunk);
+                a.items[3 * it + 2] = slot_piece_end(hb, k, chunk, he);
             } else {
                 atomicOr(&a.hdr->overflow, 2);
             }
@@ -671,12 +671,11 @@ __device__ __forceinline__ void agg_end(const BfsArgs& a, const TdCtx<RUN>& cx) 
 template <bool RUN>
 __device__ __forceinline__ void td_row(const BfsArgs& a, const TdCtx<RUN>& cx, Pager& pg, int32_t v, int32_t b,
                                        int32_t e, int32_t& cnt, int64_t& deg, int lane) {
-    for (int32_t jb = b; jb < e; jb += kTdU * kWave) {
+    for (slot_t jb = b; jb < (slot_t)e; jb += kTdU * kWave) {
         int32_t u[kTdU], pv[kTdU];
 #pragma unroll
         for (int r = 0; r < kTdU; ++r) {
-            const int32_t j = jb + r * kWave + lane;
-            u[r] = (j < e) ? a.csr_idx[j] : -1;
+            u[r] = slot_in(jb, r * kWave + lane, e) ? a.csr_idx[jb + r * kWave + lane] : -1;
             pv[r] = v;
         }
         td_batch<true>(a, cx, pg, u, pv, cnt, deg, lane);
@@ -828,12 +827,11 @@ constexpr int32_t kCoopRow = 128;  // in-rows at least this long are scanned by 
 __device__ __forceinline__ void bu_scan_row(const BfsArgs& a, const FbView& fv, int32_t b, int32_t e, int lane,
                                             int32_t& pos) {
     pos = -1;
-    for (int32_t jb = b; jb < e; jb += kBuU * kWave) {
+    for (slot_t jb = b; jb < (slot_t)e; jb += kBuU * kWave) {
         int32_t u[kBuU];
 #pragma unroll
         for (int r = 0; r < kBuU; ++r) {
-            const int32_t j = jb + r * kWave + lane;
-            u[r] = (j < e) ? a.csc_idx[j] : -1;
+            u[r] = slot_in(jb, r * kWave + lane, e) ? a.csc_idx[jb + r * kWave + lane] : -1;
         }
         bool hit[kBuU];
 #pragma unroll
@@ -908,10 +906,10 @@ __device__ __forceinline__ void level_bottom_up(const BfsArgs& a, int32_t lvl, c
         // short in-rows: each lane scans its own, in stored order, kBuB
         // independent loads at a time
         if (unvisited && !coop) {
-            for (int32_t j = rb; j < re && !found; j += kBuB) {
+            for (slot_t j = rb; j < (slot_t)re && !found; j += kBuB) {
                 int32_t u[kBuB];
 #pragma unroll
-                for (int r = 0; r < kBuB; ++r) u[r] = (j + r < re) ? a.csc_idx[j + r] : -1;
+                for (int r = 0; r < kBuB; ++r) u[r] = slot_in(j, r, re) ? a.csc_idx[j + r] : -1;
                 bool hit[kBuB];
 #pragma unroll
                 for (int r = 0; r < kBuB; ++r) hit[r] = (u[r] >= 0) && fb_test(fv, u[r]);

@@ -254,11 +254,11 @@ __global__ __launch_bounds__(256) void k_relabel_rows(int32_t n, const int32_t* 
         const int32_t b = off[v], e = off[v + 1], o = off_new[i];
         // eight slots a lane in flight: a hub's row is one wavefront's work
         constexpr int U = 8;
-        for (int32_t j0 = b + lane; j0 < e; j0 += U * kWave) {
+        for (slot_t j0 = (slot_t)b + lane; j0 < (slot_t)e; j0 += U * kWave) {
             int32_t jj[U], v_[U], m_[U];
             float w_[U];
 #pragma unroll
-            for (int k = 0; k < U; ++k) jj[k] = min(j0 + k * kWave, e - 1);
+            for (int k = 0; k < U; ++k) jj[k] = (int32_t)slot_at(j0, k * kWave, e);
             if (idx_new) {
 #pragma unroll
                 for (int k = 0; k < U; ++k) v_[k] = idx[jj[k]];
@@ -266,7 +266,7 @@ __global__ __launch_bounds__(256) void k_relabel_rows(int32_t n, const int32_t* 
                 for (int k = 0; k < U; ++k) v_[k] = iperm[v_[k]];
 #pragma unroll
                 for (int k = 0; k < U; ++k)
-                    if (j0 + k * kWave < e) idx_new[o + (jj[k] - b)] = v_[k];
+                    if (slot_in(j0, k * kWave, e)) idx_new[o + (jj[k] - b)] = v_[k];
             }
             if (w_new) {
 #pragma unroll
@@ -275,7 +275,7 @@ __global__ __launch_bounds__(256) void k_relabel_rows(int32_t n, const int32_t* 
                 for (int k = 0; k < U; ++k) w_[k] = wsrc[m_[k]];
 #pragma unroll
                 for (int k = 0; k < U; ++k)
-                    if (j0 + k * kWave < e) w_new[o + (jj[k] - b)] = w_[k];
+                    if (slot_in(j0, k * kWave, e)) w_new[o + (jj[k] - b)] = w_[k];
             }
         }
     }
@@ -303,12 +303,12 @@ __global__ __launch_bounds__(256) void k_strengths(int32_t n, const int32_t* __r
         const int32_t lb = __shfl(b, src), le = __shfl(e, src);
         constexpr int U = 8;
         double t = 0.0;
-        for (int32_t j0 = lb + lane; j0 < le; j0 += U * kWave) {
+        for (slot_t j0 = (slot_t)lb + lane; j0 < (slot_t)le; j0 += U * kWave) {
             float x[U];
 #pragma unroll
-            for (int k = 0; k < U; ++k) x[k] = w[min(j0 + k * kWave, le - 1)];
+            for (int k = 0; k < U; ++k) x[k] = w[slot_at(j0, k * kWave, le)];
 #pragma unroll
-            for (int k = 0; k < U; ++k) t += j0 + k * kWave < le ? (double)x[k] : 0.0;
+            for (int k = 0; k < U; ++k) t += slot_in(j0, k * kWave, le) ? (double)x[k] : 0.0;
         }
 #pragma unroll
         for (int d = 32; d > 0; d >>= 1) t += __shfl_xor(t, d);
@@ -343,8 +343,8 @@ __global__ void k_gather_weights(int64_t nnz, const float* __restrict__ csr_w, c
 __global__ void k_max_deg(int32_t n, const int32_t* __restrict__ off, const int32_t* __restrict__ in_off,
                           int32_t* __restrict__ out) {
     int32_t a = 0, b = 0, c = 0, z = 0;  // c: v + 1 for a vertex with in-edges
-    for (int32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gridDim.x * blockDim.x) {
-        const int32_t d = row_len(in_off, v);
+    for (uint32_t t = blockIdx.x * blockDim.x + threadIdx.x; t < (uint32_t)n; t += gridDim.x * blockDim.x) {
+        const int32_t v = (int32_t)t, d = row_len(in_off, v);
         a = max(a, row_len(off, v));
         b = max(b, d);
         if (d > 0) c = v + 1;
@@ -402,7 +402,7 @@ __global__ void k_row_owner(int32_t n, const int32_t* off, int32_t* row) {
             const int src = __ffsll((long long)m) - 1;
             m &= m - 1;
             const int32_t lb = __shfl(b, src), le = __shfl(e, src);
-            for (int32_t j = lb + lane; j < le; j += kWave) row[j] = (int32_t)(v0 + (int64_t)src * nw);
+            for (slot_t j = (slot_t)lb + lane; j < (slot_t)le; j += kWave) row[j] = (int32_t)(v0 + (int64_t)src * nw);
         }
     }
 }

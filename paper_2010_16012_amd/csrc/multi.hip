@@ -84,15 +84,14 @@ __device__ __forceinline__ uint32_t bit_of(const uint32_t* bm, int32_t v) { retu
 // before; slots past the row's end read the zero word s_zero.
 template <int STRIDE, int U, typename I>
 __device__ __forceinline__ void gather_row_slots(const I* __restrict__ ids, const float* s_c, const float* s_zero,
-                                                 int32_t j0, int32_t re, double& acc) {
+                                                 slot_t j0, slot_t re, double& acc) {
     const char* base = reinterpret_cast<const char*>(ids);
     const float* src[U];
 #pragma unroll
     for (int k = 0; k < U; ++k) {
-        const int32_t j = j0 + k * STRIDE;
-        const uint32_t boff = (uint32_t)min(j, re - 1) * (uint32_t)sizeof(I);
+        const uint32_t boff = slot_at(j0, k * STRIDE, re) * (uint32_t)sizeof(I);
         const uint32_t id = *reinterpret_cast<const I*>(base + boff);
-        src[k] = j < re ? s_c + id : s_zero;
+        src[k] = slot_in(j0, k * STRIDE, re) ? s_c + id : s_zero;
     }
     float cv[U];
 #pragma unroll
@@ -172,7 +171,7 @@ __device__ __forceinline__ void multi_pull_rows(const int32_t* in_off, const uin
         const int32_t u = s_big[i];
         double acc = 0.0;
         const int32_t rb = in_off[u], re = in_off[u + 1];
-        for (int32_t j0 = rb + wl; j0 < re; j0 += kMultiU * kWave)
+        for (slot_t j0 = (slot_t)rb + wl; j0 < (slot_t)re; j0 += kMultiU * kWave)
             gather_row_slots<kWave, kMultiU>(in_idx, s_c, s_zero, j0, re, acc);
 #pragma unroll
         for (int s = kWave / 2; s > 0; s >>= 1) acc += __shfl_xor(acc, s);
@@ -200,7 +199,7 @@ __device__ __forceinline__ void multi_pull_rows(const int32_t* in_off, const uin
                 noe = off[nu + 1];
             }
             double acc = 0.0;
-            for (int32_t j0 = rb + hl; j0 < re; j0 += kMultiU * ML)
+            for (slot_t j0 = (slot_t)rb + hl; j0 < (slot_t)re; j0 += kMultiU * ML)
                 gather_row_slots<ML, kMultiU>(in_idx, s_c, s_zero, j0, re, acc);
 #pragma unroll
             for (int s = ML / 2; s > 0; s >>= 1) acc += __shfl_xor(acc, s);
@@ -227,7 +226,7 @@ __device__ __forceinline__ void multi_pull_rows(const int32_t* in_off, const uin
             noe = off[u + pgroups + 1];
         }
         if (!grouped(re - rb)) continue;  // group-uniform
-        for (int32_t j0 = rb + plane; j0 < re; j0 += kMultiPullU * PG)
+        for (slot_t j0 = (slot_t)rb + plane; j0 < (slot_t)re; j0 += kMultiPullU * PG)
             gather_row_slots<PG, kMultiPullU>(in_idx, s_c, s_zero, j0, re, acc);
 #pragma unroll
         for (int s = PG / 2; s > 0; s >>= 1) acc += __shfl_xor(acc, s);
@@ -550,12 +549,11 @@ __global__ __launch_bounds__(kMultiBlock) void k_multi(MultiArgs a) {
                     const float cv = c[v];
                     if (cv == 0.f) continue;
                     const int32_t rb = off[v], re = off[v + 1];
-                    for (int32_t j0 = rb + wl; j0 < re; j0 += kMultiU * kWave) {
+                    for (slot_t j0 = (slot_t)rb + wl; j0 < (slot_t)re; j0 += kMultiU * kWave) {
                         int32_t ii[kMultiU];
 #pragma unroll
                         for (int k = 0; k < kMultiU; ++k) {
-                            const int32_t j = j0 + k * kWave;
-                            ii[k] = j < re ? idx[j] : -1;
+                            ii[k] = slot_in(j0, k * kWave, re) ? idx[j0 + k * kWave] : -1;
                         }
 #pragma unroll
                         for (int k = 0; k < kMultiU; ++k)
@@ -582,14 +580,14 @@ __global__ __launch_bounds__(kMultiBlock) void k_multi(MultiArgs a) {
                             ne = off[nv + 1];
                         }
                         if (cv == 0.f) continue;
-                        for (int32_t j0 = rb + hl; j0 < re; j0 += kMultiU * ML) {
+                        for (slot_t j0 = (slot_t)rb + hl; j0 < (slot_t)re; j0 += kMultiU * ML) {
                             int32_t ii[kMultiU];  // clamped to the row's last slot
 #pragma unroll
                             for (int k = 0; k < kMultiU; ++k)
-                                ii[k] = idx[(uint32_t)min(j0 + k * ML, re - 1)];
+                                ii[k] = idx[slot_at(j0, k * ML, re)];
 #pragma unroll
                             for (int k = 0; k < kMultiU; ++k)
-                                if (j0 + k * ML < re) atomicAdd(&s_acc[ii[k]], (double)cv);
+                                if (slot_in(j0, k * ML, re)) atomicAdd(&s_acc[ii[k]], (double)cv);
                         }
                     }
                 }
@@ -627,8 +625,8 @@ __global__ __launch_bounds__(kMultiBlock) void k_multi(MultiArgs a) {
                         // contribution, or a long row (done above)
                         if (v + r * groups >= n || cv[r] == 0.f || !grouped(re[r] - rb[r])) re[r] = rb[r];
                     }
-                    const int32_t len = max(re[0] - rb[0], re[1] - rb[1]);
-                    for (int32_t d = lane; d < len; d += kMultiU * kMultiGroup) {
+                    const slot_t len = max(re[0] - rb[0], re[1] - rb[1]);
+                    for (slot_t d = lane; d < len; d += kMultiU * kMultiGroup) {
                         // clamped into [0, re - 1]: a finished or empty row
                         // rereads a valid slot (the graph has edges, or len = 0)
                         int32_t ii[2][kMultiU];
@@ -636,12 +634,12 @@ __global__ __launch_bounds__(kMultiBlock) void k_multi(MultiArgs a) {
                         for (int r = 0; r < 2; ++r)
 #pragma unroll
                             for (int k = 0; k < kMultiU; ++k)
-                                ii[r][k] = idx[(uint32_t)max(min(rb[r] + d + k * kMultiGroup, re[r] - 1), 0)];
+                                ii[r][k] = idx[re[r] > 0 ? slot_at((slot_t)rb[r] + d, k * kMultiGroup, re[r]) : 0u];
 #pragma unroll
                         for (int r = 0; r < 2; ++r)
 #pragma unroll
                             for (int k = 0; k < kMultiU; ++k)
-                                if (rb[r] + d + k * kMultiGroup < re[r]) atomicAdd(&s_acc[ii[r][k]], (double)cv[r]);
+                                if (slot_in((slot_t)rb[r] + d, k * kMultiGroup, re[r])) atomicAdd(&s_acc[ii[r][k]], (double)cv[r]);
                     }
                 }
                 __syncthreads();
@@ -704,20 +702,20 @@ __global__ __launch_bounds__(kMultiBlock) void k_multi(MultiArgs a) {
         if (dir == PP_PUSH) {
             // frontier vertices claim unvisited out-neighbours (LDS atomic OR):
             // slots j0, j0 + stride, ... of v's row, which ends at re
-            auto scatter = [&](int32_t v, int32_t j0, int32_t stride, int32_t re) {
+            auto scatter = [&](int32_t v, slot_t j0, int32_t stride, slot_t re) {
                 // index loads clamped to the row's last slot, then every
                 // visited probe issued before the first claim (a probe only
                 // filters: the atomic OR decides)
                 int32_t ii[kMultiU];
 #pragma unroll
-                for (int k = 0; k < kMultiU; ++k) ii[k] = idx[(uint32_t)min(j0 + k * stride, re - 1)];
+                for (int k = 0; k < kMultiU; ++k) ii[k] = idx[slot_at(j0, k * stride, re)];
                 uint32_t seen[kMultiU];
 #pragma unroll
                 for (int k = 0; k < kMultiU; ++k) seen[k] = s_vis[min(ii[k], n - 1) >> 5];
 #pragma unroll
                 for (int k = 0; k < kMultiU; ++k) {
                     const int32_t u = ii[k];
-                    if (j0 + k * stride >= re || u >= n) continue;  // ids past the graph are ignored
+                    if (!slot_in(j0, k * stride, re) || u >= n) continue;  // ids past the graph are ignored
                     const uint32_t b = 1u << (u & 31);
                     if (seen[k] & b) continue;
                     const uint32_t old = atomicOr(&s_vis[u >> 5], b);
@@ -747,7 +745,7 @@ __global__ __launch_bounds__(kMultiBlock) void k_multi(MultiArgs a) {
                         continue;
                     }
                 }
-                for (int32_t j0 = rb + lane; j0 < re; j0 += kMultiU * kMultiGroup) scatter(v, j0, kMultiGroup, re);
+                for (slot_t j0 = (slot_t)rb + lane; j0 < (slot_t)re; j0 += kMultiU * kMultiGroup) scatter(v, j0, kMultiGroup, re);
             }
             __syncthreads();
             const int32_t nlong = min(s_n[0], kMultiMidCap);
@@ -755,9 +753,9 @@ __global__ __launch_bounds__(kMultiBlock) void k_multi(MultiArgs a) {
             for (int32_t i = 0; i < nlong; ++i) {
                 const int32_t v = s_mid[i];
                 const int32_t rb = off[v], re = off[v + 1];
-                const int32_t np = (re - rb + kBfsLong - 1) / kBfsLong;
+                const int32_t np = (int32_t)(((slot_t)(re - rb) + kBfsLong - 1) / kBfsLong);
                 for (; turn < np; turn += kWaves) {
-                    const int32_t b = rb + turn * kBfsLong, pe = min(re, b + kBfsLong);
+                    const slot_t b = (slot_t)rb + turn * kBfsLong, pe = min((slot_t)re, b + kBfsLong);
                     if (b + wl < pe) scatter(v, b + wl, kWave, pe);
                 }
                 turn -= np;
@@ -770,22 +768,22 @@ __global__ __launch_bounds__(kMultiBlock) void k_multi(MultiArgs a) {
                 int32_t hit = INT32_MAX;
                 // kMultiU steps of kMultiGroup in-neighbours per round; the
                 // first frontier member in stored order wins
-                for (int32_t jb = b0; jb < e0 && hit == INT32_MAX; jb += kMultiU * kMultiGroup) {
+                for (slot_t jb = b0; jb < (slot_t)e0 && hit == INT32_MAX; jb += kMultiU * kMultiGroup) {
                     // index loads clamped to the row's last slot, frontier words
                     // read together (ids past the graph read a valid word and
                     // are then ignored)
                     int32_t ii[kMultiU];
 #pragma unroll
                     for (int k = 0; k < kMultiU; ++k)
-                        ii[k] = in_idx[(uint32_t)min(jb + k * kMultiGroup + lane, e0 - 1)];
+                        ii[k] = in_idx[slot_at(jb, k * kMultiGroup + lane, e0)];
                     uint32_t fw[kMultiU];
 #pragma unroll
                     for (int k = 0; k < kMultiU; ++k) fw[k] = s_front[min(ii[k], n - 1) >> 5];
                     int32_t pos = INT32_MAX;
 #pragma unroll
                     for (int k = kMultiU - 1; k >= 0; --k) {
-                        const int32_t j = jb + k * kMultiGroup + lane;
-                        if (j < e0 && ii[k] < n && ((fw[k] >> (ii[k] & 31)) & 1u)) pos = j;
+                        if (slot_in(jb, k * kMultiGroup + lane, e0) && ii[k] < n && ((fw[k] >> (ii[k] & 31)) & 1u))
+                            pos = (int32_t)(jb + k * kMultiGroup + lane);
                     }
 #pragma unroll
                     for (int s = kMultiGroup / 2; s > 0; s >>= 1) pos = min(pos, __shfl_xor(pos, s));

@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "pp.h"
+#include "slots.h"
 
 #define PP_EXPORT extern "C" __attribute__((visibility("default")))
 

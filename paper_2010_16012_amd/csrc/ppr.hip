@@ -189,37 +189,37 @@ __device__ __forceinline__ Sum4<A> kt_gather4(const KArgs& a, int32_t b, int32_t
                                               int q) {
     const float4* __restrict__ src4 = reinterpret_cast<const float4*>(a.src);
     Sum4<A> acc{0, 0, 0, 0};
-    const int32_t step = U * stride;
-    int32_t j0 = b + g;
-    if (j0 >= e) return acc;
+    const slot_t step = U * stride;
+    slot_t j0 = (slot_t)b + g;
+    if (j0 >= (slot_t)e) return acc;
     int32_t vv[U];
     float ww[W ? U : 1];
-    auto fetch = [&](int32_t at) {
+    auto fetch = [&](slot_t at) {
 #pragma unroll
         for (int k = 0; k < U; ++k) {
-            const int32_t j = min(at + k * stride, e - 1);
+            const slot_t j = slot_at(at, k * stride, e);
             vv[k] = a.idx[j];
             if (W) ww[k] = a.wt[j];
         }
     };
     fetch(j0);
-    for (; j0 < e; j0 += step) {
+    for (; j0 < (slot_t)e; j0 += step) {
         float4 x[U];
 #pragma unroll
         for (int k = 0; k < U; ++k) {
             x[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (j0 + k * stride < e) x[k] = src4[(size_t)vv[k] * kq_lanes<KT>() + q];
+            if (slot_in(j0, k * stride, e)) x[k] = src4[(size_t)vv[k] * kq_lanes<KT>() + q];
         }
         float wk[W ? U : 1];
         if (W) {
 #pragma unroll
             for (int k = 0; k < U; ++k) wk[k] = ww[k];
         }
-        if (j0 + step < e) fetch(j0 + step);  // the next round's indices load beside this round's rows
+        if (slot_in(j0, step, e)) fetch(j0 + step);  // the next round's indices load beside this round's rows
         if (W) {
 #pragma unroll
             for (int k = 0; k < U; ++k)
-                if (j0 + k * stride < e) x[k] = f4_scale(x[k], wk[k]);
+                if (slot_in(j0, k * stride, e)) x[k] = f4_scale(x[k], wk[k]);
         }
         // widening is kept apart from the masked loads: inside the masks each
         // would be waited for by itself (6.0 against 4.3 ms at R-MAT 18, k = 64)
@@ -448,7 +448,7 @@ __device__ __forceinline__ void kt_scatter(const KPushArgs& a, int32_t v, int32_
                                            int32_t stride, int lane) {
     const float x = a.src[(size_t)v * KT + lane];
     if (x == 0.f) return;  // per-lane: a zero contributes nothing
-    for (int32_t j = b + g; j < e; j += stride) {
+    for (slot_t j = (slot_t)b + g; j < (slot_t)e; j += stride) {
         const int32_t u = a.idx[j];
         unsafeAtomicAdd(&a.acc[(size_t)u * KT + lane], (double)(W ? x * a.wt[j] : x));
     }
@@ -635,10 +635,10 @@ __device__ __forceinline__ void grad_row(const GradArgs& a, int32_t v, int32_t b
     const float scale = a.f * a.inv_s[v];
     const float4* __restrict__ lam = reinterpret_cast<const float4*>(a.lam);
     float* out = a.grad + a.user_off[vc] - a.off[v];
-    for (int32_t j0 = b + U * g; j0 < e; j0 += U * stride) {
+    for (slot_t j0 = (slot_t)b + U * g; j0 < (slot_t)e; j0 += U * stride) {
         int32_t u[U];
 #pragma unroll
-        for (int k = 0; k < U; ++k) u[k] = a.idx[min(j0 + k, e - 1)];
+        for (int k = 0; k < U; ++k) u[k] = a.idx[slot_at(j0, k, e)];
         float4 l[U];
 #pragma unroll
         for (int k = 0; k < U; ++k) l[k] = lam[(size_t)u[k] * Q + q];
@@ -648,7 +648,7 @@ __device__ __forceinline__ void grad_row(const GradArgs& a, int32_t v, int32_t b
                       (xv.z * (l[k].z - pv.z) + xv.w * (l[k].w - pv.w));
 #pragma unroll
             for (int s = Q / 2; s > 0; s >>= 1) t += __shfl_xor(t, s);
-            if (q == k % Q && j0 + k < e) {
+            if (q == k % Q && slot_in(j0, k, e)) {
                 const float gv = scale * t;
                 out[j0 + k] = a.add ? out[j0 + k] + gv : gv;
             }
@@ -732,7 +732,7 @@ __device__ __forceinline__ void sw_claim(const SwState& w, int32_t u) {
     if (e - b <= kSwChunk) {
         w.small[atomicAdd(&w.cnt[1], 1)] = u;
     } else {
-        const int32_t nch = (e - b + kSwChunk - 1) / kSwChunk;
+        const int32_t nch = (int32_t)(((slot_t)(e - b) + kSwChunk - 1) / kSwChunk);
         const int32_t first = atomicAdd(&w.cnt[2], nch);
         for (int32_t c = 0; c < nch; ++c) {
             const int32_t it = first + c;
@@ -742,7 +742,7 @@ __device__ __forceinline__ void sw_claim(const SwState& w, int32_t u) {
             }
             w.items[3 * it] = u;
             w.items[3 * it + 1] = b + c * kSwChunk;
-            w.items[3 * it + 2] = min(e, b + (c + 1) * kSwChunk);
+            w.items[3 * it + 2] = slot_piece_end(b, c, kSwChunk, e);
         }
     }
 }

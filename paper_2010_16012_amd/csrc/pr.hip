@@ -55,10 +55,11 @@ __device__ __forceinline__ float gather_row(const int32_t* __restrict__ idx, con
     float acc[U];
 #pragma unroll
     for (int k = 0; k < U; ++k) acc[k] = 0.f;
-    for (int32_t j0 = b + lane; j0 < e; j0 += U * G) {
-        int32_t jj[U], ii[U];
+    for (slot_t j0 = (slot_t)b + lane; j0 < (slot_t)e; j0 += U * G) {
+        slot_t jj[U];
+        int32_t ii[U];
 #pragma unroll
-        for (int k = 0; k < U; ++k) jj[k] = min(j0 + k * G, e - 1);
+        for (int k = 0; k < U; ++k) jj[k] = slot_at(j0, k * G, e);
 #pragma unroll
         for (int k = 0; k < U; ++k) ii[k] = idx[jj[k]];
         float v[U];
@@ -82,7 +83,7 @@ __device__ __forceinline__ float gather_row(const int32_t* __restrict__ idx, con
             for (int k = 0; k < U; ++k) v[k] *= wt[jj[k]];
         }
 #pragma unroll
-        for (int k = 0; k < U; ++k) acc[k] += (j0 + k * G < e) ? v[k] : 0.f;
+        for (int k = 0; k < U; ++k) acc[k] += slot_in(j0, k * G, e) ? v[k] : 0.f;
     }
 #pragma unroll
     for (int s = U / 2; s > 0; s >>= 1) {
@@ -576,10 +577,11 @@ Teleport uniform_teleport(int32_t n, float f) { return Teleport{teleport(n, f), 
 template <int G, int U, bool W>
 __device__ __forceinline__ void scatter_hot(const int32_t* __restrict__ idx, const float* __restrict__ wt, float cv,
                                             int32_t b, int32_t e, int lane, float* s_y, int32_t hot) {
-    for (int32_t j0 = b + lane; j0 < e; j0 += U * G) {
-        int32_t jj[U], ii[U];
+    for (slot_t j0 = (slot_t)b + lane; j0 < (slot_t)e; j0 += U * G) {
+        slot_t jj[U];
+        int32_t ii[U];
 #pragma unroll
-        for (int k = 0; k < U; ++k) jj[k] = min(j0 + k * G, e - 1);
+        for (int k = 0; k < U; ++k) jj[k] = slot_at(j0, k * G, e);
 #pragma unroll
         for (int k = 0; k < U; ++k) ii[k] = idx[jj[k]];
         float wv[U];
@@ -587,7 +589,7 @@ __device__ __forceinline__ void scatter_hot(const int32_t* __restrict__ idx, con
         for (int k = 0; k < U; ++k) wv[k] = W ? wt[jj[k]] : 1.f;
 #pragma unroll
         for (int k = 0; k < U; ++k)
-            if (j0 + k * G < e && ii[k] < hot) atomicAdd(&s_y[ii[k]], W ? cv * wv[k] : cv);
+            if (slot_in(j0, k * G, e) && ii[k] < hot) atomicAdd(&s_y[ii[k]], W ? cv * wv[k] : cv);
     }
 }
 

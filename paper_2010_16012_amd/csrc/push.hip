@@ -77,10 +77,11 @@ template <int G, bool W, bool HOT, int MODE>
 __device__ __forceinline__ void scatter_row(const PushArgs& a, const PushLds& s, float cv, int32_t b, int32_t e,
                                             int lane) {
     constexpr int U = unroll_for<G>();
-    for (int32_t j0 = b + lane; j0 < e; j0 += U * G) {
-        int32_t jj[U], uu[U];
+    for (slot_t j0 = (slot_t)b + lane; j0 < (slot_t)e; j0 += U * G) {
+        slot_t jj[U];
+        int32_t uu[U];
 #pragma unroll
-        for (int k = 0; k < U; ++k) jj[k] = min(j0 + k * G, e - 1);
+        for (int k = 0; k < U; ++k) jj[k] = slot_at(j0, k * G, e);
 #pragma unroll
         for (int k = 0; k < U; ++k) uu[k] = a.idx[jj[k]];
         float val[U];
@@ -88,7 +89,7 @@ __device__ __forceinline__ void scatter_row(const PushArgs& a, const PushLds& s,
         for (int k = 0; k < U; ++k) val[k] = (W && MODE != kPushCount) ? cv * a.wt[jj[k]] : cv;
 #pragma unroll
         for (int k = 0; k < U; ++k)
-            if (j0 + k * G < e) push_to<HOT, MODE>(a, s, uu[k], val[k]);
+            if (slot_in(j0, k * G, e)) push_to<HOT, MODE>(a, s, uu[k], val[k]);
     }
 }
 

@@ -152,16 +152,16 @@ __device__ __forceinline__ void tc_stream(const int32_t* idx, TcEdge& ed, int32_
     constexpr int U = kTcLoads;
     int32_t cnt = 0, back = -1;
     const int32_t v = ed.v;
-    for (int32_t j0 = b + gl; j0 < e; j0 += U * kTcGroup) {
+    const int32_t* p = idx + b + gl;  // `left` slots from here to the row's end
+    for (int32_t left = e - b - gl; left > 0; left -= U * kTcGroup, p += U * kTcGroup) {
         int32_t x[U];
 #pragma unroll
-        for (int k = 0; k < U; ++k) x[k] = idx[min(j0 + k * kTcGroup, e - 1)];
+        for (int k = 0; k < U; ++k) x[k] = p[min(k * kTcGroup, left - 1)];
 #pragma unroll
         for (int k = 0; k < U; ++k) {
-            const int32_t j = j0 + k * kTcGroup;
-            if (j < e) {
+            if (k * kTcGroup < left) {
                 cnt += hit(x[k]);
-                if (x[k] == v) back = j;
+                if (x[k] == v) back = e - left + k * kTcGroup;
             }
         }
     }
@@ -254,8 +254,8 @@ __global__ __launch_bounds__(64 * kTcMaxWaves) void k_tc_count(TcArgs a) {
             const int32_t k0 = s_run[r], k1 = s_run[r + 1];
             const int32_t ov = s_edge[s_list[k0]].v;
             const int32_t rb = a.off[ov], re = a.off[ov + 1];
-            for (int32_t lo = 0; lo < a.n; lo += a.window) {
-                for (int32_t j = rb + tid; j < re; j += blockDim.x) {
+            for (uint32_t lo = 0; lo < (uint32_t)a.n; lo += a.window) {
+                for (slot_t j = (slot_t)rb + tid; j < (slot_t)re; j += blockDim.x) {
                     const uint32_t p = (uint32_t)(a.idx[j] - lo);
                     if (p < (uint32_t)a.window) atomicOr(&bits[p >> 5], 1u << (p & 31));
                 }
@@ -264,8 +264,8 @@ __global__ __launch_bounds__(64 * kTcMaxWaves) void k_tc_count(TcArgs a) {
                     TcEdge& ed = s_edge[s_list[k]];
                     int32_t b = a.off[ed.w], e = a.off[ed.w + 1];
                     if (a.n > a.window) {
-                        b = tc_lower(a.idx, b, e, lo);
-                        e = (a.n - lo > a.window) ? tc_lower(a.idx, b, e, lo + a.window) : e;
+                        b = tc_lower(a.idx, b, e, (int32_t)lo);
+                        e = (a.n - lo > (uint32_t)a.window) ? tc_lower(a.idx, b, e, (int32_t)lo + a.window) : e;
                     }
                     tc_stream(a.idx, ed, b, e, gl, [&](int32_t x) -> int32_t {
                         const uint32_t p = min((uint32_t)(x - lo), (uint32_t)a.window - 1u);
@@ -273,7 +273,7 @@ __global__ __launch_bounds__(64 * kTcMaxWaves) void k_tc_count(TcArgs a) {
                     });
                 }
                 __syncthreads();
-                for (int32_t j = rb + tid; j < re; j += blockDim.x) {
+                for (slot_t j = (slot_t)rb + tid; j < (slot_t)re; j += blockDim.x) {
                     const uint32_t p = (uint32_t)(a.idx[j] - lo);
                     if (p < (uint32_t)a.window) bits[p >> 5] = 0u;
                 }
@@ -491,7 +491,7 @@ PP_EXPORT pp_status pp_tc_run(pp_graph g, pp_dir dir, int64_t* tc, void* ws, siz
     a.tail = reinterpret_cast<int64_t*>(w + L.tail);
     a.flag = reinterpret_cast<int32_t*>(w + L.flag);
     a.cnt = reinterpret_cast<int32_t*>(w + L.cnt);
-    a.window = std::min((a.n + 63) / 64 * 64, kTcWindow);
+    a.window = (int32_t)std::min<int64_t>(((int64_t)a.n + 63) / 64 * 64, kTcWindow);
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int32_t vb = std::max(1, std::min(ceil_div(a.n, kBlock), 4096));
     const int32_t zb = std::max(1, std::min(ceil_div(std::max<int64_t>(a.n, a.nnz), kBlock), 4096));
