@@ -7,12 +7,12 @@
 //
 // |N(v) ∩ N(w)| does not depend on the order of v and w, so k_tc_count forms it
 // once per pair, at the endpoint with the longer row (the owner, ties by id):
-// the owner's row is a bitmap in LDS and the shorter row is streamed against
-// it, sum over the edges of min(d(v), d(w)) tests in all.  The stream of N(w)
+// the owner's row is a bitmap or a list in LDS and the shorter row is streamed
+// against it, sum over the edges of min(d(v), d(w)) tests in all.  The stream of N(w)
 // meets the owner itself where the reverse edge is stored, so the count is
 // written to both slots without a search.  k_tc_slices then sums the counts of
-// each row's slots; a slot without one (a directed edge to a longer row that
-// has no edge back) is intersected there.  What bounds it: LDS bit tests and
+// each row's slots; a slot without one (two short rows, a directed edge to a longer
+// row that has no edge back) is intersected there.  What bounds it: LDS bit tests and
 // the barriers between a slice's rows.  R-MAT 16 (163M tests): 0.35 ms a call,
 // against 20.3 ms with a wavefront per 256 edges that searched or merged both
 // directions of every pair in global memory.
@@ -35,8 +35,11 @@ constexpr int32_t kTcSlice = 256;  // edges per slice
 constexpr int32_t kTcLight = 16;   // lane-serial intersections up to this shorter row
 // Owner rows up to kTcMid entries are searched in LDS by one wavefront (their
 // tests are under 1% of the total on skewed graphs, and a bitmap costs the
-// workgroup three barriers); longer ones become a bitmap.
+// workgroup three barriers); longer ones become a bitmap, where bitmaps are large
+// (kTcWide bytes) only those of more than kTcMidWide.
 constexpr int32_t kTcMid = 64;
+constexpr int32_t kTcMidWide = 512;
+constexpr size_t kTcWide = 24576, kTcWidest = 65536;
 // Lanes that stream one shorter row, and loads each keeps in flight.  R-MAT 16
 // / 18, a call: 16 x 4 0.446 / 2.50 ms, 16 x 8 0.389 / 2.04, 32 x 4 0.380 /
 // 2.20, 32 x 8 0.351 / 1.86, 64 x 4 0.402 / 2.22, 8 x 4 0.523 / 3.06.
@@ -51,10 +54,11 @@ struct TcArgs {
     int32_t slices;
     const int32_t* off;  // caller's CSR (rows sorted ascending)
     const int32_t* idx;
+    const int32_t* row;  // the row of every slot, where registration left it (nullable)
     int64_t* tc;         // [n] output (push: accumulator)
-    int64_t* head;       // [slices] first segment of each slice (pull)
+    int64_t* head;       // [slices] first segment of each slice (pull); before, edges of bitmap rows
     int64_t* tail;       // [slices] last segment of each slice (pull)
-    int32_t* cnt;        // [nnz] |N(v) ∩ N(w)| of every slot; -1: not formed
+    int32_t* cnt;        // [nnz] |N(v) ∩ N(w)| of every slot; -1: not formed (NULL: none is)
     int32_t window;      // vertices per bitmap window
     int32_t* flag;       // bit 0: a row is not strictly ascending
 };
@@ -181,37 +185,54 @@ __device__ __forceinline__ int32_t tc_lower(const int32_t* idx, int32_t b, int32
     return b;
 }
 
-// Slots of the slice whose row owns the pair.  The slice's owned edges are
-// compacted in slot order, rows of more than kTcMid entries first to s_list
-// from the front, the others from the back, so a row's edges are consecutive.
-__global__ __launch_bounds__(64 * kTcMaxWaves) void k_tc_count(TcArgs a) {
-    extern __shared__ uint32_t bits[];  // window / 32 words
+// The pairs of a slice whose longer row has more than kTcLight entries, counted at
+// the slot of the owner.  The slice's owned edges are compacted in slot order, rows
+// with a bitmap first to s_list from the front, the others from the back, so a
+// row's edges are consecutive.
+//
+// BITS: rows of more than CAP entries, by bitmap.  SEARCH: the others, searched in
+// LDS.  Where the bitmap is small one launch does both.  Where it would leave a
+// compute unit one workgroup or two, the searched rows have a launch of their own,
+// of small workgroups and no bitmap, which also notes (in head) the slices that
+// have rows for a bitmap; most sparse graphs have none.  One launch with a bitmap
+// for every graph, against this: 1000 x 1031 grid 504 -> 136 us, ER n = 1M of degree
+// 16 6.8 -> 1.9 ms, of 48 28.8 -> 6.7, n = 2.2M of 80 189 -> 36, a grid with a hub of
+// 5,000 504 -> 156 us, R-MAT 20 (edge factor 8) 6.2 -> 5.9 ms.
+template <int CAP, bool SEARCH, bool BITS>
+__global__ __launch_bounds__(64 * (BITS ? kTcMaxWaves : 4)) void k_tc_count(TcArgs a) {
+    constexpr int kWavesMax = BITS ? kTcMaxWaves : 4;
+    extern __shared__ uint32_t bits[];  // BITS: window / 32 words
     __shared__ TcEdge s_edge[kTcSlice];
-    __shared__ int16_t s_list[kTcSlice];     // owned edges, big rows then middle rows
+    __shared__ int16_t s_list[kTcSlice];     // owned edges, rows with a bitmap, then the searched ones
     __shared__ int16_t s_run[kTcSlice + 1];  // first list entry of every row
     __shared__ int32_t s_wbig[kTcSlice / kWave], s_wmid[kTcSlice / kWave], s_wrun[kTcSlice / kWave];
-    __shared__ int32_t s_row[kTcMaxWaves][kTcMid];
+    __shared__ int32_t s_row[SEARCH ? kWavesMax : 1][SEARCH ? CAP : 1];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave, nw = blockDim.x / kWave;
     const int grp = tid / kTcGroup, ngrp = blockDim.x / kTcGroup, gl = tid & (kTcGroup - 1);
     const uint64_t below = (1ull << lane) - 1ull;
-    for (int32_t i = tid; i < a.window / 32; i += blockDim.x) bits[i] = 0u;
+    if (BITS)
+        for (int32_t i = tid; i < a.window / 32; i += blockDim.x) bits[i] = 0u;
     for (int32_t s = blockIdx.x; s < a.slices; s += gridDim.x) {
+        if (!SEARCH && a.head[s] == 0) continue;
         const int64_t e0 = (int64_t)s * kTcSlice;
         const int32_t ne = (int32_t)min((int64_t)kTcSlice, a.nnz - e0);
         __syncthreads();  // the lists of the previous slice are done with
         bool big = false, mid = false;
-        int32_t v = -1, w = -1;
-        if (tid < ne) {
-            v = row_of(a.off, 0, a.n, e0 + tid);
-            w = a.idx[e0 + tid];
-            const int32_t rb = a.off[v], dv = a.off[v + 1] - rb, wb = a.off[w], dw = a.off[w + 1] - wb;
-            if (max(dv, dw) <= kTcLight) {
-                a.cnt[e0 + tid] = (int32_t)isect_lane(a.idx, rb, rb + dv, wb, wb + dw);
-            } else if (tc_owned(dv, v, dw, w)) {
-                big = dv > kTcMid;
-                mid = !big;
+        if (tid < kTcSlice) {
+            if (tid < ne) {
+                const int32_t v = a.row ? a.row[e0 + tid] : row_of(a.off, 0, a.n, e0 + tid);
+                const int32_t w = a.idx[e0 + tid];
+                const int32_t dv = a.off[v + 1] - a.off[v], dw = a.off[w + 1] - a.off[w];
+                if (dv > kTcLight && tc_owned(dv, v, dw, w)) {
+                    big = dv > CAP;
+                    mid = SEARCH && !big;
+                } else if (SEARCH && BITS && max(dv, dw) <= kTcLight) {
+                    // (few on the dense graphs of this form; k_tc_slices, which
+                    // takes them otherwise, has a wavefront a slice)
+                    a.cnt[e0 + tid] = (int32_t)isect_lane(a.idx, a.off[v], a.off[v + 1], a.off[w], a.off[w + 1]);
+                }
+                s_edge[tid] = TcEdge{v, w, 0, -1};
             }
-            s_edge[tid] = TcEdge{v, w, 0, -1};
         }
         const uint64_t mb = __ballot(big), mm = __ballot(mid);
         if (tid < kTcSlice && lane == 0) {
@@ -229,9 +250,15 @@ __global__ __launch_bounds__(64 * kTcMaxWaves) void k_tc_count(TcArgs a) {
             nbig += s_wbig[i];
             nmid += s_wmid[i];
         }
+        if (!BITS) {
+            if (tid == 0) a.head[s] = nbig;
+            nbig = 0;
+            big = false;
+        }
+        const int32_t nl = nbig + nmid;
+        if (nl == 0) continue;
         if (big) s_list[pb + __popcll(mb & below)] = (int16_t)tid;
         if (mid) s_list[nbig + pm + __popcll(mm & below)] = (int16_t)tid;
-        const int32_t nl = nbig + nmid;
         __syncthreads();
         // row starts in the list
         bool start = false;
@@ -250,57 +277,68 @@ __global__ __launch_bounds__(64 * kTcMaxWaves) void k_tc_count(TcArgs a) {
         __syncthreads();
         // rows with a bitmap: the workgroup takes one after another
         int32_t r = 0;
-        for (; r < nrun && s_run[r] < nbig; ++r) {
-            const int32_t k0 = s_run[r], k1 = s_run[r + 1];
-            const int32_t ov = s_edge[s_list[k0]].v;
-            const int32_t rb = a.off[ov], re = a.off[ov + 1];
-            for (uint32_t lo = 0; lo < (uint32_t)a.n; lo += a.window) {
-                for (slot_t j = (slot_t)rb + tid; j < (slot_t)re; j += blockDim.x) {
-                    const uint32_t p = (uint32_t)(a.idx[j] - lo);
-                    if (p < (uint32_t)a.window) atomicOr(&bits[p >> 5], 1u << (p & 31));
-                }
-                __syncthreads();
-                for (int32_t k = k0 + grp; k < k1; k += ngrp) {
-                    TcEdge& ed = s_edge[s_list[k]];
-                    int32_t b = a.off[ed.w], e = a.off[ed.w + 1];
-                    if (a.n > a.window) {
-                        b = tc_lower(a.idx, b, e, (int32_t)lo);
-                        e = (a.n - lo > (uint32_t)a.window) ? tc_lower(a.idx, b, e, (int32_t)lo + a.window) : e;
+        if constexpr (BITS) {
+            for (; r < nrun && s_run[r] < nbig; ++r) {
+                const int32_t k0 = s_run[r], k1 = s_run[r + 1];
+                const int32_t ov = s_edge[s_list[k0]].v;
+                const int32_t rb = a.off[ov], re = a.off[ov + 1];
+                for (uint32_t lo = 0; lo < (uint32_t)a.n; lo += a.window) {
+                    for (slot_t j = (slot_t)rb + tid; j < (slot_t)re; j += blockDim.x) {
+                        const uint32_t p = (uint32_t)(a.idx[j] - lo);
+                        if (p < (uint32_t)a.window) atomicOr(&bits[p >> 5], 1u << (p & 31));
                     }
-                    tc_stream(a.idx, ed, b, e, gl, [&](int32_t x) -> int32_t {
-                        const uint32_t p = min((uint32_t)(x - lo), (uint32_t)a.window - 1u);
-                        return (bits[p >> 5] >> (p & 31)) & 1u;
-                    });
+                    __syncthreads();
+                    for (int32_t k = k0 + grp; k < k1; k += ngrp) {
+                        TcEdge& ed = s_edge[s_list[k]];
+                        int32_t b = a.off[ed.w], e = a.off[ed.w + 1];
+                        if (a.n > a.window) {
+                            b = tc_lower(a.idx, b, e, (int32_t)lo);
+                            e = (a.n - lo > (uint32_t)a.window) ? tc_lower(a.idx, b, e, (int32_t)lo + a.window) : e;
+                        }
+                        tc_stream(a.idx, ed, b, e, gl, [&](int32_t x) -> int32_t {
+                            const uint32_t p = min((uint32_t)(x - lo), (uint32_t)a.window - 1u);
+                            return (bits[p >> 5] >> (p & 31)) & 1u;
+                        });
+                    }
+                    __syncthreads();
+                    for (slot_t j = (slot_t)rb + tid; j < (slot_t)re; j += blockDim.x) {
+                        const uint32_t p = (uint32_t)(a.idx[j] - lo);
+                        if (p < (uint32_t)a.window) bits[p >> 5] = 0u;
+                    }
+                    __syncthreads();
                 }
-                __syncthreads();
-                for (slot_t j = (slot_t)rb + tid; j < (slot_t)re; j += blockDim.x) {
-                    const uint32_t p = (uint32_t)(a.idx[j] - lo);
-                    if (p < (uint32_t)a.window) bits[p >> 5] = 0u;
-                }
-                __syncthreads();
             }
         }
         // the other rows: one wavefront each, the row searched in LDS
-        for (r += wv; r < nrun; r += nw) {
-            const int32_t k0 = s_run[r], k1 = s_run[r + 1];
-            const int32_t ov = s_edge[s_list[k0]].v;
-            const int32_t rb = a.off[ov], d = a.off[ov + 1] - rb;  // d <= kTcMid
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            s_row[wv][lane] = lane < d ? a.idx[rb + lane] : INT32_MAX;
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            const int32_t* row = s_row[wv];
-            for (int32_t k = k0 + lane / kTcGroup; k < k1; k += kWave / kTcGroup) {
-                TcEdge& ed = s_edge[s_list[k]];
-                tc_stream(a.idx, ed, a.off[ed.w], a.off[ed.w + 1], gl, [&](int32_t x) -> int32_t {
-                    int32_t p = 0;  // largest p with row[p] <= x, or 0
+        if constexpr (SEARCH) {
+            for (r += wv; r < nrun; r += nw) {
+                const int32_t k0 = s_run[r], k1 = s_run[r + 1];
+                const int32_t ov = s_edge[s_list[k0]].v;
+                const int32_t rb = a.off[ov], d = a.off[ov + 1] - rb;  // d <= CAP
+                int32_t size = kWave;  // what is searched: the row, filled up to a power of two
+                while (size < d) size <<= 1;
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                for (int32_t i = lane; i < size; i += kWave) s_row[wv][i] = i < d ? a.idx[rb + i] : INT32_MAX;
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                const int32_t* row = s_row[wv];
+                for (int32_t k = k0 + lane / kTcGroup; k < k1; k += kWave / kTcGroup) {
+                    TcEdge& ed = s_edge[s_list[k]];
+                    tc_stream(a.idx, ed, a.off[ed.w], a.off[ed.w + 1], gl, [&](int32_t x) -> int32_t {
+                        int32_t p = 0;  // largest p with row[p] <= x, or 0
+                        if (CAP == kWave) {
 #pragma unroll
-                    for (int st = kTcMid / 2; st > 0; st >>= 1)
-                        if (row[p + st] <= x) p += st;
-                    return row[p] == x;
-                });
+                            for (int st = kWave / 2; st > 0; st >>= 1)
+                                if (row[p + st] <= x) p += st;
+                        } else {
+                            for (int32_t st = size >> 1; st > 0; st >>= 1)
+                                if (row[p + st] <= x) p += st;
+                        }
+                        return row[p] == x;
+                    });
+                }
+                __builtin_amdgcn_wave_barrier();
             }
-            __builtin_amdgcn_wave_barrier();
         }
         __syncthreads();
         if (tid < nl) {
@@ -312,8 +350,9 @@ __global__ __launch_bounds__(64 * kTcMaxWaves) void k_tc_count(TcArgs a) {
     }
 }
 
+// (eight wavefronts a SIMD: what it waits for is gathers)
 template <bool PUSH>
-__global__ __launch_bounds__(kBlock) void k_tc_slices(TcArgs a) {
+__global__ __launch_bounds__(kBlock, 8) void k_tc_slices(TcArgs a) {
     const int lane = threadIdx.x & (kWave - 1);
     const int32_t gwave = blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
     const int32_t nwaves = gridDim.x * (kBlock / kWave);
@@ -322,10 +361,12 @@ __global__ __launch_bounds__(kBlock) void k_tc_slices(TcArgs a) {
         const int64_t e1 = min(e0 + kTcSlice, a.nnz);
         // rows holding the first and last edge of the slice bound every search
         int32_t v0 = 0, v1 = 0;
-        if (lane == 0) v0 = row_of(a.off, 0, a.n, e0);
-        if (lane == 1) v1 = row_of(a.off, 0, a.n, e1 - 1);
-        v0 = __shfl(v0, 0);
-        v1 = __shfl(v1, 1);
+        if (!a.row) {
+            if (lane == 0) v0 = row_of(a.off, 0, a.n, e0);
+            if (lane == 1) v1 = row_of(a.off, 0, a.n, e1 - 1);
+            v0 = __shfl(v0, 0);
+            v1 = __shfl(v1, 1);
+        }
         int64_t carry = 0;  // running sum of the open segment (row carry_v)
         int32_t carry_v = -1;
         for (int64_t jb = e0; jb < e1; jb += kWave) {
@@ -335,13 +376,13 @@ __global__ __launch_bounds__(kBlock) void k_tc_slices(TcArgs a) {
             int64_t cnt = 0;
             bool heavy = false;
             if (live) {
-                v = row_of(a.off, v0, v1 + 1, j);
+                v = a.row ? __builtin_nontemporal_load(a.row + j) : row_of(a.off, v0, v1 + 1, j);
                 w = a.idx[j];
                 rb = a.off[v];
                 re = a.off[v + 1];
+                cnt = a.cnt ? a.cnt[j] : -1;
                 if (j + 1 < re && a.idx[j + 1] <= w) atomicOr(a.flag, 1);
-                cnt = (w == v) ? re - rb : a.cnt[j];
-                if (cnt < 0) {  // a one-way edge into a longer row
+                if (cnt < 0) {  // two short rows, a self-loop, or a one-way edge into a longer row
                     const int32_t wb = a.off[w], we = a.off[w + 1];
                     heavy = min(re - rb, we - wb) > kTcLight;
                     if (!heavy) cnt = isect_lane(a.idx, rb, re, wb, we);
@@ -428,7 +469,7 @@ __global__ __launch_bounds__(kBlock) void k_tc_fix(TcArgs a) {
 __global__ void k_tc_zero(TcArgs a) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t v = t; v < a.n; v += stride) a.tc[v] = 0;
-    for (int64_t j = t; j < a.nnz; j += stride) a.cnt[j] = -1;
+    for (int64_t j = t; a.cnt && j < a.nnz; j += stride) a.cnt[j] = -1;
     if (blockIdx.x == 0 && threadIdx.x == 0) *a.flag = 0;
 }
 
@@ -490,7 +531,15 @@ PP_EXPORT pp_status pp_tc_run(pp_graph g, pp_dir dir, int64_t* tc, void* ws, siz
     a.head = reinterpret_cast<int64_t*>(w + L.head);
     a.tail = reinterpret_cast<int64_t*>(w + L.tail);
     a.flag = reinterpret_cast<int32_t*>(w + L.flag);
-    a.cnt = reinterpret_cast<int32_t*>(w + L.cnt);
+    // no counts beforehand: rows of at most kTcLight entries, or hardly longer ones
+    // in a sparse graph, where looking for the pairs costs more than they do (ER
+    // n = 2M of degree 4: 750 us looked for, 570 without)
+    const int32_t longest = g->max_out_deg;
+    const bool count = longest > kTcLight && !(longest <= kTcMid && a.nnz < 8 * (int64_t)a.n);
+    a.cnt = count ? reinterpret_cast<int32_t*>(w + L.cnt) : nullptr;
+    // (k_tc_slices alone is as well off with its bounded search: grids 25% faster by
+    // the list, sparse ER 10% slower)
+    a.row = count && !g->relabelled && g->d.aliased ? g->d.csc_row : nullptr;
     a.window = (int32_t)std::min<int64_t>(((int64_t)a.n + 63) / 64 * 64, kTcWindow);
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int32_t vb = std::max(1, std::min(ceil_div(a.n, kBlock), 4096));
@@ -498,10 +547,28 @@ PP_EXPORT pp_status pp_tc_run(pp_graph g, pp_dir dir, int64_t* tc, void* ws, siz
     hipLaunchKernelGGL(k_tc_zero, dim3(zb), dim3(kBlock), 0, st, a);
     if (a.slices > 0) {
         const size_t lds = (size_t)a.window / 8;
-        allow_dynamic_lds(reinterpret_cast<const void*>(&k_tc_count), lds);
-        // a workgroup clears its bitmap once: few workgroups where that is long
-        const int32_t wgs = g->num_cu * 16 * (1024 / tc_threads(lds));
-        hipLaunchKernelGGL(k_tc_count, dim3(std::min(a.slices, wgs)), dim3(tc_threads(lds)), lds, st, a);
+        // (a bitmap of kTcWidest bytes leaves a compute unit two workgroups, which
+        // still is the better form where most pairs need one: R-MAT 18 1.7 ms, 2.3 in
+        // two launches; ER n = 300,000 of degree 40 needs none: 2.6 -> 1.6 ms)
+        auto search = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(std::min(a.slices, g->num_cu * 64)), dim3(4 * kWave), 0, st, a);
+        };
+        auto with_bits = [&](auto kern) {
+            allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
+            // a workgroup clears its bitmap once: few workgroups where that is long
+            const int32_t wgs = g->num_cu * 16 * (1024 / tc_threads(lds));
+            hipLaunchKernelGGL(kern, dim3(std::min(a.slices, wgs)), dim3(tc_threads(lds)), lds, st, a);
+        };
+        if (count && longest <= kTcMid) {
+            search(&k_tc_count<kTcMid, true, false>);
+        } else if (!count) {
+            // k_tc_slices alone
+        } else if (lds <= kTcWide || (lds <= kTcWidest && longest > kTcMidWide && a.nnz >= 8 * (int64_t)a.n)) {
+            with_bits(&k_tc_count<kTcMid, true, true>);
+        } else {
+            search(&k_tc_count<kTcMidWide, true, false>);
+            if (longest > kTcMidWide) with_bits(&k_tc_count<kTcMidWide, false, true>);
+        }
         const int32_t blocks = std::min(ceil_div(a.slices, kBlock / kWave), g->num_cu * 8);
         if (dir == PP_PUSH) hipLaunchKernelGGL(k_tc_slices<true>, dim3(blocks), dim3(kBlock), 0, st, a);
         else hipLaunchKernelGGL(k_tc_slices<false>, dim3(blocks), dim3(kBlock), 0, st, a);

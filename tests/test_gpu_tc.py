@@ -127,3 +127,49 @@ def test_self_loops_count_as_before():
     push = [sum(len(rows[v] & rows[w]) for v in range(3) if w in rows[v]) // 2 for w in range(3)]
     assert _tc(host, pp.PP_PULL).tolist() == pull
     assert _tc(host, pp.PP_PUSH).tolist() == push
+
+
+@pytest.mark.parametrize("n,m", [(200_000, 0), (200_000, 900_000), (600_000, 0), (600_000, 3_000_000), (5_000, 0)])
+def test_owner_rows_searched_or_in_a_bitmap(n, m):
+    # blobs whose rows straddle the lengths at which a row's pairs are counted in the
+    # lane (16), by a search of the row (64, or 512 where a bitmap is large) and by
+    # bitmap, in sparse (m = 0) and denser graphs, whose forms differ
+    rng = np.random.default_rng(n + m)
+    at = np.sort(rng.choice(n, size=620, replace=False))
+    src, dst = [rng.integers(0, n, m)], [rng.integers(0, n, m)]
+    for size in (17, 64, 66, 512, 513, 515, 610):
+        ids = rng.choice(at, size=size, replace=False)
+        a, b = np.meshgrid(ids, ids)
+        keep = a < b
+        src.append(a[keep])
+        dst.append(b[keep])
+    _same(gg.from_edges(n, np.concatenate(src), np.concatenate(dst), True, name=f"blobs{n}_{m}"))
+
+
+@pytest.mark.parametrize("d", [2, 15, 17, 40, 64])
+def test_no_row_needs_a_bitmap(d):
+    # rows of at most 64 entries: summed without counts beforehand, or by searches alone
+    n = 30_000
+    k = np.arange(n)
+    ring = [(k + s) % n for s in range(1, d // 2 + 1)]
+    _same(gg.from_edges(n, np.tile(k, len(ring)), np.concatenate(ring), True, name=f"ring{d}"))
+
+
+def test_sparse_graphs_are_not_charged_for_bitmaps():
+    # a grid of a million vertices has no row for a bitmap: counting its triangles
+    # (134 us) is less work than 20 PageRank steps (350 us), and was more (504 us)
+    # when every slice was looked through beside a bitmap of 128 KB
+    g = pp.Graph(gg.grid(1000, 1031, 0.05, seed=1), relabel=False)
+
+    def best(fn):
+        times = []
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            fn()
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times)
+
+    assert best(lambda: pp.triangles(g, pp.PP_PULL)) < best(lambda: pp.pagerank(g, 20, 0.85, pp.PP_PULL))
