@@ -401,7 +401,7 @@ size_t pp_multi_workspace_bytes(int32_t num_graphs, int64_t total_vertices);
  * (alpha, beta as in pp_bfs_run).  One workgroup holds one graph's state in
  * LDS: pull gathers and push updates are LDS operations and the barrier
  * between sweeps is a workgroup barrier.  Where a graph has more than 49,152
- * edges (and ws holds pp_multi_workspace_bytes), each PageRank step is a launch
+ * edges and would keep one workgroup longer than all of them need together (and ws holds pp_multi_workspace_bytes), each PageRank step is a launch
  * that shares the in-rows of all graphs among the compute units (x is used
  * between the steps); PP_PUSH does so only after a device pass has found that
  * in_off/in_idx hold the transpose of every graph, and otherwise never walks

@@ -13,8 +13,8 @@
 // One compute unit sweeps about 3.5 edges a nanosecond, so a batch with large
 // graphs waited for the largest alone (a scale-14 R-MAT graph: 134 us a sweep,
 // 2.7 of the 3.1 ms of a 128-graph batch, most of the chip idle).  Where a graph
-// has more than kStepEdges edges the PageRank steps therefore run as one launch
-// each (k_multi_step), the rows of all graphs shared among one workgroup per
+// has more than kStepEdges edges and is more than its share (steps_pay) the
+// PageRank steps therefore run as one launch each (k_multi_step), the rows of all graphs shared among one workgroup per
 // compute unit: 40 us a step there, 1.07 ms in all.
 #include <hip/hip_runtime.h>
 
@@ -277,6 +277,24 @@ constexpr int32_t kStepEdges = 49152;
 constexpr int32_t kStepGraphCost = 8192;
 constexpr int32_t kStepRowCost = 16;
 
+// Whether shared steps pay (cost: of every graph, largest first, as k_multi_pieces
+// divides it).  In the one launch a sweep ends with the workgroup of the largest
+// graph, or with the compute unit that takes most graphs: at least k graphs of the
+// (256 (k - 1) + 1)-th largest's cost.  A shared step is kStepLaunch of launch and
+// then its 256th of everything, a quarter slower than one workgroup that keeps its
+// graph in LDS.  One graph of 2^s vertices among others, 20 steps pulled, one
+// launch / shared: 10,000 of 2^5, s = 12 / 13 / 14 1.70 / 1.84 / 2.94 ms against 3.0;
+// 2,000 of 2^9, s = 12 / 13 0.85 / 1.51 against 1.32; 300 of 2^12 1.40 / 1.22; 600 of
+// 2^13 4.26 / 4.73, pushed (where the one launch takes a quarter longer) 5.52 / 4.96.
+constexpr int64_t kStepLaunch = 63000;
+template <typename Cost>
+static bool steps_pay(int32_t count, int64_t total, bool push, Cost cost) {
+    int64_t sweep = 0;
+    for (int32_t i = 0, k = 1; i < count; i += kStepGroups, ++k) sweep = std::max(sweep, k * cost(i));
+    const int64_t quota = total / kStepGroups;
+    return sweep + (push ? sweep / 4 : 0) > kStepLaunch + quota + quota / 4;
+}
+
 // First row before which the graph, rows and slots cost t or more.
 __global__ void k_multi_pieces(const MultiEntry* __restrict__ table, const int32_t* __restrict__ in_off, int32_t count,
                                MultiPiece* __restrict__ pc, const int32_t* __restrict__ err,
@@ -353,7 +371,7 @@ __device__ __forceinline__ uint64_t sum_marks(const int32_t* off, const uint16_t
 // Whether the in-arrays hold the transpose of every graph: *marks ends at zero
 // where they do.  Steps that sum what a push sends where it arrives need it; a
 // caller who pushes directed graphs may have no in-arrays and pass the out-arrays
-// twice.  128 R-MAT graphs of scales 8-14: 1,058 -> 1,114 us a pushed call, 15 of it the host's look.
+// twice.  128 R-MAT graphs of scales 8-14: 1,058 -> 1,114 us a pushed call.
 __global__ __launch_bounds__(kMultiBlock) void k_multi_match(const MultiEntry* __restrict__ table,
                                                              const MultiPiece* __restrict__ pieces,
                                                              const int32_t* __restrict__ wg,
@@ -1006,15 +1024,16 @@ static pp_status multi_run(int32_t num_graphs, const int32_t* graph_n, const int
     const Tuning& t = tuning();
     a.big = t.multi_big;
     a.mid = t.multi_mid;
-    // a batch with large graphs: the steps shared among all workgroups first,
+    // where a few graphs are large: the steps shared among all workgroups first,
     // then (with no steps left to it) the launch below for the searches.
     // (The costs of a graph of 2^30 edges or more do not fit a piece.)
     std::vector<MultiPiece> pieces;
     std::vector<int32_t> wg;
-    if (pr_iters > 0 && dev[0].nnz > kStepEdges && dev[0].nnz < (1 << 30) && ws_bytes >= ML.total) {
-        auto cost_of = [&](int32_t i) { return kStepGraphCost + dev[i].nnz + kStepRowCost * (int64_t)dev[i].n; };
-        int64_t total = 0, run = 0;
-        for (int32_t i = 0; i < num_graphs; ++i) total += cost_of(i);
+    auto cost_of = [&](int32_t i) { return kStepGraphCost + dev[i].nnz + kStepRowCost * (int64_t)dev[i].n; };
+    const int64_t total = kStepGraphCost * (int64_t)num_graphs + total_nnz + kStepRowCost * vb;
+    if (pr_iters > 0 && dev[0].nnz > kStepEdges && dev[0].nnz < (1 << 30) && ws_bytes >= ML.total &&
+        steps_pay(num_graphs, total, pr_dir == PP_PUSH, cost_of)) {
+        int64_t run = 0;
         const int64_t quota = std::max<int64_t>(1, (total + kStepGroups - 1) / kStepGroups);
         wg.push_back(0);
         for (int32_t i = 0; i < num_graphs; ++i) {

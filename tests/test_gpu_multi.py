@@ -234,3 +234,31 @@ def test_pushing_reads_the_out_arrays_alone():
         for h, xi in zip(gs, mg.split(x.cpu().numpy())):
             want = oracle.pagerank(h.off, h.idx, F, iters)
             assert np.abs(xi.astype(np.float64) - want).sum() <= PR_L1_TOL, (h.name, iters)
+
+
+def test_one_larger_graph_among_thousands():
+    # thousands of graphs keep every compute unit longer than one of 90,000 edges
+    # does: its presence must not cost the batch more than a third (it took twice as
+    # long when the steps were shared for the one graph's sake)
+    small = [gg.rmat(5, 16, seed=i) for i in range(6000)]
+    large = gg.rmat(12, 16, seed=1)
+    assert large.nnz > 49152
+
+    def best(mg, d):
+        times = []
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            mg.run(pr_iters=20, pr_dir=d, bfs_policy=-1)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times)
+
+    without, with_it = pp.MultiGraph(small), pp.MultiGraph(small + [large])
+    for d in (pp.PP_PULL, pp.PP_PUSH):
+        announce(f"multi: one larger among 6000, dir={d}")
+        assert best(with_it, d) < 4 / 3 * best(without, d)
+    x = with_it.run(pr_iters=20, f=F, pr_dir=pp.PP_PULL, bfs_policy=-1)[0]
+    want = oracle.pagerank(large.off, large.idx, F, 20)
+    assert np.abs(x[-large.n:].cpu().numpy().astype(np.float64) - want).sum() <= PR_L1_TOL
