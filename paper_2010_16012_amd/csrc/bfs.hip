@@ -88,6 +88,7 @@ constexpr int32_t kSoloMax = 256;
 constexpr int32_t kDeepPages = kDeepCap / kPage;  // queue pages a workgroup hands its share back in
 constexpr int32_t kDeepMaxDeg = 16;               // longest out-row of the graphs it runs on
 constexpr int32_t kDeepOffer = 8;                 // levels of a batch between two launches of it (even)
+constexpr int32_t kDeepMinN = 32768;              // vertices from which more than one workgroup is offered frontiers
 
 struct BfsSlot {
     int32_t n;         // frontier size (accumulated by the level that builds it)
@@ -1937,6 +1938,10 @@ static bool deep_for(pp_graph g, int32_t policy) {
     return policy != PP_PULL && g->max_out_deg <= kDeepMaxDeg && g->tune.bfs_multi_n > 0 &&
            g->tune.bfs_multi_m > 0 && g->num_cu >= 2 * kDeepGroups;
 }
+// Are the cooperating workgroups offered the frontiers past what one takes?  On
+// few vertices such a frontier is most of the graph (ER n = 5,001 of degree 4: 124
+// us a switching run without, 131 with them).
+static bool deep_shared(pp_graph g) { return g->d.n >= kDeepMinN; }
 constexpr unsigned kDeepLds = 2 * kDeepCap * sizeof(DeepEntry);
 
 static size_t multi_lds(int32_t qcap) { return (size_t)(6 * qcap + 2) * 4; }
@@ -2014,22 +2019,24 @@ static pp_status bfs_graph(pp_graph g, BfsArgs a, int32_t policy, float alpha, f
     // workgroups; all return at once when the frontier is not one they take
     // on.  Where the latter run, a few bottom-up levels in between (the switch
     // rule) must not leave the rest of a batch to the level kernels: both are
-    // offered the frontier again every kDeepOffer levels.
+    // offered the frontier again every kDeepOffer levels, and after the last,
+    // which takes the narrow end of a search wherever its batch's levels fell (or
+    // the batch, sized by runs that were offered it earlier, would not suffice).
     int32_t qcap = 0, ecap = 0;
     multi_caps(g, policy, &qcap, &ecap);
     const bool deep = deep_for(g, policy);
     if (qcap > 0) allow_dynamic_lds(reinterpret_cast<const void*>(&k_bfs_multi), multi_lds(qcap));
     int32_t lvl = -1;
-    for (int32_t i = 0; i < batch && e == hipSuccess; ++i) {
-        if (i == 0 || (deep && i % kDeepOffer == 0)) {
+    for (int32_t i = 0; i <= batch && e == hipSuccess; ++i) {
+        if (i == 0 || (deep && (i % kDeepOffer == 0 || i == batch))) {
             if (deep) {
                 int32_t solo = std::min(kSoloMax, g->tune.bfs_multi_n);
                 void* dargs[] = {&a, &policy, &alpha, &beta, &solo};
                 void* iargs[] = {&a};
                 e = add(reinterpret_cast<const void*>(&k_bfs_deep<true>), dargs, 1, kDeepLds, kDeepBlock);
-                if (e == hipSuccess)
+                if (e == hipSuccess && deep_shared(g))
                     e = add(reinterpret_cast<const void*>(&k_bfs_deep_init), iargs, 1, 0, kWave);
-                if (e == hipSuccess)
+                if (e == hipSuccess && deep_shared(g))
                     e = add(reinterpret_cast<const void*>(&k_bfs_deep<false>), dargs, kDeepGroups, kDeepLds,
                             kDeepBlock);
             } else if (qcap > 0) {
@@ -2038,6 +2045,7 @@ static pp_status bfs_graph(pp_graph g, BfsArgs a, int32_t policy, float alpha, f
             }
             if (e != hipSuccess) break;
         }
+        if (i == batch) break;
         int32_t parity = i & 1;
         if (steps) {
             void* sargs[] = {&a, &parity, &policy, &alpha, &beta};

@@ -474,3 +474,34 @@ def test_bottom_up_long_rows_hit_at_any_entry(first):
     h = gg.from_edges(10 + n_top + n_rows, np.concatenate(src), np.concatenate(dst), False)
     h.ensure_transpose()
     _check(h, [0], policies=[pp.PP_PULL, pp.PP_SWITCH], fast=True)
+
+
+def test_many_searches_of_a_shallow_low_degree_graph():
+    # a batch of searches is sized by earlier runs, in which the cooperating
+    # workgroups were offered the narrow end of a search sooner: each search of the
+    # batch must find its end there too.  Where it did not, it was run again, and the
+    # batch took 1.8 times as long as its searches one by one.
+    h = gg.erdos_renyi(1_000_001, 1_000_001, seed=1)
+    roots = gg.pick_vertices(h, 4, seed=3)
+    r = pp.BfsRun(pp.Graph(h))
+
+    def best(fn):
+        times = []
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            fn()
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times)
+
+    for policy in (pp.PP_PUSH, pp.PP_SWITCH):
+        announce(f"bfs many shallow policy={policy}")
+        one_by_one = best(lambda: [r.run(int(v), policy) for v in roots])
+        assert best(lambda: r.run_many(roots, policy)) < 1.3 * one_by_one
+        stats = r.run_many(roots, policy)
+        for v, st in zip(roots, stats):
+            lv, _, levels = oracle.bfs(h.off, h.idx, int(v))
+            assert (st.levels, st.reached) == (levels, int((lv >= 0).sum()))
+        np.testing.assert_array_equal(r.level.cpu().numpy(), lv)
