@@ -192,7 +192,11 @@ pp_status pp_set_pull_slices(int32_t rows, int32_t width);
  * flight, so this pays for narrow frontiers (a path: 3.4 against 6.7 us per
  * level) and not for frontiers of thousands of vertices.  Defaults 256 and
  * 1024; max_frontier is capped by the LDS of a workgroup (6144 on gfx950);
- * 0 turns it off.  Takes effect at the next pp_graph_create. */
+ * 0 turns it off.  Where no out-row has more than 16 edges (grids, meshes) both
+ * are capped at 1024.  Such graphs of at least 65,536 vertices have both capped
+ * at 512, and their larger frontiers, up to 16,384 out-edges, run on 64
+ * cooperating workgroups in one launch before they go back to the level kernels;
+ * 0 turns these off too.  Takes effect at the next pp_graph_create. */
 pp_status pp_set_bfs_multi(int32_t max_frontier, int32_t max_edges);
 
 /* The tiled-pull plan of g: info[0..4) = R, width, S, tiles (R = 0: off). */

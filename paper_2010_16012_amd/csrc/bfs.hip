@@ -82,13 +82,14 @@ constexpr int32_t kChunkStage = 15360;
 constexpr int32_t kDeepGroups = 64;
 constexpr int32_t kDeepBlock = 256;
 constexpr int32_t kDeepCap = 512;
-// Frontier vertices one workgroup runs alone (100 x 4000 grid: 12.9 ms at 128
-// and 256, 14.1 at 64; 300 x 301: 2.0 at 256, 3.0 at 128).
-constexpr int32_t kSoloMax = 256;
+// The most frontier vertices and out-edges one workgroup runs alone; pp_set_bfs_multi
+// sets fewer (100 x 4000 grid: 12.9 ms at 128 and 256 vertices, 14.1 at 64; 300 x 301:
+// 2.0 at 256, 3.0 at 128).
+constexpr int32_t kSoloCap = 1024;
 constexpr int32_t kDeepPages = kDeepCap / kPage;  // queue pages a workgroup hands its share back in
 constexpr int32_t kDeepMaxDeg = 16;               // longest out-row of the graphs it runs on
 constexpr int32_t kDeepOffer = 8;                 // levels of a batch between two launches of it (even)
-constexpr int32_t kDeepMinN = 32768;              // vertices from which more than one workgroup is offered frontiers
+constexpr int32_t kDeepMinN = 65536;              // vertices from which more than one workgroup is offered frontiers
 
 struct BfsSlot {
     int32_t n;         // frontier size (accumulated by the level that builds it)
@@ -1639,6 +1640,7 @@ constexpr int kDeepCntShift = 28, kDeepFullShift = 48, kDeepArriveShift = 56;
 static_assert((int64_t)kDeepGroups * kDeepCap * kDeepMaxDeg < (1 << kDeepCntShift) &&
                   (int64_t)kDeepGroups * kDeepCap < (1 << (kDeepFullShift - kDeepCntShift)) && kDeepGroups < 256,
               "rendezvous word fields");
+static_assert(kSoloCap / kPage <= kDeepGroups * kDeepPages, "pages reserved for handing back");
 
 struct DeepEntry {
     int32_t v;    // vertex
@@ -1646,14 +1648,14 @@ struct DeepEntry {
     int32_t b, d; // out-row
 };
 
-// SOLO: one workgroup, frontiers of up to solo_max vertices (and as many
-// out-edges times kDeepMaxDeg): no rendezvous, and claims resolve in the local
-// L2.
+// SOLO: one workgroup, frontiers of up to solo_n vertices and solo_m out-edges (at
+// most kSoloCap): no rendezvous, and claims resolve in the local L2.
 template <bool SOLO>
 __global__ __launch_bounds__(kDeepBlock) void k_bfs_deep(BfsArgs a, int32_t policy, float alpha, float beta,
-                                                         int32_t solo_max) {
+                                                         int32_t solo_n, int32_t solo_m) {
     constexpr int32_t kGroups = SOLO ? 1 : kDeepGroups;
-    extern __shared__ __align__(16) DeepEntry s_set[];  // two frontiers of kDeepCap entries
+    constexpr int32_t kCap = SOLO ? kSoloCap : kDeepCap, kPages = kCap / kPage;
+    extern __shared__ __align__(16) DeepEntry s_set[];  // two frontiers of kCap entries
     __shared__ int32_t s_cnt[2];
     __shared__ int32_t s_deg;
     __shared__ uint64_t s_word;
@@ -1663,7 +1665,8 @@ __global__ __launch_bounds__(kDeepBlock) void k_bfs_deep(BfsArgs a, int32_t poli
     int32_t lvl = h->lv[0];
     const SlotView in = view(h->slot[lvl % 3]);
     // the same test in every workgroup: nothing it reads changes before all agree
-    if (h->finished || in.n <= 0 || (SOLO ? in.n > solo_max : in.m > kDeepGroups * kDeepCap / 2) || in.dir_prev != PP_PUSH ||
+    if (h->finished || in.n <= 0 || (SOLO ? in.n > solo_n || in.m > solo_m : in.m > kDeepGroups * kDeepCap / 2) ||
+        in.dir_prev != PP_PUSH ||
         in.n_prev > a.words ||
         !multi_push(policy, alpha, beta, a.n, lvl, in.n, in.m, in.mu_base, in.dir_prev, in.n_prev))
         return;
@@ -1682,13 +1685,13 @@ __global__ __launch_bounds__(kDeepBlock) void k_bfs_deep(BfsArgs a, int32_t poli
             if (lane == 0 && f > 0) base = atomicAdd(&s_cnt[0], f);
             base = __shfl(base, 0);
             for (int32_t i = lane; i < f; i += kWave)
-                if (base + i < kDeepCap) s_set[base + i].v = q[(size_t)p * kPage + i];
+                if (base + i < kCap) s_set[base + i].v = q[(size_t)p * kPage + i];
         }
     }
     __syncthreads();
     int32_t nloc = s_cnt[0];
     int32_t share = 0;  // out-edges: as many claims must fit
-    for (int32_t i = tid; i < min(nloc, kDeepCap); i += kDeepBlock) {
+    for (int32_t i = tid; i < min(nloc, kCap); i += kDeepBlock) {
         DeepEntry e = s_set[i];
         e.b = a.csr_off[e.v];
         e.d = a.csr_off[e.v + 1] - e.b;
@@ -1703,7 +1706,7 @@ __global__ __launch_bounds__(kDeepBlock) void k_bfs_deep(BfsArgs a, int32_t poli
     if (tid == 0) {
         int32_t go = 0;
         if (SOLO) {
-            go = nloc == in.n && s_deg <= kDeepCap ? 1 : 2;
+            go = nloc == in.n && s_deg <= kCap ? 1 : 2;
         } else if (nloc > kDeepCap || s_deg > kDeepCap) {
             atomicCAS(&ds->verdict, 0, 2);
         } else if (atomicAdd(&ds->arrived, 1) == kDeepGroups - 1) {
@@ -1753,7 +1756,7 @@ __global__ __launch_bounds__(kDeepBlock) void k_bfs_deep(BfsArgs a, int32_t poli
     __syncthreads();
     if (tid < nloc) mine = s_set[tid];
     look(mine, 0, ahead);
-    for (int32_t run = 0; nf != 0 && !full && run < kMultiLevels && (!SOLO || nf <= solo_max) &&
+    for (int32_t run = 0; nf != 0 && !full && run < kMultiLevels && (!SOLO || (nf <= solo_n && m <= solo_m)) &&
                           multi_push(policy, alpha, beta, a.n, lvl, nf, m, mu_base, PP_PUSH, n_prev);
          ++run) {
         if (blockIdx.x == 0 && tid == 0) {
@@ -1765,8 +1768,8 @@ __global__ __launch_bounds__(kDeepBlock) void k_bfs_deep(BfsArgs a, int32_t poli
         }
         reached += nf;
         edges += m;
-        const DeepEntry* A = s_set + cur * kDeepCap;
-        DeepEntry* B = s_set + (cur ^ 1) * kDeepCap;
+        const DeepEntry* A = s_set + cur * kCap;
+        DeepEntry* B = s_set + (cur ^ 1) * kCap;
         int32_t deg = 0;
         auto claim = [&](const DeepEntry& e, const Ahead& x) {
             uint32_t old[U];
@@ -1791,7 +1794,7 @@ __global__ __launch_bounds__(kDeepBlock) void k_bfs_deep(BfsArgs a, int32_t poli
                     a.parent[x.uid[k]] = e.uid;
                     deg += x.re[k] - x.rb[k];
                     const int32_t at = base + __popcll(bal & lanes_below(lane));
-                    if (at < kDeepCap) B[at] = DeepEntry{x.u[k], x.uid[k], x.rb[k], x.re[k] - x.rb[k]};
+                    if (at < kCap) B[at] = DeepEntry{x.u[k], x.uid[k], x.rb[k], x.re[k] - x.rb[k]};
                     else atomicOr(&h->overflow, 4);  // cannot happen: a share with more out-edges stops the run
                 }
             }
@@ -1817,7 +1820,7 @@ __global__ __launch_bounds__(kDeepBlock) void k_bfs_deep(BfsArgs a, int32_t poli
             s_deg = 0;
             asm volatile("" ::"v"((uint32_t)sunk), "v"((uint32_t)(sunk >> 32)));  // the word cleared last is clear
             // a share whose out-edges could all be claims must fit
-            s_word = (1ull << kDeepArriveShift) | ((unsigned long long)(d > kDeepCap ? 1 : 0) << kDeepFullShift) |
+            s_word = (1ull << kDeepArriveShift) | ((unsigned long long)(d > kCap ? 1 : 0) << kDeepFullShift) |
                      ((unsigned long long)c << kDeepCntShift) | (unsigned long long)d;
             if (!SOLO) atomicAdd(w, (unsigned long long)s_word);
         }
@@ -1852,16 +1855,16 @@ __global__ __launch_bounds__(kDeepBlock) void k_bfs_deep(BfsArgs a, int32_t poli
         cur ^= 1;
     }
     // hand frontier lvl back: queue pages reserved per workgroup, bitmap bits
-    const DeepEntry* A = s_set + cur * kDeepCap;
-    const int32_t page0 = a.static_pages + (int32_t)blockIdx.x * kDeepPages;
+    const DeepEntry* A = s_set + cur * kCap;
+    const int32_t page0 = a.static_pages + (int32_t)blockIdx.x * kPages;
     int32_t* q = a.queue[lvl & 1];
     int32_t* fill = a.fill[lvl & 1];
-    for (int32_t i = tid; i < min(nloc, kDeepCap); i += kDeepBlock) {
+    for (int32_t i = tid; i < min(nloc, kCap); i += kDeepBlock) {
         const int32_t v = A[i].v;
         q[(size_t)page0 * kPage + i] = v;
         atomicOr(reinterpret_cast<unsigned long long*>(&a.fb[lvl % 3][v >> 6]), 1ull << (v & 63));
     }
-    if (tid < kDeepPages) fill[page0 + tid] = max(0, min(kPage, nloc - tid * kPage));
+    if (tid < kPages) fill[page0 + tid] = max(0, min(kPage, nloc - tid * kPage));
     if (blockIdx.x == 0 && tid == 0) {
         BfsSlot fresh{};
         fresh.pages = a.static_pages;
@@ -1869,7 +1872,7 @@ __global__ __launch_bounds__(kDeepBlock) void k_bfs_deep(BfsArgs a, int32_t poli
         o.n = nf;
         o.dir_prev = PP_PUSH;
         o.n_prev = n_prev;
-        o.pages = a.static_pages + kGroups * kDeepPages;
+        o.pages = a.static_pages + kGroups * kPages;
         o.m = m;
         o.mu_base = mu_base;
         h->slot[lvl % 3] = o;
@@ -1940,9 +1943,9 @@ static bool deep_for(pp_graph g, int32_t policy) {
 }
 // Are the cooperating workgroups offered the frontiers past what one takes?  On
 // few vertices such a frontier is most of the graph (ER n = 5,001 of degree 4: 124
-// us a switching run without, 131 with them).
+// us a switching run without, 131 with them; n = 40,001 of degree 2 231 and 243).
 static bool deep_shared(pp_graph g) { return g->d.n >= kDeepMinN; }
-constexpr unsigned kDeepLds = 2 * kDeepCap * sizeof(DeepEntry);
+constexpr unsigned kDeepLds = 2 * kDeepCap * sizeof(DeepEntry), kSoloLds = 2 * kSoloCap * sizeof(DeepEntry);
 
 static size_t multi_lds(int32_t qcap) { return (size_t)(6 * qcap + 2) * 4; }
 
@@ -2030,10 +2033,13 @@ static pp_status bfs_graph(pp_graph g, BfsArgs a, int32_t policy, float alpha, f
     for (int32_t i = 0; i <= batch && e == hipSuccess; ++i) {
         if (i == 0 || (deep && (i % kDeepOffer == 0 || i == batch))) {
             if (deep) {
-                int32_t solo = std::min(kSoloMax, g->tune.bfs_multi_n);
-                void* dargs[] = {&a, &policy, &alpha, &beta, &solo};
+                // (what one cooperating workgroup holds, where they take over: a 1000 x
+                // 1031 grid 7.67 ms at 512 edges, 7.80 at 1,024)
+                const int32_t cap = deep_shared(g) ? kDeepCap : kSoloCap;
+                int32_t solo_n = std::min(cap, g->tune.bfs_multi_n), solo_m = std::min(cap, g->tune.bfs_multi_m);
+                void* dargs[] = {&a, &policy, &alpha, &beta, &solo_n, &solo_m};
                 void* iargs[] = {&a};
-                e = add(reinterpret_cast<const void*>(&k_bfs_deep<true>), dargs, 1, kDeepLds, kDeepBlock);
+                e = add(reinterpret_cast<const void*>(&k_bfs_deep<true>), dargs, 1, kSoloLds, kDeepBlock);
                 if (e == hipSuccess && deep_shared(g))
                     e = add(reinterpret_cast<const void*>(&k_bfs_deep_init), iargs, 1, 0, kWave);
                 if (e == hipSuccess && deep_shared(g))

@@ -505,3 +505,30 @@ def test_many_searches_of_a_shallow_low_degree_graph():
             lv, _, levels = oracle.bfs(h.off, h.idx, int(v))
             assert (st.levels, st.reached) == (levels, int((lv >= 0).sum()))
         np.testing.assert_array_equal(r.level.cpu().numpy(), lv)
+
+
+@pytest.mark.parametrize("caps", [(1, 1), (3, 1024), (256, 7), (64, 256), (1024, 1024), (6144, 100000)])
+def test_low_degree_levels_under_any_caps(caps):
+    # frontiers about the caps of the one-workgroup launch and about what it can hold
+    # (1,024 vertices and edges): handed over and back at every size, same search
+    hosts = [gg.grid(300, 301, 0.05, seed=3), gg.grid(40, 400, 0.0, seed=3), _ring_lattice(60000, 2, 3000, 6),
+             H.path(400), gg.grid(60, 60, 0.0, seed=2)]
+    for host in hosts:
+        assert np.diff(host.off).max() <= 16
+        root = int((np.diff(host.off) > 0).argmax())
+        pp._lib.pp_set_bfs_multi(*caps)
+        try:
+            g = pp.Graph(host)
+        finally:
+            pp._lib.pp_set_bfs_multi(256, 1024)
+        want, _, nlev = oracle.bfs(host.off, host.idx, root)
+        for policy in (pp.PP_PUSH, pp.PP_SWITCH):
+            announce(f"low degree caps={caps} n={host.n} policy={policy}")
+            r = pp.BfsRun(g)
+            st, dirs, nf, mf = r.run_logged(root, policy)
+            assert st.levels == nlev
+            lv = r.level.cpu().numpy()
+            np.testing.assert_array_equal(lv, want)
+            np.testing.assert_array_equal(nf, np.bincount(want[want >= 0], minlength=nlev))
+            assert H.bfs_violations_fast(host, root, lv, r.parent.cpu().numpy()) == []
+        g.close()
