@@ -43,6 +43,7 @@ struct KPlan {
     int32_t unit_off[PP_NUM_BINS + 1];  // units per bin, launch order 5, 4, ..., 0
     int32_t list_off[PP_NUM_BINS + 1];
     int32_t units;
+    bool spread3;  // the float4 sweep: a row of bin 3 takes a workgroup, not a wavefront
 };
 
 // Units of a KT-column sweep over a binned vertex list: bins 0-2 put
@@ -62,6 +63,7 @@ static KPlan kplan(const BinPlan& p, int kt) {
     k.unit_off[PP_NUM_BINS] = at;
     k.units = at;
     for (int b = 0; b <= PP_NUM_BINS; ++b) k.list_off[b] = p.list_off[b];
+    k.spread3 = false;
     return k;
 }
 
@@ -330,14 +332,21 @@ static int32_t kplan_bin_units(const KPlan& kp, int b) {
 
 // Units of the float4 sweep over the row-unit plan kp: bins 0-2 put
 // kBlock/(KT/4) rows in a unit, bin 3 one row a wavefront, bin 4 one row, bin 5
-// one chunk.
-static KPlan kplan_pull4(const KPlan& kp, int kt) {
+// one chunk.  Where bin 3 has few rows its longest one is the sweep: they take a
+// workgroup each then (up to two a compute unit; a wavefront takes up to 32 rounds
+// for a row at 64 columns, 16 at 32).  30 sweeps of 100 columns in tiles of 64, a
+// wavefront / a workgroup a row: R-MAT 10 960 / 625 us, 11 1,446 / 615, 12 (298 such
+// rows) 1,332 / 840, 13 (819) 1,204 / 1,214; of 32 columns, R-MAT 12 442 / 355, 13 410
+// / 417; of 8, where a wavefront's round is 256 slots, R-MAT 14 356 / 440.
+static KPlan kplan_pull4(const KPlan& kp, int kt, int32_t num_cu) {
     KPlan k = kp;
+    const int32_t mid = kp.list_off[4] - kp.list_off[3];
+    k.spread3 = kt >= 32 && mid <= 2 * num_cu;
     int32_t at = 0;
     for (int b = PP_NUM_BINS - 1; b >= 0; --b) {
         const int32_t rows = kp.list_off[b + 1] - kp.list_off[b];
-        const int32_t units = (b <= 2) ? ceil_div(rows, kBlock / (kt / 4)) : (b == 3) ? ceil_div(rows, kBlock / kWave)
-                                                                                    : kplan_bin_units(kp, b);
+        const int32_t units = (b <= 2) ? ceil_div(rows, kBlock / (kt / 4)) : (b == 3 && !k.spread3) ? ceil_div(rows, kBlock / kWave)
+                                                                                                  : kplan_bin_units(kp, b);
         k.unit_off[b] = at;
         at += units;
     }
@@ -368,7 +377,7 @@ template <int KT, bool W, typename T>
 __global__ __launch_bounds__(kBlock) void k_kcol_sweep(KArgs a) {
     constexpr int Q = kq_lanes<KT>();
     constexpr int G = kBlock / Q;
-    __shared__ Sum4<T> red4[Q * (kBlock / kWave)];
+    __shared__ Sum4<double> red4[Q * (kBlock / kWave)];
     __shared__ float redf[2 * (kBlock / kWave)];
     if (kt_stopped(a.stop)) return;
     const int q = threadIdx.x % Q;
@@ -385,7 +394,7 @@ __global__ __launch_bounds__(kBlock) void k_kcol_sweep(KArgs a) {
                                            : kt_gather4<KT, 8, W, T>(a, a.off[u], a.off[u + 1], 0, 1, q);
             res = kt_epilogue4<KT, T>(a, u, q, s4_float(acc));
         }
-    } else if (bin == 3) {
+    } else if (bin == 3 && !a.kp.spread3) {
         const int32_t i = lu * (kBlock / kWave) + threadIdx.x / kWave;
         if (i < a.kp.list_off[4] - a.kp.list_off[3]) {
             const int32_t u = a.list[a.kp.list_off[3] + i];
@@ -396,15 +405,20 @@ __global__ __launch_bounds__(kBlock) void k_kcol_sweep(KArgs a) {
             acc = kt_wave_sum4<KT, double>(acc);
             if (grp % GW == 0) res = kt_epilogue4<KT, T>(a, u, q, s4_float(acc));
         }
+    } else if (bin == 3) {
+        const int32_t u = a.list[a.kp.list_off[bin] + lu];
+        Sum4<double> acc = kt_gather4<KT, 8, W, T, double>(a, a.off[u], a.off[u + 1], grp, G, q);
+        acc = kt_block_sum4<KT, double>(acc, reinterpret_cast<Sum4<double>*>(red4));
+        if (threadIdx.x < Q) res = kt_epilogue4<KT, T>(a, u, q, s4_float(acc));
     } else if (bin == 4) {
         const int32_t u = a.list[a.kp.list_off[bin] + lu];
         Sum4<T> acc = kt_gather4<KT, 8, W, T>(a, a.off[u], a.off[u + 1], grp, G, q);
-        acc = kt_block_sum4<KT, T>(acc, red4);
+        acc = kt_block_sum4<KT, T>(acc, reinterpret_cast<Sum4<T>*>(red4));
         if (threadIdx.x < Q) res = kt_epilogue4<KT, T>(a, u, q, s4_float(acc));
     } else {
         const int32_t b = a.tab[a.tab_cap + lu], e = a.tab[2 * a.tab_cap + lu];
         Sum4<T> acc = kt_gather4<KT, 8, W, T>(a, b, e, grp, G, q);
-        acc = kt_block_sum4<KT, T>(acc, red4);
+        acc = kt_block_sum4<KT, T>(acc, reinterpret_cast<Sum4<T>*>(red4));
         if (threadIdx.x < Q) reinterpret_cast<Sum4<T>*>(a.part)[(size_t)lu * Q + q] = acc;
     }
     if (a.resid_part) resid_flush(res, redf, a.resid_part, unit);
@@ -671,13 +685,13 @@ __global__ __launch_bounds__(kBlock) void k_kcol_grad(GradArgs a) {
             const int32_t v = a.list[a.kp.list_off[bin] + i];
             grad_row<KT>(a, v, a.off[v], a.off[v + 1], 0, 1, q);
         }
-    } else if (bin == 3) {
+    } else if (bin == 3 && !a.kp.spread3) {
         const int32_t i = lu * (kBlock / kWave) + threadIdx.x / kWave;
         if (i < a.kp.list_off[4] - a.kp.list_off[3]) {
             const int32_t v = a.list[a.kp.list_off[3] + i];
             grad_row<KT>(a, v, a.off[v], a.off[v + 1], grp % (kWave / Q), kWave / Q, q);
         }
-    } else if (bin == 4) {
+    } else if (bin <= 4) {
         const int32_t v = a.list[a.kp.list_off[bin] + lu];
         grad_row<KT>(a, v, a.off[v], a.off[v + 1], grp, G, q);
     } else {
@@ -885,7 +899,7 @@ static int32_t launch_sweep_t(const KArgs& a, int32_t nsplit, hipStream_t st, bo
 template <int KT>
 static int32_t launch_sweep(pp_graph g, const KArgs& a_rows, int32_t nsplit, hipStream_t st, bool push = false) {
     KArgs a = a_rows;
-    a.kp = kplan_pull4(a_rows.kp, KT);
+    a.kp = kplan_pull4(a_rows.kp, KT, g->num_cu);
     if (!kplan_valid(a_rows.kp) || !kplan_valid(a.kp) || kplan_bin_units(a.kp, 5) != kplan_bin_units(a_rows.kp, 5))
         return -1;  // never launch over an inconsistent plan
     return push ? launch_sweep_t<KT, double>(a, nsplit, st, g->weighted)
@@ -1200,7 +1214,7 @@ static pp_status adjoint_grad(pp_graph g, int32_t k, int32_t col0, float f, cons
     if (launch_sweep<KT>(g, a, w.nsplit, st) < 0)
         return set_error(PP_E_GRAPH, "inconsistent k-column sweep plan");
     GradArgs ga{};
-    ga.kp = kplan_pull4(w.kp, KT);
+    ga.kp = kplan_pull4(w.kp, KT, g->num_cu);
     ga.off = w.off;
     ga.idx = w.idx;
     ga.list = w.list;

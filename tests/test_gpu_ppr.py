@@ -498,3 +498,54 @@ def test_rows_of_every_length_class_all_forms(kt, weighted):
             assert np.abs(got[on, d] - want).sum(axis=0).max() <= 1e-6, (on, d)
         g.close()
     assert np.array_equal(got[1, pp.PP_PULL], got[0, pp.PP_PULL])
+
+
+@pytest.mark.parametrize("rows", [1, 511, 512, 513])
+@pytest.mark.parametrize("kt", [16, 32, 64])
+def test_rows_of_the_fourth_bin_on_wavefronts_and_workgroups(rows, kt):
+    # `rows` vertices of 65 to 1,024 in-edges (up to two a compute unit take a
+    # workgroup each at 32 columns and more, else a wavefront): forwards in both
+    # forms, the adjoint solve and the edge gradient
+    n = 3000
+    rng = np.random.default_rng(rows + kt)
+    deg = np.concatenate([[1024], rng.integers(65, 130, rows - 1)])
+    dst = np.repeat(np.arange(rows), deg)
+    src = np.concatenate([rng.choice(n, d, replace=False) for d in deg])
+    host = gg.from_edges(n, np.concatenate([src, np.arange(n)]), np.concatenate([dst, (np.arange(n) + 1) % n]), False)
+    gg.with_weights(host, seed=3)
+    s = gg.pick_vertices(host, kt, seed=5)
+    want, _ = oracle.ppr(host.off, host.idx, s, F, T=12, weights=host.weights)
+    g = pp.Graph(host)
+    announce(f"fourth bin rows={rows} k_tile={kt}")
+    for d in (pp.PP_PULL, pp.PP_PUSH):
+        X, _ = pp.ppr(g, s, iters=12, f=F, k_tile=kt, direction=d)
+        assert np.abs(X.cpu().numpy().astype(np.float64) - want).sum(axis=0).max() <= 1e-6, d
+    Xs, _ = oracle.ppr(host.off, host.idx, s, F, T=200, weights=host.weights)
+    G = np.random.default_rng(1).normal(size=Xs.shape).astype(np.float32)
+    _, want_g, _ = oracle.ppr_adjoint(host.off, host.idx, Xs, G, F, T=200, weights=host.weights)
+    X32 = torch.as_tensor(Xs.astype(np.float32)).cuda()
+    _, grad, _ = pp.ppr_adjoint(g, X32, torch.as_tensor(G).cuda(), iters=200, f=F, k_tile=kt)
+    err = np.linalg.norm(grad.cpu().numpy().astype(np.float64) - want_g) / np.linalg.norm(want_g)
+    assert err <= 1e-5
+
+
+def test_a_wide_tile_on_a_small_graph():
+    # R-MAT 11 has so little in a sweep that 64 columns take no longer than 16 (310
+    # and 330 us for 30 sweeps); with its few hundred rows of 65 to 1,024 slots on a
+    # wavefront each, 64 columns took 720
+    host = gg.rmat(11, 16, seed=1)
+    g = pp.Graph(host)
+    s = gg.pick_vertices(host, 64, seed=3)
+
+    def best(k):
+        times = []
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            pp.ppr(g, s[:k], iters=30, k_tile=k)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times)
+
+    assert best(64) < 1.5 * best(16)
