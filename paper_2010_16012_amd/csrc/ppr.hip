@@ -373,8 +373,13 @@ static bool kplan_valid(const KPlan& kp) {
 // k = 64 took 168 us a sweep, this takes 124.  Loading the next round's indices
 // ahead is worth most on small graphs, where the longest rows' chains of round
 // trips set the time: R-MAT 16, k = 32 weighted 53 -> 27 us.
-template <int KT, bool W, typename T>
-__global__ __launch_bounds__(kBlock) void k_kcol_sweep(KArgs a) {
+// LEAN: held to the registers of seven wavefronts a SIMD (its 86 allow five), for
+// graphs that have few of those rows and wait for short ones side by side: 700 x 700
+// grid, 64 columns with a test for a tolerance 161 -> 123 us a sweep, ER n = 50,001
+// of degree 16, 30 sweeps of 32 columns 514 -> 436 us; R-MAT 14 to 16 would lose 3 to
+// 5%.  The weighted and FP64 forms would spill.
+template <int KT, bool W, typename T, bool LEAN = false>
+__global__ __launch_bounds__(kBlock, LEAN ? 7 : 1) void k_kcol_sweep(KArgs a) {
     constexpr int Q = kq_lanes<KT>();
     constexpr int G = kBlock / Q;
     __shared__ Sum4<double> red4[Q * (kBlock / kWave)];
@@ -886,7 +891,10 @@ static bool valid_kt(int32_t kt) { return kt == 8 || kt == 16 || kt == 32 || kt 
 template <int KT, typename T>
 static int32_t launch_sweep_t(const KArgs& a, int32_t nsplit, hipStream_t st, bool weighted) {
     if (a.kp.units > 0) {
+        const bool lean = 16 * (int64_t)(a.kp.list_off[PP_NUM_BINS] - a.kp.list_off[3]) <= a.kp.list_off[PP_NUM_BINS];
         if (weighted) hipLaunchKernelGGL((k_kcol_sweep<KT, true, T>), dim3(a.kp.units), dim3(kBlock), 0, st, a);
+        else if (sizeof(T) == 4 && lean)
+            hipLaunchKernelGGL((k_kcol_sweep<KT, false, T, sizeof(T) == 4>), dim3(a.kp.units), dim3(kBlock), 0, st, a);
         else hipLaunchKernelGGL((k_kcol_sweep<KT, false, T>), dim3(a.kp.units), dim3(kBlock), 0, st, a);
     }
     float* resid_fix = a.resid_part ? a.resid_part + 2 * (size_t)a.kp.units : nullptr;
