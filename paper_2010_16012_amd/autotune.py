@@ -5,7 +5,8 @@ Searches, per (GPU architecture, graph size class):
     sweeps);
   * pull sweep: LDS-staged contributions, workgroup size and how many of the
     heaviest rows take the tiled (source-sliced) sweep;
-  * push sweep: LDS-privatised targets and persistent workgroups;
+  * LDS-privatised targets and persistent workgroups, on the sweep that has
+    them: the hybrid, or the push of a graph it is not routed for;
   * BFS direction switch: the alpha/beta constants of the switch rule (on
     roots of their own seed);
   * personalised PageRank: the column tile width for a given k;
@@ -127,8 +128,18 @@ def tune_bins(host, iters=5, log=print) -> dict:
     return {"upper": best[1], "split_chunk": best[2]}
 
 
+def privatised_sweep(n: int, nnz: int) -> int:
+    """The sweep whose time ``hot`` and ``push_blocks`` change: pushes past one
+    workgroup's size that are not routed (fewer than 65,536 edges, more than 2^25
+    vertices or 2^30 edges) privatise their first targets, all other pushes read
+    neither; the hybrid sweep always does."""
+    if n > 10240 and (nnz < 1 << 16 or n > 1 << 25 or nnz > 1 << 30):
+        return PP_PUSH
+    return PP_SWITCH
+
+
 def tune_pagerank(host, iters=5, log=print, base=None) -> dict:
-    """Best pull and push settings for this graph."""
+    """Best pull, push and hybrid settings for this graph."""
     out = dict(base or {})
     x = torch.empty(host.n, dtype=torch.float32, device="cuda")
 
@@ -154,13 +165,15 @@ def tune_pagerank(host, iters=5, log=print, base=None) -> dict:
                     best = (t, pull_hot, block, rows)
     out["pull_hot"], out["pull_block"], out["slice_rows"], out["slice_width"] = best[1], best[2], best[3], 32768
     best = None
+    d = privatised_sweep(host.n, int(host.nnz))
+    name = "push" if d == PP_PUSH else "hybrid"
     for hot in (8192, 16384, 32768, 40960):
         for blocks in ((512, 1024, 2048) if hot <= 16384 else (256, 512)):
             apply({**out, "hot": hot, "push_blocks": blocks})
             g = Graph(host)
-            t = run(g, PP_PUSH)
+            t = run(g, d)
             g.close()
-            log(f"push hot={hot} blocks={blocks}: {t / iters * 1e3:.1f} us/iter")
+            log(f"{name} hot={hot} blocks={blocks}: {t / iters * 1e3:.1f} us/iter")
             if best is None or t < best[0]:
                 best = (t, hot, blocks)
     out["hot"], out["push_blocks"] = best[1], best[2]

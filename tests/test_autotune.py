@@ -68,3 +68,35 @@ def test_bfs_multi_caps_candidates_and_range():
         with pytest.raises(_lib.PPError):
             autotune.apply(bad)
     autotune.apply({})
+
+
+@pytest.mark.parametrize("n,nnz,sweep", [(1 << 20, 1 << 24, "switch"), (8192, 1 << 16, "switch"), (5000, 20000, "switch"),
+                                         (60000, 65535, "push"), (10240, 30000, "switch"), ((1 << 25) + 1, 1 << 28, "push")])
+def test_privatised_targets_are_timed_on_a_sweep_that_has_them(monkeypatch, n, nnz, sweep):
+    # hot and push_blocks are picked by the time of a sweep that reads them: routed
+    # pushes and those of one workgroup do not, the hybrid always does
+    from types import SimpleNamespace
+
+    from paper_2010_16012_amd import PP_PULL, PP_PUSH, PP_SWITCH
+
+    now, timed = {}, []
+
+    def fake_time(fn, reps=3):
+        fn()
+        return timed[-1][1]
+
+    def fake_run(g, x, iters, f, d):
+        # a sweep that privatises is fastest at 32,768 targets and 256 workgroups
+        mine = d == (PP_PUSH if sweep == "push" else PP_SWITCH)
+        t = 1.0 + (abs(now["hot"] - 32768) + abs(now["push_blocks"] - 256)) * 1e-6 if mine else 1.0
+        timed.append((d, t))
+
+    monkeypatch.setattr(autotune, "apply", lambda cfg: now.update({**autotune.DEFAULTS, **cfg}))
+    monkeypatch.setattr(autotune, "Graph", lambda host: SimpleNamespace(close=lambda: None))
+    monkeypatch.setattr(autotune, "pagerank_into", fake_run)
+    monkeypatch.setattr(autotune, "_time", fake_time)
+    monkeypatch.setattr(autotune, "torch", SimpleNamespace(
+        empty=lambda *a, **k: SimpleNamespace(fill_=lambda v: None), float32=None))
+    out = autotune.tune_pagerank(SimpleNamespace(n=n, nnz=nnz), log=lambda m: None)
+    assert (out["hot"], out["push_blocks"]) == (32768, 256)
+    assert {d for d, _ in timed} == {PP_PULL, PP_PUSH if sweep == "push" else PP_SWITCH}
