@@ -532,3 +532,33 @@ def test_low_degree_levels_under_any_caps(caps):
             np.testing.assert_array_equal(nf, np.bincount(want[want >= 0], minlength=nlev))
             assert H.bfs_violations_fast(host, root, lv, r.parent.cpu().numpy()) == []
         g.close()
+
+
+@pytest.mark.parametrize("first", [0, 1, 7, 8, 9, 63, 64, 127, 128, 129, 191, 192, 255, 256, 299])
+def test_bottom_up_long_rows_whose_only_hit_is_at_an_entry(first):
+    # 100 rows of 300 in-edges, the same for all: `first` vertices that nothing
+    # reaches, the one vertex of level 1, and unreached ones again.  The entries one
+    # lane tests (8), the rest of the leading 128, the hand-over to the chunk items
+    # and the items themselves
+    hub, n_rows = 10 + first, 100
+    row0 = 10 + 300
+    ins = 10 + np.arange(300)
+    rows = row0 + np.arange(n_rows)
+    src = np.concatenate([[0], np.tile(ins, n_rows)])
+    dst = np.concatenate([[hub], np.repeat(rows, 300)])
+    h = gg.from_edges(row0 + n_rows, src, dst, False, name=f"only{first}")
+    h.ensure_transpose()
+    level = oracle.bfs(h.off, h.idx, 0)[0]
+    for r in rows:
+        ids = np.asarray(h.in_idx[h.in_off[r]:h.in_off[r + 1]])
+        assert len(ids) == 300 and np.flatnonzero(level[ids] == 1).tolist() == [first] and (level[ids] < 2).all()
+    _check(h, [0], policies=[pp.PP_PULL], fast=True)
+    for rl in (True, False):
+        g = pp.Graph(h, relabel=rl)
+        r = pp.BfsRun(g)
+        r.init(0)
+        for lvl in range(3):
+            r.step(lvl, pp.PP_PULL)
+        np.testing.assert_array_equal(r.level.cpu().numpy(), level)
+        assert (r.parent.cpu().numpy()[rows] == hub).all()
+        g.close()
