@@ -596,3 +596,40 @@ def test_a_wrong_slot_map_leaves_the_pushes_alone():
     for kt in (1, 8):
         X = pp.ppr(g, src, iters=8, f=F, k_tile=kt, direction=pp.PP_PUSH)[0].cpu().numpy().astype(np.float64)
         assert np.abs(X - want).sum(axis=0).max() <= PR_L1_TOL, kt
+
+
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("hot,blocks", [(1, 7), (1, 1024), (100, 333), (8192, 1024), (16384, 3), (16385, 3), (30000, 1000),
+                                        (40960, 256), (0, 64)])
+def test_push_of_graphs_that_are_not_routed(hot, blocks, weighted):
+    # fewer than 65,536 edges on more than 10,240 vertices: pushes are neither routed
+    # nor one workgroup's.  The privatised targets (narrow and wide), the binned
+    # updates past them (four bins of 16,384 at hot = 1) and, with bins off or
+    # hot = 0, the atomics; uniform and single-source (slices left part-filled)
+    if weighted:
+        host = H.random_graph(60000, 60000, 3, symmetric=False, connected=False)
+        gg.with_weights(host, seed=2)
+    else:
+        host = H.random_graph(60000, 32000, 5, symmetric=True)
+    assert host.n > 10240 and 50000 < host.nnz < 65536
+    deg = np.diff(host.off)
+    src = np.argsort(-deg, kind="stable")[:3].astype(np.int32)
+    want, _ = oracle.ppr(host.off, host.idx, src, F, T=12, weights=host.weights)
+    want_x = None if weighted else oracle.pagerank(host.off, host.idx, F, 12)
+    _lib.pp_set_push_tuning(hot, blocks)
+    try:
+        for rl in (True, False):
+            for on in (1, 0):
+                _lib.pp_set_push_bins(on)
+                g = pp.Graph(host, relabel=rl)
+                info = g.push_bins()
+                assert info[0] == (-(-(host.n - hot) // 16384) if on and hot else 0), info
+                announce(f"unrouted push bins={on} hot={hot} blocks={blocks} relabel={rl} weighted={weighted}")
+                X = pp.ppr(g, src, iters=12, f=F, k_tile=1, direction=pp.PP_PUSH)[0].cpu().numpy().astype(np.float64)
+                assert np.abs(X - want).sum(axis=0).max() <= PR_L1_TOL, (rl, on)
+                if want_x is not None:
+                    assert np.abs(pr_gpu(g, pp.PP_PUSH, 12).astype(np.float64) - want_x).sum() <= PR_L1_TOL, (rl, on)
+                g.close()
+    finally:
+        _lib.pp_set_push_tuning(8192, 1024)
+        _lib.pp_set_push_bins(1)
