@@ -157,7 +157,8 @@ pp_status pp_set_push_tuning(int32_t hot, int32_t push_blocks);
 pp_status pp_set_push_bins(int32_t on);
 
 /* The binned-push layout of g: info[0..4) = bins (0: global atomics),
- * first binned target, workgroups of the sweep, units of the summing kernel. */
+ * first binned target, workgroups of the sweep, units of the summing kernel (0 for
+ * graphs whose pushes are buffered by target block: the bins stay unused). */
 pp_status pp_graph_push_bins(pp_graph g, int32_t* info);
 
 /* Pull-sweep tuning: each workgroup of the persistent pull sweep stages the

@@ -1266,14 +1266,14 @@ PP_EXPORT pp_status pp_graph_create(int32_t n, int64_t nnz, const int32_t* csr_o
         const hipError_t e = hipHostMalloc(&g->bfs_hdr_host, pp_graph_s::kBfsHdrHost, hipHostMallocDefault);
         if (e != hipSuccess) return fail(hip_error(e, "pinned BFS header buffer"));
     }
-    if (d.pb_base) {
-        s = build_push_bins(g, st);
-        if (s != PP_OK) return fail(s);
-    }
     // (without owner sums the binned push needs its pairs, where the plan would lie)
     if (route_possible(n, nnz) && g->transposed) {
         hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, st, 1, d.err + 41);
         s = build_route(g, at(L.rt_edges), at(L.rt_tables), st);
+        if (s != PP_OK) return fail(s);
+    }
+    if (d.pb_base) {
+        s = build_push_bins(g, st);
         if (s != PP_OK) return fail(s);
     }
     *out = g;

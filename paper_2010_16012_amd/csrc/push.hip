@@ -345,6 +345,10 @@ pp_status build_push_bins(pp_graph g, hipStream_t st) {
     if (!g->d.pb_base || g->push_plan.total_blocks == 0) return PP_OK;
     const PushShape sh = push_shape(g, true);
     if (sh.hot <= 0 || sh.nbins <= 0 || sh.nbins > push_bins_cap(n) || sh.grid > g->tune.push_blocks) return PP_OK;
+    if (route_for(g, PP_PUSH)) {  // the bins stay unused: their layout, without the walk and its two waits
+        g->pbins = PushBins{sh.nbins, sh.hot, sh.sub, sh.grid, 0};
+        return PP_OK;
+    }
     // walk the sweep's static assignment once, counting each workgroup's
     // updates per bin
     const PushArgs a = push_args(g, nullptr, nullptr, sh);
@@ -395,6 +399,7 @@ pp_status build_push_bins(pp_graph g, hipStream_t st) {
 pp_status launch_push(pp_graph g, const float* c, float* y, hipStream_t st) {
     if (g->push_plan.total_blocks == 0) return PP_OK;
     const bool binned = g->pbins.nbins > 0;
+    if (binned && route_for(g, PP_PUSH)) return set_error(PP_E_GRAPH, "push of a routed graph outside its plan");
     const PushShape sh = push_shape(g, binned);
     if (binned && (sh.hot != g->pbins.hot || sh.nbins != g->pbins.nbins || sh.grid != g->pbins.groups ||
                    sh.sub != g->pbins.sub))

@@ -633,3 +633,16 @@ def test_push_of_graphs_that_are_not_routed(hot, blocks, weighted):
     finally:
         _lib.pp_set_push_tuning(8192, 1024)
         _lib.pp_set_push_bins(1)
+
+
+def test_routed_graphs_are_not_walked_for_bins():
+    # the counting walk of the binned push (a sweep and two waits) is left out at
+    # registration where pushes are routed; it stays where they are not
+    routed, plain = gg.rmat(16, 16, seed=1), H.random_graph(60000, 32000, 5, symmetric=True)
+    assert pp.Graph(routed).push_bins()[0] > 0 and pp.Graph(routed).push_bins()[3] == 0
+    assert pp.Graph(plain).push_bins()[0] > 0 and pp.Graph(plain).push_bins()[3] > 0
+    # ... and where the owner sums are not to be had
+    host = H.random_graph(30000, 200000, 41, symmetric=False, connected=True)
+    host.ensure_transpose()
+    host.in_off, host.in_idx = host.off, host.idx
+    assert host.nnz >= 65536 and pp.Graph(host).push_bins()[3] > 0
