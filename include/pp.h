@@ -151,8 +151,10 @@ pp_status pp_set_push_tuning(int32_t hot, int32_t push_blocks);
  * Partition-Awareness, buffered instead of applied one by one).  On graphs of
  * at least 8192 vertices and 65536 edges (and at most 2^25 vertices) every
  * update, hot targets included, is buffered by target block instead, at a place
- * fixed at registration, and summed there in slot order.  Needs hot >
- * 0; its workspace (8 bytes per edge plus tables) is part of
+ * fixed at registration, and summed there in slot order; not so where registration
+ * finds that the CSC is not the transpose of the CSR (a push reads the CSR alone,
+ * and a caller who only pushes may have registered the CSR arrays twice).  Needs
+ * hot > 0; its workspace (8 bytes per edge plus tables) is part of
  * pp_graph_workspace_bytes.  Takes effect at the next pp_graph_create. */
 pp_status pp_set_push_bins(int32_t on);
 
@@ -209,9 +211,9 @@ pp_status pp_graph_slices(pp_graph g, int32_t* info);
  * P_uv = 1/d(v) (unweighted) or w(v->u)/s(v) (weighted); a vertex with
  * d(v) = 0 contributes nothing.  x, y: float[n], distinct.  pp_pr_push
  * sends every edge's value to its target: through the target block's buffer
- * (graphs of at least 8192 vertices and 65536 edges with pp_set_push_bins(1);
- * fixed summation order; graphs of at most 10240 vertices and some 30000 edges
- * run in one workgroup, likewise), else by scattering along the CSR rows with the
+ * (graphs of at least 8192 vertices and 65536 edges with pp_set_push_bins(1) whose
+ * CSC is the transpose of their CSR; fixed summation order; graphs of at most 10240
+ * vertices and some 30000 edges run in one workgroup, likewise), else by scattering along the CSR rows with the
  * privatised and binned or atomic updates of pp_set_push_tuning and
  * pp_set_push_bins (the summation order, hence the last bits, may vary between
  * runs).  pp_pr_pull gathers along CSC rows with no atomics
@@ -233,7 +235,11 @@ pp_status pp_pr_run(pp_graph g, pp_dir dir, int32_t iters, float f, float* x_ino
 
 /* -------------------------------------------------------------------- BFS */
 /* BFS state: frontier queues, frontier and visited bitmaps and counters
- * (device memory, caller-owned).  Size in bytes for graph g. */
+ * (device memory, caller-owned).  Size in bytes for graph g.  Every wavefront of
+ * a level has queue pages of its own, and a level takes a workgroup to 4,096
+ * vertices or 8,192 edges, up to one a compute unit: small dense graphs take more
+ * than their vertices say (R-MAT scale 16, edge factor 16: 31 MB; 4 MB if counted
+ * by vertices alone). */
 size_t pp_bfs_state_bytes(pp_graph g);
 
 /* Statistics of one BFS run (host struct). */
@@ -342,8 +348,9 @@ size_t pp_ppr_scratch_bytes(pp_graph g, int32_t k, int32_t k_tile);
  * moves one coalesced k_tile-float row.  dir PP_PULL gathers along CSC (no
  * atomics, deterministic, FP32 sums), PP_PUSH delivers every update to its
  * target's owner, who sums in FP64 along the CSC list of what is sent to it
- * (deterministic); with pp_set_push_bins(0) it scatters along CSR with FP64
- * atomics into an FP64 accumulator instead.  PP_SWITCH applies the Generic-Switch strategy of
+ * (deterministic); with pp_set_push_bins(0), or where the CSC is not the
+ * transpose of the CSR, it scatters along CSR with FP64 atomics into an FP64
+ * accumulator instead.  PP_SWITCH applies the Generic-Switch strategy of
  * Sec. 5: while the tile's support (the vertices within t hops of its
  * sources) has at most m/14 out-edges, a sweep pushes from the support only
  * (sparse matrix times sparse vector along CSR, Sec. 7.1, FP64 atomics);

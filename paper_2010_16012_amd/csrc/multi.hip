@@ -14,8 +14,9 @@
 // graphs waited for the largest alone (a scale-14 R-MAT graph: 134 us a sweep,
 // 2.7 of the 3.1 ms of a 128-graph batch, most of the chip idle).  Where a graph
 // has more than kStepEdges edges and is more than its share (steps_pay) the
-// PageRank steps therefore run as one launch each (k_multi_step), the rows of all graphs shared among one workgroup per
-// compute unit: 40 us a step there, 1.07 ms in all.
+// PageRank steps therefore run as one launch each (k_multi_step), the rows of all
+// graphs shared among one workgroup per compute unit: 40 us a step there, 1.07 ms
+// in all.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -13,7 +13,7 @@
 // written to both slots without a search.  k_tc_slices then sums the counts of
 // each row's slots; a slot without one (two short rows, a directed edge to a longer
 // row that has no edge back) is intersected there.  What bounds it: LDS bit tests and
-// the barriers between a slice's rows.  R-MAT 16 (163M tests): 0.35 ms a call,
+// the barriers between a slice's rows.  R-MAT 16 (163M tests): 0.34 ms a call,
 // against 20.3 ms with a wavefront per 256 edges that searched or merged both
 // directions of every pair in global memory.
 //
