@@ -85,10 +85,10 @@ size_t pp_graph_workspace_bytes(int32_t n, int64_t nnz, uint32_t flags);
  * and csc_to_csr (int32[nnz], the CSR slot of each CSC slot).  ws: device
  * workspace of at least pp_graph_workspace_bytes(n, nnz, flags) bytes, kept
  * by the handle until pp_graph_destroy; it also holds the owner (row) of
- * every in-adjacency slot, which streamed bottom-up BFS levels use.  Where csc
- * aliases csr but the graph is not symmetric, or csc_to_csr is not the slot map,
- * pushing sweeps keep to the out-rows (elsewhere the targets' owners may sum
- * what is pushed along the in-rows).  SYNC (reads back bin sizes). */
+ * every in-adjacency slot, which streamed bottom-up BFS levels use.  Where the
+ * csc does not hold the csr's edges (checked by sums of hashes), or csc_to_csr is
+ * not the slot map, pushing sweeps keep to the out-rows (elsewhere the targets'
+ * owners may sum what is pushed along the in-rows).  SYNC (reads back bin sizes). */
 pp_status pp_graph_create(int32_t n, int64_t nnz,
                           const int32_t* csr_off, const int32_t* csr_idx,
                           const int32_t* csc_off, const int32_t* csc_idx,

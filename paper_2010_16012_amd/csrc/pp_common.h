@@ -297,8 +297,7 @@ struct pp_graph_s {
     int32_t empty_in;            // vertices without in-edges
     // The in-adjacency is the transpose: what a push sends may be summed by the
     // targets' owners over their in-edges.  Not so for a caller who only pushes
-    // and gave the out-arrays of a directed graph twice (other in-arrays are taken
-    // to be what they are said to be), or a slot map that is none.
+    // and gave the out-arrays of a directed graph twice, or a slot map that is none.
     bool transposed;
     int32_t num_cu;              // compute units of the device the graph lives on
     int32_t max_lds;             // LDS bytes one workgroup may allocate

@@ -584,6 +584,55 @@ def test_pushing_a_directed_graph_given_its_out_arrays_twice(n, m, weighted):
         g.close()
 
 
+@pytest.mark.parametrize("n,m", [(3, 4), (700, 5000), (30000, 200000), (70000, 300000)])
+def test_pushing_a_directed_graph_given_in_arrays_of_its_own(n, m):
+    # the same where the in-arrays are other memory: a copy of the out-arrays, and
+    # the transpose but for one edge, whose source is another vertex; with the
+    # transpose itself, for comparison, the owners sum
+    host = H.random_graph(n, m, 47, symmetric=False, connected=False)
+    host.ensure_transpose()
+    src = gg.pick_vertices(host, 1, seed=5)
+    want, _ = oracle.ppr(host.off, host.idx, src, F, T=8)
+    want_x = oracle.pagerank(host.off, host.idx, F, 8)
+    in_off, in_idx = host.in_off, host.in_idx
+    other = in_idx.copy()
+    at = host.nnz // 2
+    other[at] = (other[at] + 1) % n
+    for name, off, idx in (("copy", host.off.copy(), host.idx.copy()), ("one edge", in_off, other),
+                           ("transpose", in_off, in_idx)):
+        host.in_off, host.in_idx = off, idx
+        for rl in (True, False):
+            g = pp.Graph(host, relabel=rl)
+            announce(f"in-arrays: {name} n={n} relabel={rl}")
+            for kt in (1, 8):
+                X = pp.ppr(g, src, iters=8, f=F, k_tile=kt, direction=pp.PP_PUSH)[0].cpu().numpy().astype(np.float64)
+                assert np.abs(X - want).sum(axis=0).max() <= PR_L1_TOL, (name, rl, kt)
+            assert np.abs(pr_gpu(g, pp.PP_PUSH, 8).astype(np.float64) - want_x).sum() <= PR_L1_TOL, (name, rl)
+            g.close()
+
+
+def test_a_slot_map_that_serves_one_slot_twice_leaves_the_pushes_alone():
+    # parallel edges of different weights, both in-slots mapped to one of them
+    rng = np.random.default_rng(53)
+    n = 20000
+    s = rng.integers(0, n, 80000)
+    t = rng.integers(0, n, 80000)
+    off = np.concatenate([[0], np.cumsum(2 * np.bincount(s, minlength=n))]).astype(np.int64)
+    host = gg.HostGraph(n, off, np.repeat(t[np.argsort(s, kind="stable")], 2).astype(np.int32), False, name="parallel")
+    host.ensure_transpose()
+    host.weights = (0.5 + rng.random(host.nnz)).astype(np.float32)
+    src = gg.pick_vertices(host, 2, seed=5)
+    want, _ = oracle.ppr(host.off, host.idx, src, F, T=8, weights=host.weights)
+    host.in_to_out = (host.in_to_out // 2 * 2).astype(np.int32)
+    for rl in (True, False):
+        g = pp.Graph(host, relabel=rl)
+        announce(f"slot map with repeats relabel={rl}")
+        for kt in (1, 8):
+            X = pp.ppr(g, src, iters=8, f=F, k_tile=kt, direction=pp.PP_PUSH)[0].cpu().numpy().astype(np.float64)
+            assert np.abs(X - want).sum(axis=0).max() <= PR_L1_TOL, (rl, kt)
+        g.close()
+
+
 def test_a_wrong_slot_map_leaves_the_pushes_alone():
     # a symmetric weighted graph whose in-slots are mapped to themselves: the
     # weights of the out-slots are the ones that a push sends
