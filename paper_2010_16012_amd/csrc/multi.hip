@@ -430,10 +430,11 @@ struct StepArgs {
 // One PageRank step of every graph: a workgroup stages the contributions of a
 // piece's graph in LDS and pulls the piece's rows as k_multi does (the pushing
 // form too, where the in-arrays are the transpose: an FP64 sum over the in-edges
-// is what the FP64 adds of the out-edges come to, rounded once).  Bound by latency: the pieces' rows of a 128-graph batch are 32 MB of
-// ids, 5 us at the rate of memory.  Laying the gathered values down in slot order
-// and summing rows from there took 73 to 100 us a step against 74 of this form,
-// before the shares knew what a graph costs.
+// is what the FP64 adds of the out-edges come to, rounded once).  Bound by latency:
+// the pieces' rows of a 128-graph batch are 32 MB of ids, 5 us at the rate of
+// memory.  Laying the gathered values down in slot order and summing rows from
+// there took 73 to 100 us a step against 74 of this form, before the shares knew
+// what a graph costs.
 template <int PG, int ML>
 __global__ __launch_bounds__(kMultiBlock) void k_multi_step(StepArgs a) {
     extern __shared__ __align__(16) float s_c[];  // [largest n]
