@@ -535,18 +535,24 @@ PP_EXPORT pp_status pp_tc_run(pp_graph g, pp_dir dir, int64_t* tc, void* ws, siz
     // in a sparse graph, where looking for the pairs costs more than they do (ER
     // n = 2M of degree 4: 750 us looked for, 570 without)
     const int32_t longest = g->max_out_deg;
-    const bool count = longest > kTcLight && !(longest <= kTcMid && a.nnz < 8 * (int64_t)a.n);
+    const bool sparse = longest <= kTcLight || (longest <= kTcMid && a.nnz < 8 * (int64_t)a.n);
+    // few slices leave most of the chip idle: what counts then is that a slice has a
+    // workgroup instead of the wavefront of k_tc_slices, and one launch does it all
+    // (ER, degree x n, us a call without / with: 4 x 5,591 60 / 46, 8 x 5,591 76 / 60,
+    // 16 x 20,001 117 / 89, 4 x 80,001 68 / 59; level at 8 x 45,001 and 12 x 65,535)
+    a.window = (int32_t)std::min<int64_t>(((int64_t)a.n + 63) / 64 * 64, kTcWindow);
+    const size_t lds = (size_t)a.window / 8;
+    const bool few = lds <= kTcWide && a.slices <= (sparse ? 5 : 12) * g->num_cu;
+    const bool count = few || !sparse;
     a.cnt = count ? reinterpret_cast<int32_t*>(w + L.cnt) : nullptr;
     // (k_tc_slices alone is as well off with its bounded search: grids 25% faster by
     // the list, sparse ER 10% slower)
     a.row = count && !g->relabelled && g->d.aliased ? g->d.csc_row : nullptr;
-    a.window = (int32_t)std::min<int64_t>(((int64_t)a.n + 63) / 64 * 64, kTcWindow);
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int32_t vb = std::max(1, std::min(ceil_div(a.n, kBlock), 4096));
     const int32_t zb = std::max(1, std::min(ceil_div(std::max<int64_t>(a.n, a.nnz), kBlock), 4096));
     hipLaunchKernelGGL(k_tc_zero, dim3(zb), dim3(kBlock), 0, st, a);
     if (a.slices > 0) {
-        const size_t lds = (size_t)a.window / 8;
         // (a bitmap of kTcWidest bytes leaves a compute unit two workgroups, which
         // still is the better form where most pairs need one: R-MAT 18 1.7 ms, 2.3 in
         // two launches; ER n = 300,000 of degree 40 needs none: 2.6 -> 1.6 ms)
@@ -559,10 +565,10 @@ PP_EXPORT pp_status pp_tc_run(pp_graph g, pp_dir dir, int64_t* tc, void* ws, siz
             const int32_t wgs = g->num_cu * 16 * (1024 / tc_threads(lds));
             hipLaunchKernelGGL(kern, dim3(std::min(a.slices, wgs)), dim3(tc_threads(lds)), lds, st, a);
         };
-        if (count && longest <= kTcMid) {
-            search(&k_tc_count<kTcMid, true, false>);
-        } else if (!count) {
+        if (!count) {
             // k_tc_slices alone
+        } else if (longest <= kTcMid && !few) {
+            search(&k_tc_count<kTcMid, true, false>);
         } else if (lds <= kTcWide || (lds <= kTcWidest && longest > kTcMidWide && a.nnz >= 8 * (int64_t)a.n)) {
             with_bits(&k_tc_count<kTcMid, true, true>);
         } else {

@@ -155,6 +155,20 @@ def test_no_row_needs_a_bitmap(d):
     _same(gg.from_edges(n, np.tile(k, len(ring)), np.concatenate(ring), True, name=f"ring{d}"))
 
 
+@pytest.mark.parametrize("n,d", [(1, 0), (3, 2), (100, 40), (5_000, 2), (5_000, 16), (5_000, 18), (5_000, 64),
+                                 (20_481, 16), (20_479, 16), (49_152, 18), (49_151, 18)])
+def test_few_slices_have_a_workgroup_each(n, d):
+    # small graphs without rows for a bitmap, to both sides of the edge counts from
+    # which they are summed without counts (327,680 edges) or searched alone (786,432;
+    # with 256 compute units), and a directed graph whose pairs are met one way
+    k = np.arange(n)
+    ring = [(k + s) % n for s in range(1, d // 2 + 1)]
+    src, dst = np.tile(k, len(ring)), np.concatenate(ring) if ring else np.zeros(0, int)
+    _same(gg.from_edges(n, src, dst, True, name=f"ring{n}_{d}"))
+    if 100 < n <= 20_000:
+        _same(gg.from_edges(n, src, dst, False, name=f"arcs{n}_{d}").ensure_transpose())
+
+
 def test_sparse_graphs_are_not_charged_for_bitmaps():
     # a grid of a million vertices has no row for a bitmap: counting its triangles
     # (134 us) is less work than 20 PageRank steps (350 us), and was more (504 us)
