@@ -374,10 +374,13 @@ static bool kplan_valid(const KPlan& kp) {
 // ahead is worth most on small graphs, where the longest rows' chains of round
 // trips set the time: R-MAT 16, k = 32 weighted 53 -> 27 us.
 // LEAN: held to the registers of seven wavefronts a SIMD (its 86 allow five), for
-// graphs that have few of those rows and wait for short ones side by side: 700 x 700
-// grid, 64 columns with a test for a tolerance 161 -> 123 us a sweep, ER n = 50,001
-// of degree 16, 30 sweeps of 32 columns 514 -> 436 us; R-MAT 14 to 16 would lose 3 to
-// 5%.  The weighted and FP64 forms would spill.
+// graphs that have none of those rows and wait for short ones side by side: 700 x 700
+// grid, 64 columns with a test for a tolerance 161 -> 123 us a sweep; 30 sweeps of 32
+// columns 1,419 -> 1,323 us there, ER n = 100,001 of degree 6 566 -> 530, n = 500,001
+// of degree 2 1,303 -> 1,151.  A row's chain is longer with fewer registers: where
+// even one row in a thousand is long, 30 sweeps lose 2 to 4% (R-MAT 10 to 18, edge
+// factors 1 to 8), and 2 to 3% where a tenth of the rows pass 16 slots (ER n = 250,001
+// of degree 16).  The weighted and FP64 forms would spill.
 template <int KT, bool W, typename T, bool LEAN = false>
 __global__ __launch_bounds__(kBlock, LEAN ? 7 : 1) void k_kcol_sweep(KArgs a) {
     constexpr int Q = kq_lanes<KT>();
@@ -891,7 +894,8 @@ static bool valid_kt(int32_t kt) { return kt == 8 || kt == 16 || kt == 32 || kt 
 template <int KT, typename T>
 static int32_t launch_sweep_t(const KArgs& a, int32_t nsplit, hipStream_t st, bool weighted) {
     if (a.kp.units > 0) {
-        const bool lean = 16 * (int64_t)(a.kp.list_off[PP_NUM_BINS] - a.kp.list_off[3]) <= a.kp.list_off[PP_NUM_BINS];
+        const int32_t* at = a.kp.list_off;  // no row of bins 3-5, hardly any of bin 2
+        const bool lean = at[PP_NUM_BINS] == at[3] && 64 * (int64_t)(at[3] - at[2]) <= at[3];
         if (weighted) hipLaunchKernelGGL((k_kcol_sweep<KT, true, T>), dim3(a.kp.units), dim3(kBlock), 0, st, a);
         else if (sizeof(T) == 4 && lean)
             hipLaunchKernelGGL((k_kcol_sweep<KT, false, T, sizeof(T) == 4>), dim3(a.kp.units), dim3(kBlock), 0, st, a);
